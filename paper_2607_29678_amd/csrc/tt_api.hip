@@ -153,8 +153,8 @@ struct tt_tokenizer {
   int device = 0;
   int profile = 0;  // calls whose stage events are kept (0: no events)
   u64x2* d_slots = nullptr;    // cuckoo buckets
-  uint32_t nb = 0;             // merge-table buckets
-  uint32_t* d_pair0 = nullptr;  // [65536] byte-pair ranks
+  uint32_t shift = 0;          // merge-table buckets: 2^(32 - shift)
+  PairJ* d_pairj = nullptr;    // [65536] byte pairs: rank, lowest junction rank
   u32x4* d_dict = nullptr;      // whole-unit dictionary
   uint32_t dnb = 0;             // dictionary buckets
   u32x4* d_dict2 = nullptr;     // long-unit dictionary
@@ -629,7 +629,7 @@ int handle_pattern(const tt_tokenizer* h) { return h->pattern; }
 int handle_device(const tt_tokenizer* h) { return h->device; }
 bool handle_ignore(const tt_tokenizer* h) { return h->ignore; }
 DevTables handle_tables(const tt_tokenizer* h) {
-  return DevTables{h->d_slots, h->nb,     h->d_pair0,  h->d_join,  h->d_ext,   h->n_ids,
+  return DevTables{h->d_slots, h->shift,     h->d_pairj,  h->d_join,  h->d_ext,   h->n_ids,
                    h->d_dict,  h->dnb,    h->d_dict2,  h->dnb2,    h->d_toklen, h->vmax,
                    h->d_vdict, h->vdnb,   h->d_vdict2, h->vdnb2,   h->d_vlong, h->vlnb,
                    h->d_vblob};
@@ -779,18 +779,24 @@ int tt_create_ex(const tt_merge* merges, int32_t n_merges, const uint8_t* vocab_
     toklen[256 + (size_t)n_merges + j] = l > 0xFFFFFFFFll ? 0xFFFFFFFFu : (uint32_t)l;
   }
 
-  // byte-pair ranks, and the two-choice cuckoo table of all pairs (two slots
-  // per bucket, load 0.8; the table grows by 1/8 while an insertion cannot be
-  // placed)
-  std::vector<uint32_t> pair0(65536, RANK_INF);
+  // byte pairs (their ranks, and the lowest rank of a merge across their
+  // boundary), and the two-choice cuckoo table of all pairs (two slots
+  // per bucket, load at most 0.8; the table doubles while an insertion cannot
+  // be placed)
+  std::vector<PairJ> pairj(65536, PairJ{RANK_INF, RANK_INF});
   for (int32_t r = 0; r < n_merges; ++r) {
     const int32_t a = internal[merges[r].left], b = internal[merges[r].right];
-    if (a < 256 && b < 256) pair0[((uint32_t)a << 8) | (uint32_t)b] = (uint32_t)r;
+    if (a < 256 && b < 256) pairj[((uint32_t)a << 8) | (uint32_t)b].rank = (uint32_t)r;
+    // (operands are never empty: each is a byte or spells its own operands)
+    const uint32_t x = vptr(merges[r].left)[vlen(merges[r].left) - 1], y = vptr(merges[r].right)[0];
+    PairJ& e = pairj[(x << 8) | y];
+    e.low = std::min(e.low, (uint32_t)r);
   }
-  uint32_t nb = (uint32_t)((uint64_t)n_merges * 5 / 8) + 16;
+  uint32_t shift = 32 - 5;
+  while (((uint64_t)1 << (32 - shift)) < (uint64_t)n_merges * 5 / 8) --shift;
   std::vector<uint64_t> slots;
   for (;;) {
-    slots.assign(2 * (size_t)nb, SLOT_EMPTY);
+    slots.assign((size_t)2 << (32 - shift), SLOT_EMPTY);
     uint64_t rng = 0x9E3779B97F4A7C15ull;
     bool ok = true;
     for (int32_t r = 0; r < n_merges && ok; ++r) {
@@ -799,7 +805,7 @@ int tt_create_ex(const tt_merge* merges, int32_t n_merges, const uint8_t* vocab_
       ok = false;
       for (int kick = 0; kick < 1000; ++kick) {
         const uint32_t a = (uint32_t)(item & ID_LIMIT), b = (uint32_t)((item >> ID_BITS) & ID_LIMIT);
-        const uint32_t b1 = bucket_of(pair_hash(a, b), nb), b2 = bucket_of(pair_hash2(a, b), nb);
+        const uint32_t b1 = pair_bucket(a, b, shift), b2 = pair_bucket2(a, b, shift);
         size_t free_at = SIZE_MAX;
         for (size_t c : {2 * (size_t)b1, 2 * (size_t)b1 + 1, 2 * (size_t)b2, 2 * (size_t)b2 + 1})
           if (slots[c] == SLOT_EMPTY) {
@@ -819,8 +825,7 @@ int tt_create_ex(const tt_merge* merges, int32_t n_merges, const uint8_t* vocab_
       }
     }
     if (ok) break;
-    nb += nb / 8;
-    if (nb > (1u << 28)) return TT_ERR_OOM;
+    if (--shift < 32 - 28) return TT_ERR_OOM;
   }
 
   // whole-unit dictionaries: every byte string of 3..DICT2_MAX bytes that is
@@ -954,13 +959,8 @@ int tt_create_ex(const tt_merge* merges, int32_t n_merges, const uint8_t* vocab_
   // boundary has its junction exactly there, so a boundary whose byte pair is
   // no merge's junction is never crossed
   std::vector<uint32_t> join(2048, 0u);
-  for (int32_t r = 0; r < n_merges; ++r) {
-    if (vlen(merges[r].left) == 0 || vlen(merges[r].right) == 0) continue;
-    uint32_t x = vptr(merges[r].left)[vlen(merges[r].left) - 1];
-    uint32_t y = vptr(merges[r].right)[0];
-    uint32_t key = (x << 8) | y;
-    join[key >> 5] |= 1u << (key & 31u);
-  }
+  for (uint32_t key = 0; key < 65536u; ++key)
+    if (pairj[key].low != RANK_INF) join[key >> 5] |= 1u << (key & 31u);
 
   tt_tokenizer* h = new tt_tokenizer();
   h->pattern = pattern_id;
@@ -972,7 +972,7 @@ int tt_create_ex(const tt_merge* merges, int32_t n_merges, const uint8_t* vocab_
   h->added = std::move(added);
   h->n_merges = n_merges;
   h->vocab_size = vocab_size;
-  h->nb = nb;
+  h->shift = shift;
   h->dnb = dnb;
   h->dnb2 = dnb2;
   h->n_ids = n_ids;
@@ -984,8 +984,8 @@ int tt_create_ex(const tt_merge* merges, int32_t n_merges, const uint8_t* vocab_
     delete h;
     return TT_ERR_HIP;
   }
-  if (hipMalloc(reinterpret_cast<void**>(&h->d_slots), 16 * (size_t)nb) != hipSuccess ||
-      hipMalloc(reinterpret_cast<void**>(&h->d_pair0), sizeof(uint32_t) * 65536) != hipSuccess ||
+  if (hipMalloc(reinterpret_cast<void**>(&h->d_slots), sizeof(uint64_t) * slots.size()) != hipSuccess ||
+      hipMalloc(reinterpret_cast<void**>(&h->d_pairj), sizeof(PairJ) * 65536) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&h->d_dict), sizeof(u32x4) * dict.size()) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&h->d_dict2), sizeof(u32x4) * dict2.size()) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&h->d_ext), sizeof(int32_t) * n_ids) != hipSuccess ||
@@ -1009,8 +1009,8 @@ int tt_create_ex(const tt_merge* merges, int32_t n_merges, const uint8_t* vocab_
     tt_destroy(h);
     return TT_ERR_HIP;
   }
-  if (hipMemcpy(h->d_slots, slots.data(), 16 * (size_t)nb, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(h->d_pair0, pair0.data(), sizeof(uint32_t) * 65536, hipMemcpyHostToDevice) != hipSuccess ||
+  if (hipMemcpy(h->d_slots, slots.data(), sizeof(uint64_t) * slots.size(), hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(h->d_pairj, pairj.data(), sizeof(PairJ) * 65536, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(h->d_dict, dict.data(), sizeof(u32x4) * dict.size(), hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(h->d_dict2, dict2.data(), sizeof(u32x4) * dict2.size(), hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(h->d_ext, ext.data(), sizeof(int32_t) * n_ids, hipMemcpyHostToDevice) != hipSuccess ||
@@ -1030,7 +1030,7 @@ void tt_destroy(tt_tokenizer* h) {
   for (auto& kv : h->ws) free_ws(kv.second);
   if (h->d_slots) (void)hipFree(h->d_slots);
   if (h->d_ext) (void)hipFree(h->d_ext);
-  if (h->d_pair0) (void)hipFree(h->d_pair0);
+  if (h->d_pairj) (void)hipFree(h->d_pairj);
   if (h->d_dict) (void)hipFree(h->d_dict);
   if (h->d_dict2) (void)hipFree(h->d_dict2);
   if (h->d_toklen) (void)hipFree(h->d_toklen);

@@ -10,11 +10,11 @@
 // merging them one by one, and after a merge only the pairs that touch the new
 // token need a new rank lookup.  The unit length picks the execution unit
 // (Sec. 4.2 dispatches by piece length):
-//   bpe_thread  <= 16 bytes: one thread, the unit in registers;
-//   bpe_wave    <= 64 bytes: one wave64, one token per lane;
-//   bpe_pair32  two units of <= 32 bytes: one wave64, one unit per half;
-//   bpe_rows    longer:      NW waves over rows of 64 tokens in LDS or global
-//                            memory.
+//   bpe_lanes   <= 64 bytes:  one wave64 holds 8 units of <= 8 bytes, 4 of <= 16,
+//                             2 of <= 32 or one of <= 64, one byte per lane;
+//   bpe_wave2   <= 128 bytes: one wave64, two tokens per lane;
+//   bpe_rows    longer:       NW waves over rows of 64 tokens in LDS or global
+//                             memory.
 // IDs are internal: byte b is b, the result of merge r is 256 + r.
 #pragma once
 
@@ -69,174 +69,150 @@ __device__ __forceinline__ uint32_t wave_incl_sum(uint32_t v) {
 }
 
 // ---------------------------------------------------------------------------
-// One thread, at most 16 bytes.  The unit's tokens live in its own LDS words
-// ids[0..L) (the caller puts the bytes there; merged tokens overwrite their
-// left operand in place, and the tokens end compacted in ids[0..count)).  The
-// rank of the pair at slot j is kept in LDS at rk[j * TH_THREADS]: the caller
-// passes its own column of a [SMALL_MAX - 1][TH_THREADS] array (the last slot
-// never has a pair), so the lanes of a wave never share a bank.  A rank is
-// kept as (rank << 4) | j, so that one unsigned minimum finds the lowest rank
-// and, among equal ranks (the same pair), the leftmost occurrence; a merge
-// rewrites at most three slots with three stores.  A merge clears the right
-// token's bit in an alive mask instead of shifting the tail.  The chain is one
-// round trip for the initial byte pairs (all loads in flight at once) and one
-// per merge (its two neighbour lookups overlap).  Returns the number of tokens.
+// Units of at most 64 bytes: 64 / W units on one wave64, W lanes per unit (W is
+// 8, 16, 32 or 64, the same for the whole wave), one byte position per lane.
+//
+// A token stays at the lane of its first byte and the lanes of its other bytes
+// are dead, so a round moves no token: a merge changes the left token's ID and
+// clears the right token's bit in the wave's alive mask (a scalar), and every
+// lane finds the tokens after it from that mask.  Lane i holds the rank of the
+// pair (token i, next token).
+//
+// Which pairs a round merges.  Merging only the lowest rank of the unit makes
+// the number of rounds the number of different ranks (14 on average for units
+// of 17..32 bytes of multilingual text).  But no merge ever crosses the byte
+// boundary (x, y) with a rank below J(x, y), the lowest rank among the merges
+// whose left operand ends in x and whose right operand starts with y
+// (DevTables::pairj).  So when a pair's rank r is below J at the boundary before
+// its left token and below J at the boundary after its right one, its two
+// tokens are cut off from the rest of the unit until rank r is reached: they
+// merge with each other then, whatever happens elsewhere before, and merging
+// them now gives the same result.  A round merges all such pairs and the
+// occurrences of the unit's lowest rank (leftmost first, without overlap).
+// Two pairs taken in one round never share a token unless they are occurrences
+// of the lowest rank: J at the boundary inside a pair is at most its rank.
+// Rounds per unit, multilingual text: 13.7 -> 6.1 (17..32 bytes), 9.9 -> 5.0
+// (13..16), 6.8 -> 4.1 (9..12); agent transcript: 17.0 -> 9.4, 11.8 -> 6.5,
+// 7.7 -> 4.4.  A round is bound by instruction issue when every wave of
+// a compute unit is in this loop (five waves per SIMD at four cycles an
+// instruction), else by latency: one L2 round trip for the rank lookups.
+// Engine phase of a tile, mean / slowest, against one thread per unit of 3..16
+// bytes and one or two units per wave merging lowest ranks only: 1M-character
+// agent transcript 8.4 / 19.5 -> 4.4 / 10.8 us, multilingual 14.7 / 29.6 ->
+// 9.9 / 20.7 us; a 16M-character corpus 414 -> 351 us (whole calls).
+//
+// L is the length of the calling lane's unit (0: none), byte the byte at the
+// lane's position in it.  On return id is the token at the calling lane's
+// position if the lane is set in the returned mask.  Every lane of the wave
+// calls it.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t bpe_thread(uint32_t L, uint32_t* ids, uint32_t* rk, const DevTables& tb) {
-  constexpr int S = SMALL_MAX;
-  constexpr int ST = TH_THREADS;
-  const u64x2* __restrict__ tab = tb.slots;
-  const uint32_t nb = tb.nb;
+
+// Minimum over the W lanes of the calling lane's group, in every lane of it.
+__device__ __forceinline__ uint32_t group_min_u32(uint32_t v, uint32_t W) {
+  // (an old value of all ones is the identity of the minimum, which lets the
+  // lane move fuse with it)
+#define TT_MIN_DPP(ctrl) v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, ctrl, 0xF, 0xF, false))
+  TT_MIN_DPP(0xB1);   // quad_perm 1,0,3,2
+  TT_MIN_DPP(0x4E);   // quad_perm 2,3,0,1
+  TT_MIN_DPP(0x141);  // row_half_mirror
+  if (W > 8u) TT_MIN_DPP(0x140);  // row_mirror
+#undef TT_MIN_DPP
+  if (W > 16u) {  // rows 0 and 1, rows 2 and 3
+    const auto p = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    v = min((uint32_t)p[0], (uint32_t)p[1]);
+  }
+  if (W > 32u) {  // the two halves
+    const auto p = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    v = min((uint32_t)p[0], (uint32_t)p[1]);
+  }
+  return v;
+}
+
+// Trailing zeros, all ones for zero (one instruction).
+__device__ __forceinline__ uint32_t ffbl(uint32_t x) { return (uint32_t)__builtin_ffs((int)x) - 1u; }
+
+// WIDE: W is 64 (a unit spans both halves of the wave); else a unit lies in
+// one half, and the masks a lane looks at are one word.
+template <bool WIDE>
+__device__ __forceinline__ uint64_t bpe_lanes(uint32_t W, uint32_t L, uint32_t byte, const DevTables& tb,
+                                              uint32_t& id) {
+  const uint32_t lane = threadIdx.x & 63u;
+  const uint32_t j = lane & (W - 1u);  // byte position in the unit
+  const uint32_t half = lane & 32u;
+  // the unit's lanes after this one, as a mask of the wave (WIDE) or of the half
+  const uint64_t above64 = ~((2ull << lane) - 1ull);
+  const uint32_t h = lane & 31u;
+  const uint32_t above = (W >= 32u ? ~0u : (((1u << W) - 1u) << (h - j))) & ~((2u << h) - 1u);
+  id = byte;
+  uint32_t rk = RANK_INF, jr = RANK_INF;  // J at the boundary after this byte
   {
-    uint32_t b[S], r[S - 1];
-#pragma unroll
-    for (int j = 0; j < S; ++j) b[j] = (uint32_t)j < L ? ids[j] : 0u;
-    // every initial rank load is issued before any is used (no branches)
-#pragma unroll
-    for (int j = 0; j < S - 1; ++j) r[j] = tb.pair0[(b[j] << 8) | b[j + 1]];
-#pragma unroll
-    for (int j = 0; j < S - 1; ++j)
-      rk[j * ST] = ((uint32_t)(j + 1) < L && r[j] != RANK_INF) ? ((r[j] << 4) | (uint32_t)j) : RANK_INF;
-  }
-  uint32_t alive = (1u << L) - 1u;  // L <= 16
-  for (;;) {
-    uint32_t best = RANK_INF;
-#pragma unroll
-    for (int j = 0; j < S - 1; ++j) best = min(best, rk[j * ST]);
-    if (best == RANK_INF) break;
-    const uint32_t k = best & 15u;
-    const uint32_t nid = 256u + (best >> 4);
-    // token k absorbs the next live token m
-    const uint32_t m = (uint32_t)__builtin_ctz(alive & ~((2u << k) - 1u));
-    alive &= ~(1u << m);
-    const uint32_t above_m = alive & ~((2u << m) - 1u);
-    const uint32_t below_k = alive & ((1u << k) - 1u);
-    const bool hr = above_m != 0u, hl = below_k != 0u;
-    const uint32_t right = ids[hr ? (uint32_t)__builtin_ctz(above_m) : k];
-    const uint32_t l_i = hl ? 31u - (uint32_t)__builtin_clz(below_k) : k;
-    const uint32_t left = ids[l_i];
-    ids[k] = nid;
-    // both lookups are issued unconditionally (a missing neighbour looks up a
-    // harmless pair) so that their four loads are in flight together
-    const ProbeIssued pr = probe_issue(tab, nb, nid, right);
-    const ProbeIssued pl = probe_issue(tab, nb, left, nid);
-    const uint32_t rr = hr ? probe_finish(pr, nid, right) : RANK_INF;
-    const uint32_t rl = probe_finish(pl, left, nid);
-    if (m < (uint32_t)(S - 1)) rk[m * ST] = RANK_INF;
-    rk[k * ST] = rr == RANK_INF ? RANK_INF : ((rr << 4) | k);
-    if (hl) rk[l_i * ST] = rl == RANK_INF ? RANK_INF : ((rl << 4) | l_i);
-  }
-  // compact in place: the c-th live token moves to ids[c], c <= its slot
-  uint32_t c = 0;
-  for (uint32_t al = alive; al; al &= al - 1u) ids[c++] = ids[__builtin_ctz(al)];
-  return c;
-}
-
-// ---------------------------------------------------------------------------
-// One wave64, at most 64 bytes: lane i holds token i and the rank of the pair
-// (i, i+1).  A round is a wave minimum, one ballot, the closed-form leftmost
-// non-overlapping choice, a push permute that compacts the survivors, and the
-// rank lookups of the changed pairs (one probe round trip).  Every lane of the
-// wave calls it with the same arguments.
-// ---------------------------------------------------------------------------
-template <class ByteF, class OutF>
-__device__ __forceinline__ uint32_t bpe_wave(uint32_t L, ByteF byte, const DevTables& tb, OutF out) {
-  const int lane = (int)(threadIdx.x & 63u);
-  uint32_t n = L;  // <= 64
-  uint32_t id = (uint32_t)lane < n ? byte(lane) : 0u;
-  uint32_t idn = (uint32_t)__shfl_down((int)id, 1, 64);
-  uint32_t rk = (uint32_t)lane + 1u < n ? tb.pair0[(id << 8) | idn] : RANK_INF;
-  for (;;) {
-    const uint32_t m = wave_min_u32(rk);
-    if (m == RANK_INF) break;
-    const uint64_t sel = leftmost_nonoverlapping(__ballot(rk == m));
-    const uint64_t valid = n >= 64u ? ~0ull : ((1ull << n) - 1ull);
-    const uint64_t keep = valid & ~(sel << 1);
-    const bool me_sel = (sel >> lane) & 1ull;
-    const bool nx_sel = lane < 63 && ((sel >> (lane + 1)) & 1ull);
-    const uint32_t nid = me_sel ? 256u + m : id;
-    const uint32_t r = (me_sel || nx_sel) ? RANK_DIRTY : rk;
-    // at least one pair merged, so at most 63 tokens survive and lane 63 is
-    // free to take the values of the lanes that do not survive
-    const int dest = ((keep >> lane) & 1ull) ? (int)bits_below(keep) : 63;
-    id = (uint32_t)__builtin_amdgcn_ds_permute(dest << 2, (int)nid);
-    const uint32_t r2 = (uint32_t)__builtin_amdgcn_ds_permute(dest << 2, (int)r);
-    n = (uint32_t)__popcll(keep);
-    idn = (uint32_t)__shfl_down((int)id, 1, 64);
-    rk = RANK_INF;
-    if ((uint32_t)lane < n) {
-      rk = r2;
-      if (r2 == RANK_DIRTY) rk = (uint32_t)lane + 1u < n ? probe_rank(tb.slots, tb.nb, id, idn) : RANK_INF;
+    const uint32_t idn = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((lane + 1u) << 2), (int)id);
+    if (j + 1u < L) {
+      const PairJ e = tb.pairj[(id << 8) | idn];
+      rk = e.rank;
+      jr = e.low;
     }
   }
-  if ((uint32_t)lane < n) out(lane, id);
-  return n;
-}
-
-// ---------------------------------------------------------------------------
-// Two units of at most 32 bytes on one wave64: lanes 0..31 hold the tokens of
-// unit A, lanes 32..63 those of unit B, and each half runs the rounds of
-// bpe_wave on its own unit (its own minimum, occurrences and compaction) until
-// both are done; a half whose unit is done keeps its lanes in place.  The pair
-// (lane 31, lane 32) is never a pair: the rank at lane 31 is always RANK_INF.
-// byte(h, j) and out(h, j, id) take the half (0: A, 1: B) and the position in
-// it.  Returns count(A) | count(B) << 16.  Every lane of the wave calls it
-// with the same arguments.
-// ---------------------------------------------------------------------------
-// Minimum over the calling lane's half (32 lanes) of a wave: complete in
-// lanes 31 and 63 (the row steps of wave_min_u32, then one row broadcast
-// into rows 1 and 3).
-__device__ __forceinline__ uint32_t half_min_u32(uint32_t v) {
-  int x = (int)v;
-  x = (int)min((uint32_t)x, (uint32_t)__builtin_amdgcn_update_dpp(x, x, 0xB1, 0xF, 0xF, false));   // quad_perm 1,0,3,2
-  x = (int)min((uint32_t)x, (uint32_t)__builtin_amdgcn_update_dpp(x, x, 0x4E, 0xF, 0xF, false));   // quad_perm 2,3,0,1
-  x = (int)min((uint32_t)x, (uint32_t)__builtin_amdgcn_update_dpp(x, x, 0x141, 0xF, 0xF, false));  // row_half_mirror
-  x = (int)min((uint32_t)x, (uint32_t)__builtin_amdgcn_update_dpp(x, x, 0x140, 0xF, 0xF, false));  // row_mirror
-  x = (int)min((uint32_t)x, (uint32_t)__builtin_amdgcn_update_dpp(x, x, 0x142, 0xA, 0xF, false));  // row_bcast15 into rows 1, 3
-  return (uint32_t)x;
-}
-
-template <class ByteF, class OutF>
-__device__ __forceinline__ uint32_t bpe_pair32(uint32_t LA, uint32_t LB, ByteF byte, const DevTables& tb, OutF out) {
-  const int lane = (int)(threadIdx.x & 63u);
-  const uint32_t h = (uint32_t)lane >> 5;  // 0: unit A, 1: unit B
-  const uint32_t j = (uint32_t)lane & 31u;  // position in the half
-  const uint64_t half = h ? 0xFFFFFFFF00000000ull : 0x00000000FFFFFFFFull;
-  uint32_t n = h ? LB : LA;  // tokens of this half's unit (<= 32)
-  uint32_t id = j < n ? byte(h, j) : 0u;
-  uint32_t idn = (uint32_t)__shfl_down((int)id, 1, 64);
-  uint32_t rk = j + 1u < n ? tb.pair0[(id << 8) | idn] : RANK_INF;
-  for (;;) {
-    const uint32_t mh = half_min_u32(rk);
-    const uint32_t mA = (uint32_t)__builtin_amdgcn_readlane((int)mh, 31);
-    const uint32_t mB = (uint32_t)__builtin_amdgcn_readlane((int)mh, 63);
-    if (mA == RANK_INF && mB == RANK_INF) break;
-    const uint32_t m = h ? mB : mA;
-    const bool active = m != RANK_INF;  // this half merges this round
-    const uint64_t sel = leftmost_nonoverlapping(__ballot(active && rk == m));
-    const uint64_t keep = __ballot(j < n) & ~(sel << 1);
-    const bool me_sel = (sel >> lane) & 1ull;
-    const bool nx_sel = j < 31u && ((sel >> (lane + 1)) & 1ull);
-    const uint32_t nid = me_sel ? 256u + m : id;
-    const uint32_t r = (me_sel || nx_sel) ? RANK_DIRTY : rk;
-    // a half that merged at least one pair has a free last lane for the
-    // lanes that do not survive; a half that merged none stays in place
-    const bool kept = (keep >> lane) & 1ull;
-    const int dest = kept ? (int)(32u * h + bits_below(keep & half)) : active ? (int)(32u * h + 31u) : lane;
-    id = (uint32_t)__builtin_amdgcn_ds_permute(dest << 2, (int)nid);
-    const uint32_t r2 = (uint32_t)__builtin_amdgcn_ds_permute(dest << 2, (int)r);
-    n = (uint32_t)__popcll(keep & half);
-    idn = (uint32_t)__shfl_down((int)id, 1, 64);
-    rk = RANK_INF;
-    if (j < n) {
-      rk = r2;
-      if (r2 == RANK_DIRTY) rk = j + 1u < n ? probe_rank(tb.slots, tb.nb, id, idn) : RANK_INF;
-    }
+  const uint32_t jl = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((lane + 63u) << 2), (int)jr);
+  const uint32_t bl = j == 0u ? RANK_INF : jl;  // J at the boundary before this byte
+  // the lower of the two bounds of the pair that starts here
+  uint32_t bd = bl;
+  {
+    const uint32_t b2 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)((lane + 2u) << 2), (int)bl);
+    if (j + 2u < L) bd = min(bd, b2);
   }
-  if (j < n) out(h, j, id);
-  const uint32_t cA = (uint32_t)__builtin_amdgcn_readlane((int)n, 0);
-  const uint32_t cB = (uint32_t)__builtin_amdgcn_readlane((int)n, 32);
-  return cA | (cB << 16);
+  uint64_t alive = __ballot(j < L);
+  for (;;) {
+    const uint32_t m = group_min_u32(rk, W);
+    if (__ballot(m != RANK_INF) == 0ull) break;
+    uint64_t sel = __ballot(rk < bd) | (__ballot(rk == m) & __ballot(rk != RANK_INF));
+    // the token after each chosen one: adding at the position above it carries
+    // through the dead lanes up to the next live one
+    uint64_t nx = ((sel << 1) + ~alive) & alive;
+    if (nx & sel) {
+      // overlapping occurrences (a run of one token): every second one from
+      // the start of the run; the tokens of a run are equally long
+      const uint64_t upto = sel & ~nx & ((2ull << lane) - 1ull);
+      const uint32_t s = upto ? 63u - (uint32_t)__builtin_clzll(upto) : lane;
+      const uint64_t x = alive & above64;
+      const uint32_t span = x ? (uint32_t)__builtin_ctzll(x) - lane : 1u;
+      const bool odd = (((lane - s) / span) & 1u) != 0u;
+      sel &= ~(nx & __ballot(odd));
+      nx = ((sel << 1) + ~alive) & alive;
+    }
+    alive &= ~nx;
+    const bool me_sel = __builtin_amdgcn_inverse_ballot_w64(sel);
+    id = me_sel ? 256u + rk : id;
+    // the next two live tokens of the unit, and whether the next one merged
+    uint32_t n1, n2;
+    bool has1, has2, nsel;
+    if (WIDE) {
+      const uint64_t x1 = alive & above64, x2 = x1 & (x1 - 1ull);
+      has1 = x1 != 0ull;
+      has2 = x2 != 0ull;
+      n1 = has1 ? (uint32_t)__builtin_ctzll(x1) : lane;
+      n2 = has2 ? (uint32_t)__builtin_ctzll(x2) : lane;
+      nsel = (sel >> n1) & 1ull;
+    } else {
+      const uint32_t ah = half ? (uint32_t)(alive >> 32) : (uint32_t)alive;
+      const uint32_t sh = half ? (uint32_t)(sel >> 32) : (uint32_t)sel;
+      const uint32_t x1 = ah & above, x2 = x1 & (x1 - 1u);
+      has1 = x1 != 0u;
+      has2 = x2 != 0u;
+      n1 = ffbl(x1);  // (all ones for none: the permutes and the shift take it modulo 32)
+      n2 = ffbl(x2);
+      nsel = (sh >> (n1 & 31u)) & 1u;
+      n1 = (n1 & 31u) | half;
+      n2 = (n2 & 31u) | half;
+    }
+    const uint32_t idn = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(n1 << 2), (int)id);
+    const uint32_t b2 = (uint32_t)__builtin_amdgcn_ds_bpermute((int)(n2 << 2), (int)bl);
+    bd = has2 ? min(bl, b2) : bl;
+    const bool pair = __builtin_amdgcn_inverse_ballot_w64(alive) && has1;
+    rk = pair ? rk : RANK_INF;
+    if (pair && (me_sel || nsel)) rk = probe_rank(tb, id, idn);
+  }
+  return alive;
 }
 
 // ---------------------------------------------------------------------------
@@ -261,8 +237,8 @@ __device__ __forceinline__ uint32_t bpe_wave2(uint32_t L, ByteF byte, const DevT
     return lane == 63 ? head1 : nx;
   };
   uint32_t nx0 = next0(), nx1 = (uint32_t)__shfl_down((int)id1, 1, 64);
-  uint32_t rk0 = l0 + 1u < n ? tb.pair0[(id0 << 8) | nx0] : RANK_INF;
-  uint32_t rk1 = l1 + 1u < n ? tb.pair0[(id1 << 8) | nx1] : RANK_INF;
+  uint32_t rk0 = l0 + 1u < n ? tb.pairj[(id0 << 8) | nx0].rank : RANK_INF;
+  uint32_t rk1 = l1 + 1u < n ? tb.pairj[(id1 << 8) | nx1].rank : RANK_INF;
   for (;;) {
     const uint32_t m = wave_min_u32(min(rk0, rk1));
     if (m == RANK_INF) break;
@@ -296,9 +272,9 @@ __device__ __forceinline__ uint32_t bpe_wave2(uint32_t L, ByteF byte, const DevT
     nx0 = next0();
     nx1 = (uint32_t)__shfl_down((int)id1, 1, 64);
     rk0 = r0;
-    if (r0 == RANK_DIRTY) rk0 = l0 + 1u < n ? probe_rank(tb.slots, tb.nb, id0, nx0) : RANK_INF;
+    if (r0 == RANK_DIRTY) rk0 = l0 + 1u < n ? probe_rank(tb, id0, nx0) : RANK_INF;
     rk1 = r1;
-    if (r1 == RANK_DIRTY) rk1 = l1 + 1u < n ? probe_rank(tb.slots, tb.nb, id1, nx1) : RANK_INF;
+    if (r1 == RANK_DIRTY) rk1 = l1 + 1u < n ? probe_rank(tb, id1, nx1) : RANK_INF;
   }
   if (l0 < n) out(lane, id0);
   if (l1 < n) out(64 + lane, id1);
@@ -333,7 +309,7 @@ __device__ uint32_t bpe_rows(uint32_t L, ByteF byte, const DevTables& tb, uint32
 
   for (uint32_t i = tid; i < n; i += NT) I0[i] = byte(i);
   __syncthreads();
-  for (uint32_t i = tid; i < n; i += NT) R0[i] = i + 1 < n ? tb.pair0[(I0[i] << 8) | I0[i + 1]] : RANK_INF;
+  for (uint32_t i = tid; i < n; i += NT) R0[i] = i + 1 < n ? tb.pairj[(I0[i] << 8) | I0[i + 1]].rank : RANK_INF;
   __syncthreads();
 
   for (;;) {
@@ -433,7 +409,7 @@ __device__ uint32_t bpe_rows(uint32_t L, ByteF byte, const DevTables& tb, uint32
     n = n2;
     // 4. ranks of the pairs next to the merges
     for (uint32_t i = tid; i < n; i += NT) {
-      if (R2[i] == RANK_DIRTY) R2[i] = i + 1 < n ? probe_rank(tb.slots, tb.nb, I2[i], I2[i + 1]) : RANK_INF;
+      if (R2[i] == RANK_DIRTY) R2[i] = i + 1 < n ? probe_rank(tb, I2[i], I2[i + 1]) : RANK_INF;
     }
     __syncthreads();
     cur ^= 1;

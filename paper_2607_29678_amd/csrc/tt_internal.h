@@ -65,47 +65,39 @@ __device__ __forceinline__ uint32_t wave_uniform(uint32_t x) {
 // bucket count; the high bits of a multiplicative hash are the good ones).
 __host__ __device__ inline uint32_t bucket_of(uint32_t h, uint32_t nb) { return (uint32_t)(((uint64_t)h * nb) >> 32); }
 
-// Two bucket hashes of a pair (multiplicative).
-__host__ __device__ inline uint32_t pair_hash(uint32_t a, uint32_t b) { return (a * 0x9E3779B1u + b) * 0x85EBCA77u; }
-__host__ __device__ inline uint32_t pair_hash2(uint32_t a, uint32_t b) {
-  return ((b * 0xC2B2AE3Du) ^ (a + 0x165667B1u)) * 0x27D4EB2Fu;
-}
-
 // The merge table is a two-choice cuckoo table of 16-byte buckets holding
 // two slots each: a pair lives in one of the two buckets its hashes name, so
 // every lookup is exactly two independent 16-byte loads (one memory round
 // trip, no probe chain).  Pairs of two bytes, the only pairs before any
-// merge, also have a direct 64 K-entry rank table.
+// merge, also have a direct 64 K-entry table (PairJ).
+//
+// The two hashes of a pair are sums of 24-bit products (internal IDs have 21
+// bits, so they cost two full-rate instructions each; a 32-bit product takes
+// four times as long) and the bucket is their top bits: the bucket count is
+// 2^(32 - shift), at a load of 0.4 to 0.8.
+constexpr uint32_t PAIR_K[4] = {0x9E3779u, 0xC2B2AFu, 0x85EBCBu, 0xD6E8FDu};
+__host__ __device__ inline uint32_t mul24(uint32_t a, uint32_t k) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return (uint32_t)__umul24(a, k);
+#else
+  return a * k;  // (both below 2^24: the low 32 bits of the product)
+#endif
+}
+__host__ __device__ inline uint32_t pair_bucket(uint32_t a, uint32_t b, uint32_t shift) {
+  return (mul24(a, PAIR_K[0]) + mul24(b, PAIR_K[1])) >> shift;
+}
+__host__ __device__ inline uint32_t pair_bucket2(uint32_t a, uint32_t b, uint32_t shift) {
+  return (mul24(a, PAIR_K[2]) + mul24(b, PAIR_K[3])) >> shift;
+}
+
 typedef uint64_t u64x2 __attribute__((ext_vector_type(2)));
 
-struct ProbeIssued {
-  u64x2 x, y;
+// What a byte pair (x, y) says before any merge: the rank of merging the two
+// bytes, and the lowest rank among all merges across a boundary between a
+// token that ends in x and one that starts with y (RANK_INF: none).
+struct PairJ {
+  uint32_t rank, low;
 };
-__device__ __forceinline__ ProbeIssued probe_issue(const u64x2* __restrict__ tab, uint32_t nb, uint32_t a,
-                                                   uint32_t b) {
-  return ProbeIssued{tab[bucket_of(pair_hash(a, b), nb)], tab[bucket_of(pair_hash2(a, b), nb)]};
-}
-// Only the high word of the matching slot is kept (key bits 32..41 below the
-// rank): no empty slot matches, because no internal ID has all 21 bits set.
-__device__ __forceinline__ uint32_t probe_finish(const ProbeIssued& p, uint32_t a, uint32_t b) {
-  const uint32_t klo = a | (b << ID_BITS), khi = b >> (32 - ID_BITS);
-  constexpr uint32_t HI_KEY = (1u << (2 * ID_BITS - 32)) - 1u;
-  uint32_t hi = 0xFFFFFFFFu;
-  auto check = [&](uint64_t v) {
-    const uint32_t vh = (uint32_t)(v >> 32);
-    hi = ((uint32_t)v == klo && (vh & HI_KEY) == khi) ? vh : hi;
-  };
-  check(p.x.x);
-  check(p.x.y);
-  check(p.y.x);
-  check(p.y.y);
-  return hi == 0xFFFFFFFFu ? RANK_INF : hi >> (2 * ID_BITS - 32);
-}
-// Rank of the pair (a, b), or RANK_INF if no merge joins it.
-__device__ __forceinline__ uint32_t probe_rank(const u64x2* __restrict__ tab, uint32_t nb, uint32_t a,
-                                               uint32_t b) {
-  return probe_finish(probe_issue(tab, nb, a, b), a, b);
-}
 
 // Whole-unit dictionary: a unit of 3..DICT_MAX bytes whose BPE is a single
 // token is found with one lookup.  An entry holds the unit's bytes (zero
@@ -193,8 +185,8 @@ __host__ __device__ inline uint32_t long_hash_final(uint32_t h, uint32_t len) {
 // Everything a kernel needs to know about a tokenizer handle.
 struct DevTables {
   const u64x2* slots;       // cuckoo buckets of two slots: key (left | right << 21), rank in bits 42..63
-  uint32_t nb;              // bucket count
-  const uint32_t* pair0;    // [65536] rank of the byte pair (x << 8 | y), or RANK_INF
+  uint32_t shift;           // 32 - log2(bucket count)
+  const PairJ* pairj;       // [65536] of the byte pair (x << 8 | y)
   const uint32_t* join;     // [2048] bit (x << 8 | y): some merge joins a token ending
                             // in byte x to a token starting with byte y
   const int32_t* ext_id;    // [n_ids] caller's ID of every internal ID
@@ -214,6 +206,29 @@ struct DevTables {
   uint32_t vlnb;
   const uint8_t* vblob;     // bytes of the longer strings
 };
+
+// Rank of the pair (a, b), or RANK_INF if no merge joins it.  Only the high
+// word of the matching slot is kept (key bits 32..41 below the rank): no empty
+// slot matches, because no internal ID has all 21 bits set.  Ranks have 21
+// bits, so the shift that takes the key bits off can be an arithmetic one,
+// which leaves all ones (no match) as they are.
+static_assert(MAX_MERGES < (1u << 21), "the sign bit of a slot's high word is free");
+__device__ __forceinline__ uint32_t probe_rank(const DevTables& tb, uint32_t a, uint32_t b) {
+  const u64x2* __restrict__ tab = tb.slots;
+  const u64x2 x = tab[pair_bucket(a, b, tb.shift)], y = tab[pair_bucket2(a, b, tb.shift)];
+  const uint32_t klo = a | (b << ID_BITS), khi = b >> (32 - ID_BITS);
+  constexpr uint32_t HI_KEY = (1u << (2 * ID_BITS - 32)) - 1u;
+  uint32_t hi = 0xFFFFFFFFu;
+  auto check = [&](uint64_t v) {
+    const uint32_t vh = (uint32_t)(v >> 32);
+    hi = ((uint32_t)v == klo && (vh & HI_KEY) == khi) ? vh : hi;
+  };
+  check(x.x);
+  check(x.y);
+  check(y.x);
+  check(y.y);
+  return (uint32_t)((int32_t)hi >> (2 * ID_BITS - 32));
+}
 
 // ---------------------------------------------------------------------------
 // Control words of a workspace.  Nothing is cleared between calls: every call
@@ -268,9 +283,8 @@ constexpr int PT_HALO = 32;                        // context bytes each side
 constexpr int PT_OWN = PT_WIN - 2 * PT_HALO;       // bytes a tile decides
 constexpr int PT_PAD = 8;  // LDS arrays also hold window positions [-8, 0) and [PT_WIN, PT_WIN + 16)
 
-constexpr int SMALL_MAX = 16;                      // thread-per-unit limit (bytes)
-constexpr int TH_THREADS = 256;                    // threads of a tile that run the thread engine
-constexpr int WAVE_MAX = 128;                      // wave-per-unit limit (bytes)
+constexpr int SMALL_MAX = 16;                      // units listed by exact length (bytes)
+constexpr int WAVE_MAX = 128;                      // longest unit that one wave encodes (bytes)
 constexpr int ROWS_LDS = 480;                      // longer units: rows in LDS up to this length
 
 inline uint32_t n_tiles_for(uint32_t n) { return (n + PT_OWN - 1) / PT_OWN; }

@@ -271,6 +271,7 @@ __device__ uint32_t piece_find(const DevTables& tb, const uint8_t* buf, int64_t 
   return DICT_NONE;
 }
 
+constexpr int SMALL_CAP = PT_OWN / 3 + 2;              // units of 3..SMALL_MAX bytes in a tile (the incoming one too)
 constexpr int MED_CAP = PT_WIN / (SMALL_MAX + 1) + 2;  // units of 17..WAVE_MAX bytes in a tile
 // wave units are taken longest first, in classes of 8 bytes
 constexpr int MED_CLASSES = (WAVE_MAX - SMALL_MAX + 7) / 8;
@@ -303,7 +304,7 @@ union PhaseMem {
   struct {
     uint32_t tok[PT_WIN];     // tokens of unit k at tok[ustart[k] ..]
     uint16_t uoff[PT_WIN];    // first output of each unit within the tile
-    uint16_t small[PT_OWN + 2];  // units of 3..16 bytes, sorted by length
+    uint16_t small[SMALL_CAP];  // units of 3..16 bytes, sorted by length
     union {
       uint32_t wscr[PT_THREADS / 64][256];  // wave engine for 65..128 bytes: one area per wave
       struct {                              // block engine for 129..ROWS_LDS bytes
@@ -311,7 +312,6 @@ union PhaseMem {
         uint64_t sel[ROWS_LDS / 64 + 2];
       } rows;
     } x;
-    uint32_t rk[SMALL_MAX - 1][TH_THREADS];  // thread engine: pair ranks, one column per thread
   } b;
 };
 
@@ -327,10 +327,9 @@ struct PtShared {
   uint32_t hist[SMALL_MAX + 1];  // small units per length, then where each length starts
   uint32_t hmed[MED_CLASSES];    // wave units per length class, then where each class starts
   uint32_t n_small, n_med, n_big;
-  uint32_t med_next;             // next wave unit to take
+  uint32_t pass_next;            // next pass of the wave engines to take (in steps of 64)
   uint32_t wave_tot[PT_THREADS / 64];
   uint32_t tile;
-  uint32_t inc_ids[SMALL_MAX];  // the incoming unit's tokens (thread engine)
   uint32_t s_prev;            // start of the incoming unit
   uint32_t prefix;            // outputs of all earlier tiles
   uint32_t err;               // invalid input in this tile or an earlier one
@@ -565,7 +564,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
   if (tid == 0) {
     sh.tile = ticket - w.ticket_base;
     sh.n_med = 0;
-    sh.med_next = 0;
+    sh.pass_next = 0;
     sh.n_big = 0;
     sh.inc_cnt = 0;
     sh.ws_pend = -1;
@@ -1525,15 +1524,13 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
 
   // ---- BPE dispatch ---------------------------------------------------------
   // Units of one or two bytes are finished here, and so are units of up to 24
-  // bytes found in the whole-unit dictionaries.  Other units of 3..16 bytes go to
-  // one thread each, counting-sorted by length, so that the threads of a wave
-  // hold units of similar length (a wave runs as long as its longest unit).
-  // Units of 17..WAVE_MAX bytes go to one wave each, longest first, to the
-  // waves as they become free (no block barrier between the two engines), and
-  // longer units to the whole block.
+  // bytes found in the whole-unit dictionaries.  Other units of up to WAVE_MAX
+  // bytes go to the wave engines: those of 3..16 bytes counting-sorted by
+  // length (units that share a wave should take about as many rounds), longer
+  // ones in 8-byte classes.  Longer units go to the whole block.
   constexpr int UPT = (PT_OWN + 1 + PT_THREADS - 1) / PT_THREADS;  // units per thread
   const uint32_t U = m_proc + (has_inc ? 1u : 0u);
-  uint32_t mine[UPT];  // thread and wave units: (length << 16) | position within its length class
+  uint32_t mine[UPT];  // units of the wave engines: (length << 16) | position within its length class
 #pragma unroll
   for (int r = 0; r < UPT; ++r) {
     mine[r] = 0;
@@ -1567,7 +1564,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
       uint32_t c = 1, t0 = b0, t1 = 0;
       if (L == 2u) {
         const uint32_t b1 = inc_u ? inc_byte_own(1) : sh.buf[PT_PAD + a + 1];
-        const uint32_t r2 = tb.pair0[(b0 << 8) | b1];
+        const uint32_t r2 = tb.pairj[(b0 << 8) | b1].rank;
         if (r2 != RANK_INF) {
           t0 = 256u + r2;
         } else {
@@ -1654,87 +1651,78 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
   const uint32_t n_small = wave_uniform(sh.n_small), n_med = wave_uniform(sh.n_med);
 
   TT_PHASE(6);
-  // thread per unit, on the first TH_THREADS threads
-  if (tid < TH_THREADS) {
-    uint32_t* rk = &sh.ph.b.rk[0][tid];
-#pragma unroll 1
-    for (uint32_t i = tid; i < n_small; i += TH_THREADS) {
-      const uint32_t u = sh.ph.b.small[i];
-      const bool inc_u = u == U_INCOMING;
-      // a unit's own window slots hold its tokens while it is encoded (the
-      // incoming unit's are in inc_ids); one call site, so that a wave does
-      // not run the merge loop twice when it holds the incoming unit
-      const uint32_t a = inc_u ? 0u : sh.ustart[u];
-      const uint32_t L = inc_u ? L_inc : sh.ustart[u + 1] - a;
-      uint32_t* ids = inc_u ? sh.inc_ids : &sh.ph.b.tok[a];
-      for (uint32_t j = 0; j < L; ++j) ids[j] = inc_u ? inc_byte(j) : (uint32_t)sh.buf[PT_PAD + a + j];
-      const uint32_t c = bpe_thread(L, ids, rk, tb);
-      if (inc_u) {
-        for (uint32_t j = 0; j < c; ++j) inc_out(j, ids[j]);
-        sh.inc_cnt = c;
-      } else {
-        sh.ucnt[u] = (uint16_t)c;
-      }
-    }
-  }
-
-  // wave per unit: the units are taken longest first from a shared queue,
-  // each by the next wave that is free (the waves with thread work join when
-  // it is done), so that no wave runs two long units while another idles
+  // The wave engines.  A pass is what a wave encodes at once: one unit of
+  // 65..128 bytes, one of 33..64, two of 17..32, four of 9..16 or eight of
+  // 3..8.  Passes are ordered by the units' length, longest first (they take
+  // the most rounds); a wave's first pass is the one of its own number, and
+  // the waves take the others from a shared counter as they become free.
   {
+    const uint32_t n2 = wave_uniform(sh.hmed[med_class(64)]);        // units of 65..128 bytes
+    const uint32_t b32 = wave_uniform(sh.hmed[med_class(32)]);       // first unit of 17..32 bytes
+    const uint32_t n8 = wave_uniform(sh.hist[9]);                    // units of 3..8 bytes
+    const uint32_t p64 = b32, p32 = p64 + (n_med - b32 + 1u) / 2u;   // passes up to each width
+    const uint32_t p16 = p32 + (n_small - n8 + 3u) / 4u, p8 = p16 + (n8 + 7u) / 8u;
+    uint32_t i = wave_uniform((uint32_t)wave);
 #pragma unroll 1
-    for (;;) {
+    while (i < p8) {
+      if (i < n2) {
+        const uint32_t u = wave_uniform(sh.med[i]);
+        const bool inc_u = u == U_INCOMING;
+        const uint32_t a = inc_u ? 0u : sh.ustart[u];
+        const uint32_t L = inc_u ? L_inc : sh.ustart[u + 1] - a;
+        const uint32_t c = bpe_wave2(
+            L,
+            [&](int j) -> uint32_t {
+              return inc_u ? inc_byte((uint32_t)j) : (uint32_t)sh.buf[PT_PAD + a + (uint32_t)j];
+            },
+            tb, sh.ph.b.x.wscr[wave],
+            [&](int j, uint32_t id) {
+              if (inc_u) inc_out((uint32_t)j, id);
+              else sh.ph.b.tok[a + (uint32_t)j] = id;
+            });
+        if (lane == 0) {
+          if (inc_u) sh.inc_cnt = c;
+          else sh.ucnt[u] = (uint16_t)c;
+        }
+      } else {
+        // the lane's unit: entry k of its list, counted so that the longest
+        // come first (the short units' list is in ascending order)
+        const uint32_t W = i < p64 ? 64u : i < p32 ? 32u : i < p16 ? 16u : 8u;
+        const uint32_t g = (uint32_t)lane / W;
+        uint32_t k, e;
+        if (W >= 32u) {
+          k = W == 64u ? i : b32 + 2u * (i - p64) + g;
+          e = n_med;
+        } else {
+          k = W == 16u ? 4u * (i - p32) + g : n_small - n8 + 8u * (i - p16) + g;
+          e = W == 16u ? n_small - n8 : n_small;
+        }
+        const uint16_t* list = W >= 32u ? sh.med : sh.ph.b.small;
+        const bool has = k < e;
+        const uint32_t u = has ? list[W >= 32u ? k : n_small - 1u - k] : 0u;
+        const bool inc_u = has && u == U_INCOMING;
+        const uint32_t a = !has || inc_u ? 0u : sh.ustart[u];
+        const uint32_t L = !has ? 0u : inc_u ? L_inc : sh.ustart[u + 1] - a;
+        const uint32_t j = (uint32_t)lane & (W - 1u);
+        uint32_t id = 0u;
+        if (j < L) id = inc_u ? inc_byte(j) : (uint32_t)sh.buf[PT_PAD + a + j];
+        const uint64_t alive = W == 64u ? bpe_lanes<true>(64u, L, id, tb, id) : bpe_lanes<false>(W, L, id, tb, id);
+        const uint64_t own = alive & (W == 64u ? ~0ull : (((1ull << W) - 1ull) << ((uint32_t)lane - j)));
+        if ((alive >> lane) & 1ull) {
+          const uint32_t o = bits_below(own);
+          if (inc_u) inc_out(o, id);
+          else sh.ph.b.tok[a + o] = id;
+        }
+        if (has && j == 0u) {
+          const uint32_t c = (uint32_t)__popcll(own);
+          if (inc_u) sh.inc_cnt = c;
+          else sh.ucnt[u] = (uint16_t)c;
+        }
+      }
       // all 64 lanes add one (no branch on the lane before the broadcast,
       // which would make the loop exit divergent), so a wave's grab moves the
       // counter by 64 and lane 0 reads a multiple of 64
-      const uint32_t i = wave_uniform(atomicAdd(&sh.med_next, 1u)) / 64u;
-      if (i >= n_med) break;
-      const uint32_t u = wave_uniform(sh.med[i]);
-      const bool inc_u = u == U_INCOMING;
-      const uint32_t a = inc_u ? 0u : sh.ustart[u];
-      const uint32_t L = inc_u ? L_inc : sh.ustart[u + 1] - a;
-      if (!(IGN && SPANS) && L <= 32u) {
-        // the queue is in 8-byte length classes, longest first, and 32 bytes
-        // end a class, so every unit left has at most 32 bytes too: take the
-        // next one as well, one unit per half wave (not in the rarely used
-        // ignore_merges span export, which it would push into spills)
-        const uint32_t i2 = wave_uniform(atomicAdd(&sh.med_next, 1u)) / 64u;
-        if (i2 < n_med) {
-          const uint32_t u2 = wave_uniform(sh.med[i2]);
-          const bool inc2 = u2 == U_INCOMING;
-          const uint32_t a2 = inc2 ? 0u : sh.ustart[u2];
-          const uint32_t L2 = inc2 ? L_inc : sh.ustart[u2 + 1] - a2;
-          auto by2 = [&](uint32_t hf, uint32_t j) -> uint32_t {
-            const bool in = hf ? inc2 : inc_u;
-            return in ? inc_byte(j) : (uint32_t)sh.buf[PT_PAD + (hf ? a2 : a) + j];
-          };
-          auto ot2 = [&](uint32_t hf, uint32_t j, uint32_t id) {
-            if (hf ? inc2 : inc_u) inc_out(j, id);
-            else sh.ph.b.tok[(hf ? a2 : a) + j] = id;
-          };
-          const uint32_t c2 = bpe_pair32(L, L2, by2, tb, ot2);
-          if (lane == 0) {
-            if (inc_u) sh.inc_cnt = c2 & 0xFFFFu;
-            else sh.ucnt[u] = (uint16_t)(c2 & 0xFFFFu);
-            if (inc2) sh.inc_cnt = c2 >> 16;
-            else sh.ucnt[u2] = (uint16_t)(c2 >> 16);
-          }
-          continue;
-        }
-      }
-      auto by = [&](int j) -> uint32_t {
-        return inc_u ? inc_byte((uint32_t)j) : (uint32_t)sh.buf[PT_PAD + a + (uint32_t)j];
-      };
-      auto ot = [&](int j, uint32_t id) {
-        if (inc_u) inc_out((uint32_t)j, id);
-        else sh.ph.b.tok[a + (uint32_t)j] = id;
-      };
-      uint32_t* scr = sh.ph.b.x.wscr[wave];
-      const uint32_t c = L <= 64u ? bpe_wave(L, by, tb, ot) : bpe_wave2(L, by, tb, scr, ot);
-      if (lane == 0) {
-        if (inc_u) sh.inc_cnt = c;
-        else sh.ucnt[u] = (uint16_t)c;
-      }
+      i = (uint32_t)(PT_THREADS / 64) + wave_uniform(atomicAdd(&sh.pass_next, 1u)) / 64u;
     }
   }
   __syncthreads();
