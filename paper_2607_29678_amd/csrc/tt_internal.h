@@ -10,31 +10,11 @@
 namespace tt {
 
 // ---------------------------------------------------------------------------
-// Character codes kept per byte in LDS by the tile kernel.
-//   bits 0..2  class of the character whose first byte is here:
-//              O other, L letter, N number, WS whitespace except CR/LF,
-//              NL CR or LF, NONE for continuation bytes and positions
-//              outside the text
-//   bits 3..6  identity of a few characters the rules test by value
+// Character codes kept per byte in LDS by the walked patterns: the class in
+// bits 0..3, and
 //   bit  7     a document starts here (no context crosses this position)
 // ---------------------------------------------------------------------------
-enum : uint32_t { C_O = 0, C_L = 1, C_N = 2, C_WS = 3, C_NL = 4, C_NONE = 7 };
-enum : uint32_t {
-  I_NONE = 0,
-  I_SP = 1,   // U+0020
-  I_APO = 2,  // U+0027
-  I_S = 3,    // contraction letters, folded per pattern
-  I_T = 4,
-  I_R = 5,
-  I_E = 6,
-  I_V = 7,
-  I_M = 8,
-  I_L = 9,
-  I_D = 10
-};
 constexpr uint32_t CODE_DOCSTART = 0x80u;
-__host__ __device__ inline uint32_t code_cls(uint32_t c) { return c & 7u; }
-__host__ __device__ inline uint32_t code_id(uint32_t c) { return (c >> 3) & 15u; }
 
 // ---------------------------------------------------------------------------
 // Token IDs inside the library.  Byte b is ID b and the result of the merge

@@ -9,9 +9,10 @@
 // at most four characters of lookback and a few per-run aggregates (Sec. 4.1,
 // "Removing the sequential regex scan"; Sec. 4.2 lists the stages: decode,
 // classify, runs, predicate, scans).  A block stages a 2,048-byte window (32
-// bytes of context on each side of the bytes it owns) in LDS and every thread
-// decodes and classifies two positions.  Runs that reach past the window are
-// resolved without a second pass:
+// bytes of context on each side of the bytes it owns) in LDS, every thread
+// decodes and classifies four positions, and one wave evaluates the rules of
+// the GPT-2- and cl100k-style patterns on bitmaps of the window (tt_runs.h).
+// Runs that reach past the window are resolved without a second pass:
 //   - backwards (cl100k: a number run's length mod 3, the class before a
 //     CR/LF stretch) from run summaries that earlier blocks publish before
 //     they wait on anything;
@@ -46,14 +47,11 @@
 #include "tt_internal.h"
 #include "tt_deepseek.h"
 #include "tt_o200k.h"
+#include "tt_runs.h"
 
 namespace tt {
 
 namespace {
-
-// trailing-run summary of a tile (cl100k): bit 0 the run spans the whole tile,
-// bits 1..2 its character count mod 3, bits 3..5 the class before it
-constexpr uint32_t SUM_RUNALL = 1u;
 
 // Words published for later blocks are self-contained values (the consumer
 // reads nothing else the producer wrote), so relaxed device-scope atomics are
@@ -77,12 +75,12 @@ __device__ __forceinline__ uint64_t wait_word(const uint64_t* p, uint32_t epoch)
 
 constexpr int CLS_L1_BYTES = 4352, CLS_L2_BYTES = TT_CLS_NBLOCKS * 64;
 
-// The probed class table, staged in LDS by every block, and the code of every
-// ASCII character (built by the block).
+// The probed class table, staged in LDS by every block, and the bitmap bits of
+// every ASCII character (built by the block).
 struct ClassLds {
   uint8_t l1[CLS_L1_BYTES] __attribute__((aligned(16)));
   uint8_t l2[CLS_L2_BYTES] __attribute__((aligned(16)));
-  uint8_t asc[128];
+  uint32_t asc[128];
 };
 
 // The 4-bit class table of a pattern whose pieces are walked (o200k-style,
@@ -102,23 +100,6 @@ __device__ __forceinline__ uint32_t table_class(const ClassLds& ct, uint32_t cp)
   return (b >> ((cp & 3u) * 2u)) & 3u;
 }
 
-__device__ __forceinline__ uint32_t letter_ident(uint32_t lower) {
-  switch (lower) {
-    case 's': return I_S;
-    case 't': return I_T;
-    case 'r': return I_R;
-    case 'e': return I_E;
-    case 'v': return I_V;
-    case 'm': return I_M;
-    case 'l': return I_L;
-    case 'd': return I_D;
-    default: return I_NONE;
-  }
-}
-
-// Class and identity code of one code point.  Contraction letters are
-// case-sensitive for GPT-2 and folded for cl100k, where the engine also folds
-// U+017F (long s) to 's'.
 // Code of one code point for the o200k-style pattern: its class only (the
 // walks read apostrophes, "/" and contraction letters from the bytes).
 __device__ __forceinline__ uint32_t o2_code(const O2Lds& t, uint32_t cp) {
@@ -146,24 +127,20 @@ __device__ __forceinline__ uint32_t walk_code(const O2Lds& t, uint32_t cp) {
   return PAT == TT_PATTERN_DEEPSEEK ? ds_code(t, cp) : o2_code(t, cp);
 }
 
-template <int PAT>
-__device__ __forceinline__ uint32_t char_code(const ClassLds& ct, uint32_t cp) {
-  uint32_t cls, id = I_NONE;
-  if (cp < 128u) {
-    if (((cp | 32u) - 'a') < 26u) cls = C_L;
-    else if ((cp - '0') < 10u) cls = C_N;
-    else if (cp == 10u || cp == 13u) cls = C_NL;
-    else if (cp == 32u || (cp - 9u) < 5u) cls = C_WS;
-    else cls = C_O;
-    if (cp == 32u) id = I_SP;
-    else if (cp == 39u) id = I_APO;
-    else if (cls == C_L && (PAT == TT_PATTERN_CL100K || cp >= 'a')) id = letter_ident(cp | 32u);
-  } else {
-    uint32_t c2 = table_class(ct, cp);
-    cls = c2 == 1u ? C_L : c2 == 2u ? C_N : c2 == 3u ? C_WS : C_O;
-    if (PAT == TT_PATTERN_CL100K && cp == 0x17Fu) id = I_S;
-  }
-  return cls | (id << 3);
+// Bitmap bits (tt_runs.h) of an ASCII character, and of a character of a class
+// of the probed table.
+__device__ __forceinline__ uint32_t ascii_bits(uint32_t cp) {
+  if (((cp | 32u) - 'a') < 26u) return 1u << (4 * BM_L);
+  if ((cp - '0') < 10u) return 1u << (4 * BM_N);
+  if (cp == 10u || cp == 13u) return 1u << (4 * BM_NL);
+  if (cp == 32u) return (1u << (4 * BM_WS)) | (1u << (4 * BM_SP));
+  if ((cp - 9u) < 5u) return 1u << (4 * BM_WS);
+  if (cp == 39u) return (1u << (4 * BM_O)) | (1u << (4 * BM_APO));
+  return 1u << (4 * BM_O);
+}
+__device__ __forceinline__ uint32_t class_bits(uint32_t cls2) {  // 0 other, 1 letter, 2 number, 3 whitespace
+  constexpr uint32_t AT = (4u * BM_O) | (4u * BM_L) << 8 | (4u * BM_N) << 16 | (4u * BM_WS) << 24;
+  return 1u << ((AT >> (8u * cls2)) & 31u);
 }
 
 // Strict UTF-8 decode from bytes in registers, with selects only: the length
@@ -183,27 +160,6 @@ __device__ __forceinline__ uint32_t decode_sel(uint32_t b0, uint32_t b1, uint32_
   cp = len <= 1u ? b0 : len == 2u ? c2 : len == 3u ? c3 : c4;
   return (len != 0u && len <= avail && ok1 && ok2 && ok3) ? len : 0u;
 }
-
-// char_code for any code point of at most U+10FFFF, with selects only (both
-// tables are read).
-template <int PAT>
-__device__ __forceinline__ uint32_t char_code_sel(const ClassLds& ct, uint32_t cp) {
-  const uint32_t a = ct.asc[cp & 127u];
-  const uint32_t c2 = table_class(ct, cp);
-  const uint32_t cls = c2 == 1u ? C_L : c2 == 2u ? C_N : c2 == 3u ? C_WS : C_O;
-  const uint32_t id = (PAT == TT_PATTERN_CL100K && cp == 0x17Fu) ? I_S : I_NONE;
-  return cp < 128u ? a : (cls | (id << 3));
-}
-
-// Segmented char-count scan state for cl100k: has-head (bit 31), window index
-// of the latest run head (bits 16..27), characters since that head (bits 0..15;
-// or since the tile start when there is no head yet).
-__device__ __forceinline__ uint32_t seg_combine(uint32_t a, uint32_t b) {
-  return (b & 0x80000000u) ? b : ((a & 0xFFFF0000u) | ((a + b) & 0xFFFFu));
-}
-__device__ __forceinline__ bool seg_has(uint32_t s) { return (s & 0x80000000u) != 0; }
-__device__ __forceinline__ int seg_head(uint32_t s) { return (int)((s >> 16) & 0x0FFFu); }
-__device__ __forceinline__ uint32_t seg_cnt(uint32_t s) { return s & 0xFFFFu; }
 
 template <typename F>
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, int lane, F comb) {
@@ -283,24 +239,29 @@ constexpr uint16_t U_INCOMING = 0xFFFFu;               // list entry for the inc
 // LDS of the classification phase and of the BPE phase share one region:
 // nothing of the first is read after the unit scan, nothing of the second is
 // written before it.
+template <bool WALK>
+struct RulesMem;
+template <>
+struct RulesMem<false> {    // GPT-2, cl100k
+  ClassLds cls;             // character classes
+  uint32_t join[2048];      // junction byte pairs of the merges
+  uint32_t bm[BM_COUNT * BM_STRIDE];  // bitmaps of the window
+  uint32_t bm_doc[BM_WORDS];          // batch: document starts
+  uint32_t nocut[PT_WIN / 32];        // ignore_merges: window positions no junction cut may split
+};
+template <>
+struct RulesMem<true> {     // o200k, DeepSeek
+  O2Lds o2;                 // character classes
+  uint32_t join[2048];      // junction byte pairs of the merges
+  uint8_t code[PT_PAD + PT_WIN + 16] __attribute__((aligned(16)));  // class/doc-start codes
+  uint8_t o2piece[PT_WIN];  // 1 at the piece starts the walks find
+  uint32_t o2bits[WALK_BITMAPS * WIN_WORDS];  // class-set bitmaps of the window
+  uint32_t o2seg[PT_WIN / 32];    // segment starts (synchronizing positions, document starts)
+  uint32_t nocut[PT_WIN / 32];    // ignore_merges: window positions no junction cut may split
+};
+template <bool WALK>
 union PhaseMem {
-  struct {
-    union {
-      ClassLds cls;           // character classes (GPT-2, cl100k)
-      O2Lds o2;               // character classes (o200k, DeepSeek)
-    };
-    uint32_t join[2048];      // junction byte pairs of the merges
-    uint8_t code[PT_PAD + PT_WIN + 16] __attribute__((aligned(16)));  // class/identity/doc-start codes
-    union {
-      int16_t run_end[PT_WIN];  // cl100k: window index of the head after a run's head
-      struct {
-        uint8_t o2piece[PT_WIN];  // walked patterns: 1 at the piece starts the walks find
-        uint32_t o2bits[WALK_BITMAPS * WIN_WORDS];  // walked patterns: class-set bitmaps of the window
-      };
-    };
-    uint32_t o2seg[PT_WIN / 32];    // walked patterns: segment starts (synchronizing positions, document starts)
-    uint32_t nocut[PT_WIN / 32];    // ignore_merges: window positions no junction cut may split
-  } a;
+  RulesMem<WALK> a;
   struct {
     uint32_t tok[PT_WIN];     // tokens of unit k at tok[ustart[k] ..]
     uint16_t uoff[PT_WIN];    // first output of each unit within the tile
@@ -315,10 +276,11 @@ union PhaseMem {
   } b;
 };
 
+template <bool WALK>
 struct PtShared {
   uint8_t buf[PT_PAD + PT_WIN + 16] __attribute__((aligned(16)));     // window bytes
   uint8_t dstart[PT_PAD + PT_WIN + 16] __attribute__((aligned(16)));  // 1 where a document starts
-  PhaseMem ph;
+  PhaseMem<WALK> ph;
   uint16_t ustart[PT_OWN + 2];  // window index of every unit start in the owned bytes
   uint16_t ucnt[PT_OWN + 2];    // tokens of each unit
   RowsShared<PT_THREADS / 64> rows;
@@ -334,8 +296,8 @@ struct PtShared {
   uint32_t prefix;            // outputs of all earlier tiles
   uint32_t err;               // invalid input in this tile or an earlier one
   uint32_t inc_cnt;           // its tokens
-  uint32_t carry_n;           // cl100k: number-run chars before the tile, mod 3
-  uint32_t carry_nlpre;       // cl100k: class before a CR/LF stretch entering the tile
+  uint32_t uw[BM_WORDS], upre[BM_WORDS];  // unit starts, and those before each word
+  uint32_t m;                 // their number
   uint32_t cwave[PT_THREADS / 64];  // span export: per-wave sums
   int64_t o2_doc_after;          // walked patterns, batch: first document start after the window
   int64_t o2_last_s, o2_last_e;  // walked patterns: the tile's last piece (window indices)
@@ -344,14 +306,10 @@ struct PtShared {
   uint32_t cbase;             // span export: non-continuation bytes before the tile
   uint32_t ctile;             // span export: non-continuation bytes the tile owns
   int64_t doc_lo_idx;         // batch: first document start index touching the window
-  int last_own;               // cl100k: window index of the tile's last own character
   // walked patterns: where the run of each run set through the window's end
   // ends past it, its last tracked character there, and whether wave 0 has
   // published them
   FarRuns far;
-  // cl100k: a whitespace stretch after CR/LF that reaches the window's end
-  int32_t ws_pend;            // its window index, or -1
-  uint32_t ws_res;            // 1 when it is the last stretch of its run (read on past the window)
 };
 
 }  // namespace
@@ -506,7 +464,10 @@ template <int PAT, bool BATCH, int MODE, bool IGN>
 __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6))) void tile_kernel(Work w, DevTables tb) {
   constexpr bool SEG = MODE >= 1;
   constexpr bool SPANS = MODE == 2;
-  __shared__ PtShared sh;
+  // the patterns whose pieces are walked between synchronizing positions
+  constexpr bool DS = PAT == TT_PATTERN_DEEPSEEK;
+  constexpr bool WALK = PAT == TT_PATTERN_O200K || DS;
+  __shared__ PtShared<WALK> sh;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
@@ -521,9 +482,6 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
     sh.ph.a.nocut[tid] = 0;
     sh.whole[tid] = 0;
   }
-  // the patterns whose pieces are walked between synchronizing positions
-  constexpr bool DS = PAT == TT_PATTERN_DEEPSEEK;
-  constexpr bool WALK = PAT == TT_PATTERN_O200K || DS;
   // the ticket's round trip (tickets are handed out one at a time) overlaps
   // the staging of the tables, which do not depend on the tile
   uint32_t ticket = 0;
@@ -531,7 +489,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
   {
     // the class table (12.9 KB) is read once per block
     static_assert(CLS_L1_BYTES % 16 == 0 && CLS_L2_BYTES % 16 == 0, "class table staging uses 16-byte words");
-    if (WALK) {
+    if constexpr (WALK) {
       constexpr int N1 = 4352 / 16, N2 = (DS ? TT_DS_NBLOCKS : TT_O2_NBLOCKS) * 128 / 16;
       const uint4* s1 = reinterpret_cast<const uint4*>(DS ? TT_DS_L1 : TT_O2_L1);
       const uint4* s2 = reinterpret_cast<const uint4*>(DS ? TT_DS_L2 : TT_O2_L2);
@@ -552,7 +510,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
         if (i < N1) d1[i] = s1[i];
         else d2[i - N1] = s2[i - N1];
       }
-      if (tid < 128) sh.ph.a.cls.asc[tid] = (uint8_t)char_code<PAT>(sh.ph.a.cls, (uint32_t)tid);
+      if (tid < 128) sh.ph.a.cls.asc[tid] = ascii_bits((uint32_t)tid);
     }
   }
   if (SEG) {
@@ -567,7 +525,6 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
     sh.pass_next = 0;
     sh.n_big = 0;
     sh.inc_cnt = 0;
-    sh.ws_pend = -1;
   }
   if (tid < WALK_BITMAPS) sh.far.state[tid] = FAR_NONE;
   __syncthreads();
@@ -615,6 +572,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
       v = make_uint2(lo, hi);
     }
     *reinterpret_cast<uint2*>(&sh.buf[PT_PAD + q0]) = v;
+    if (!WALK && !BATCH) return;  // (the text start is the only document start)
     uint2 d = make_uint2(0u, 0u);
     if (p0 <= 0 && p0 + 8 > 0) d.x = (p0 == 0) ? 1u : 0u;  // the text start is a document start
     if (p0 < 0 && p0 + 8 > 0) {
@@ -668,6 +626,11 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
   // decides everything from registers: a sequence starts at most three bytes
   // before a position it covers and ends at most three bytes after.  Four
   // ASCII bytes inside the text take their codes from the ASCII table.
+  // GPT-2- and cl100k-style: the codes are bits of the window's bitmaps, only
+  // the lead bytes of longer sequences are decoded, one after the other (a
+  // word of valid text holds two at most), and continuation bytes are checked
+  // as byte masks of the whole word: 2.0 us of a tile in multilingual text, 4.1
+  // at most (decoding at all four positions took 4.2, 10.4 at most).
   static_assert(PT_BPT == 4 && PT_PAD % 4 == 0, "classification works on aligned 4-byte words");
   bool bad = false;
   uint32_t nc_own = 0;  // span export: non-continuation bytes among the thread's own positions
@@ -683,7 +646,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
     }
     return c;
   };
-  {
+  if constexpr (WALK) {
     const int q0 = tid * PT_BPT;
     const uint32_t* bw = reinterpret_cast<const uint32_t*>(&sh.buf[PT_PAD + q0 - 4]);
     const uint32_t* dw = reinterpret_cast<const uint32_t*>(&sh.dstart[PT_PAD + q0 - 4]);
@@ -693,7 +656,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
     if (SPANS) nc_own = own_noncont(bw1, q0, p0);
     uint32_t codes;
     if ((bw1 & 0x80808080u) == 0u && p0 >= 0 && p0 + PT_BPT <= n) {
-      const uint8_t* asc = WALK ? sh.ph.a.o2.asc : sh.ph.a.cls.asc;
+      const uint8_t* asc = sh.ph.a.o2.asc;
       codes = (uint32_t)asc[bw1 & 255u] | ((uint32_t)asc[(bw1 >> 8) & 255u] << 8) |
               ((uint32_t)asc[(bw1 >> 16) & 255u] << 16) | ((uint32_t)asc[bw1 >> 24] << 24);
       codes |= (dw1 & 0x01010101u) << 7;  // document starts (flags are 0 or 1)
@@ -737,8 +700,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
           claimed = claimed || (!blocked && ok && !c && ll > (uint32_t)k);
           blocked = blocked || !ok || !c || dst(j - k);
         }
-        const uint32_t code = WALK ? ((!in_j || cont) ? O2_NONE : len == 0u ? O2_O : walk_code<PAT>(sh.ph.a.o2, cp))
-                                 : (!in_j || cont) ? C_NONE : len == 0u ? C_O : char_code_sel<PAT>(sh.ph.a.cls, cp);
+        const uint32_t code = (!in_j || cont) ? O2_NONE : len == 0u ? O2_O : walk_code<PAT>(sh.ph.a.o2, cp);
         bad = bad || (own && (cont ? !claimed : len == 0u));
         codes |= (code | (dst(j) ? CODE_DOCSTART : 0u)) << (8 * j);
       }
@@ -746,13 +708,70 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
     *reinterpret_cast<uint32_t*>(&sh.ph.a.code[PT_PAD + q0]) = codes;
     if (tid < 3) {  // positions outside [0, PT_WIN) carry no character for the rules
       const int qx = tid == 0 ? -8 : PT_WIN + 8 * (tid - 1);
-      const uint32_t none4 = WALK ? 0x0F0F0F0Fu : 0x07070707u;
+      const uint32_t none4 = 0x0F0F0F0Fu;
       *reinterpret_cast<uint2*>(&sh.ph.a.code[PT_PAD + qx]) = make_uint2(none4, none4);
     }
+  } else {
+    const int q0 = tid * PT_BPT;
+    const int64_t p0 = w0 + q0;  // text position of the first of the four
+    const uint32_t* bw = reinterpret_cast<const uint32_t*>(&sh.buf[PT_PAD + q0 - 4]);
+    const uint32_t x0 = bw[0], x1 = bw[1], x2 = bw[2];
+    if (SPANS) nc_own = own_noncont(x1, q0, p0);
+    // the low bits of four bytes as a nibble
+    auto nibble = [](uint32_t x) -> uint32_t { return __builtin_amdgcn_udot4(x & 0x01010101u, 0x08040201u, 0u, false); };
+    uint32_t dw1 = 0;
+    if (BATCH) dw1 = *reinterpret_cast<const uint32_t*>(&sh.dstart[PT_PAD + q0]);
+    // junction cuts: the byte pairs that no merge joins
+    uint32_t cuts = 0;
+    if (SEG && !IGN) {
+      const uint64_t bb = x0 | ((uint64_t)x1 << 32);
+#pragma unroll
+      for (int j = 0; j < PT_BPT; ++j) {
+        const uint32_t key = (uint32_t)(bb >> (8 * (j + 3)));  // b[q-1] | b[q] << 8
+        const uint32_t k2 = ((key & 255u) << 8) | ((key >> 8) & 255u);
+        cuts |= ((~sh.ph.a.join[k2 >> 5] >> (k2 & 31u)) & 1u) << j;
+      }
+    }
+    const uint32_t* asc = sh.ph.a.cls.asc;
+    uint32_t e = asc[x1 & 127u] | (asc[(x1 >> 8) & 127u] << 1) | (asc[(x1 >> 16) & 127u] << 2) | (asc[(x1 >> 24) & 127u] << 3);
+    if (((x0 | x1) & 0x80808080u) != 0u) {
+      e &= nibble(~x1 >> 7) * 0x11111111u;  // (not the bytes above 127)
+      const bool own = q0 >= PT_HALO && q0 < PT_HALO + PT_OWN;
+      static_assert(PT_HALO % PT_BPT == 0 && PT_OWN % PT_BPT == 0, "a word is the tile's own or not");
+      // bit 7 of every byte: leads of at least two, three and four bytes, in
+      // this word and the one before, and the continuation bytes they call for
+      const uint32_t l2 = x1 & (x1 << 1) & 0x80808080u, m2 = x0 & (x0 << 1) & 0x80808080u;
+      const uint32_t l3 = l2 & (x1 << 2), m3 = m2 & (x0 << 2), l4 = l3 & (x1 << 3), m4 = m3 & (x0 << 3);
+      const uint32_t want = __builtin_amdgcn_alignbyte(l2, m2, 3) | __builtin_amdgcn_alignbyte(l3, m3, 2) |
+                            __builtin_amdgcn_alignbyte(l4, m4, 1);
+      const uint32_t cont = x1 & ~(x1 << 1) & 0x80808080u;
+      // (a document starts with a character; past the end of the text, where
+      // the window is zero, a sequence that the end cuts shows up)
+      bad = ((want ^ cont) | (cont & (dw1 << 7))) != 0u && (own || p0 + PT_BPT > n);
+      uint32_t leads = l2;
+      while (leads) {
+        const uint32_t j = (uint32_t)__builtin_ctz(leads) >> 3;
+        leads &= leads - 1u;
+        const uint32_t v = __builtin_amdgcn_alignbyte(x2, x1, j);
+        uint32_t cp;
+        const uint32_t b0 = v & 255u;
+        // (its continuation bytes are checked above: here, that the lead is
+        // one and the ranges of the second byte)
+        const uint32_t len = decode_sel(b0, (v >> 8) & 255u, (v >> 16) & 255u, v >> 24, 4u, cp);
+        bad = bad || (own && len == 0u);
+        e |= class_bits(table_class(sh.ph.a.cls, len ? cp : 0xFFFDu)) << j;
+      }
+    }
+    if (p0 < 0 || p0 + PT_BPT > n) {  // nothing is set outside the text
+      uint32_t in = 0;
+      for (int j = 0; j < PT_BPT; ++j) in |= (p0 + j >= 0 && p0 + j < n ? 1u : 0u) << j;
+      e &= in * 0x11111111u;
+    }
+    e |= cuts << (4 * BM_CUT);
+    sh.ph.a.bm[(lane & 7) * BM_STRIDE + (tid >> 3)] = to_bitmaps(e, lane);
+    if (BATCH) store_nibbles(sh.ph.a.bm_doc, q0, lane, nibble(dw1));
   }
-  if (PAT == TT_PATTERN_CL100K)
-    for (int q = tid; q < PT_WIN; q += PT_THREADS) sh.ph.a.run_end[q] = -1;
-  if (WALK) *reinterpret_cast<uint32_t*>(&sh.ph.a.o2piece[tid * PT_BPT]) = 0u;
+  if constexpr (WALK) *reinterpret_cast<uint32_t*>(&sh.ph.a.o2piece[tid * PT_BPT]) = 0u;
   if (SPANS) {
     const uint32_t nc_incl = wave_incl_sum(nc_own);
     if (lane == 63) sh.cwave[wave] = nc_incl;
@@ -768,233 +787,19 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
   }
 
   TT_PHASE(3);
-  // ---- neighbour helpers (window indices; -1 = none) ----------------------
-  auto code_at = [&](int q) -> uint32_t { return sh.ph.a.code[PT_PAD + q]; };
-  auto cls = [&](int q) -> uint32_t { return code_cls(code_at(q)); };
-  auto ident = [&](int q) -> uint32_t { return code_id(code_at(q)); };
-  auto prev = [&](int q) -> int {
-    if (code_at(q) & CODE_DOCSTART) return -1;
-    for (int r = q - 1; r >= 0; --r) {
-      if (!inside(r)) return -1;
-      if (code_cls(code_at(r)) != C_NONE) return r;
-    }
-    return -1;
-  };
-  auto next = [&](int q) -> int {
-    for (int r = q + 1; r < PT_WIN + 8; ++r) {
-      if (!inside(r)) return -1;
-      const uint32_t c = code_at(r);
-      if (c & CODE_DOCSTART) return -1;
-      if (code_cls(c) != C_NONE) return r;
-    }
-    return -1;
-  };
-  auto is_char = [&](int q) -> bool { return inside(q) && code_cls(code_at(q)) != C_NONE; };
-  auto is_w = [](uint32_t c) -> bool { return c == C_WS || c == C_NL; };
-
-  // Suffix of a contraction starting at letter q: 1 or 2 letters, or 0.
-  auto suffix_len = [&](int q) -> int {
-    uint32_t a = ident(q);
-    if (a == I_S || a == I_T || a == I_M || a == I_D) return 1;
-    if (a == I_R || a == I_V || a == I_L) {
-      int q1 = next(q);
-      if (q1 >= 0) {
-        uint32_t b = ident(q1);
-        if ((a == I_R && b == I_E) || (a == I_V && b == I_E) || (a == I_L && b == I_L)) return 2;
-      }
-    }
-    return 0;
-  };
-  // Letter q starts a contraction suffix: the apostrophe before it begins a
-  // match, i.e. it is a one-character "other" run not preceded by U+0020.
-  auto contraction_len_at = [&](int q) -> int {
-    int p1 = prev(q);
-    if (p1 < 0 || ident(p1) != I_APO) return 0;
-    int p2 = prev(p1);
-    if (p2 >= 0 && (cls(p2) == C_O || ident(p2) == I_SP)) return 0;
-    return suffix_len(q);
-  };
-  // Letter q (inside a letter run) is the first letter after a contraction.
-  auto contraction_ends_here = [&](int q) -> bool {
-    int p1 = prev(q);
-    if (contraction_len_at(p1) == 1) return true;
-    int p2 = prev(p1);
-    return p2 >= 0 && cls(p2) == C_L && contraction_len_at(p2) == 2;
-  };
-
-  // ---- the codes around the thread's positions, in registers ---------------
-  // cr(r) is the code of window position qb + r for r in [-8, 8): enough to
-  // find the characters on either side of the thread's positions (and the one
-  // before that), which are at most four bytes away in valid text.
-  const int qb = tid * PT_BPT;
-  const uint32_t* cwp = reinterpret_cast<const uint32_t*>(&sh.ph.a.code[PT_PAD + qb - 8]);
-  const uint32_t cw0 = cwp[0], cw1 = cwp[1], cw2 = cwp[2], cw3 = cwp[3];
-  auto cr = [&](int r) -> uint32_t {
-    const int i = r + 8;
-    const uint32_t lo = (i & 4) ? cw1 : cw0, hi = (i & 4) ? cw3 : cw2;
-    return (((i & 8) ? hi : lo) >> ((i & 3) * 8)) & 255u;
-  };
-  // an apostrophe one byte before position qb + r (a contraction can start at
-  // qb + r only then), or two or three bytes before (a contraction can end just
-  // before qb + r only then: the suffix is one or two ASCII letters, or U+017F)
-  auto apo_at = [&](int r) -> bool { return code_id(cr(r)) == I_APO; };
-  // The character before window position qb + r (r in [-4, 8)) and its code,
-  // from the register window: in valid text it starts at most four bytes
-  // before (in invalid text, whose output is discarded, the search stops
-  // there).  Returns its distance, 0 when there is none.
-  auto prev_reg = [&](int r, uint32_t& pc) -> uint32_t {
-    uint32_t d = 0, x = 0;
-#pragma unroll
-    for (int k = 4; k >= 1; --k) {
-      const uint32_t c = cr(r - k);
-      const bool ch = code_cls(c) != C_NONE;
-      d = ch ? (uint32_t)k : d;
-      x = ch ? c : x;
-    }
-    pc = x;
-    return (cr(r) & CODE_DOCSTART) ? 0u : d;
-  };
-  // Whether a character follows position qb + r (r in [-8, 4)) in the same
-  // document, within four bytes, and its code.
-  auto next_reg = [&](int r, uint32_t& nc) -> bool {
-    bool found = false, stop = false;
-    uint32_t x = 0;
-#pragma unroll
-    for (int k = 1; k <= 4; ++k) {
-      const uint32_t c = cr(r + k);
-      const bool ds = (c & CODE_DOCSTART) != 0u, ch = code_cls(c) != C_NONE;
-      found = found || (!stop && !ds && ch);
-      x = (!stop && !ds && ch) ? c : x;
-      stop = stop || ds || ch;
-    }
-    nc = x;
-    return found;
-  };
-
-  // ---- cl100k: run scan, run ends, summaries, carries ----------------------
-  // scan element of window position qb + j: a run head restarts the char count
-  auto elem_of = [&](int j) -> uint32_t {
-    const int q = qb + j;
-    const uint32_t c = cr(j);
-    if (q < PT_HALO || code_cls(c) == C_NONE) return 0u;
-    uint32_t pc = 0;
-    const bool head = prev_reg(j, pc) == 0u || code_cls(pc) != code_cls(c);
-    return head ? (0x80000000u | ((uint32_t)q << 16) | 1u) : 1u;
-  };
-  uint32_t elems[PT_BPT];
-#pragma unroll
-  for (int j = 0; j < PT_BPT; ++j) elems[j] = PAT == TT_PATTERN_CL100K ? elem_of(j) : 0u;
-  uint32_t s0 = 0;  // scan state before the thread's first position
-  if (PAT == TT_PATTERN_CL100K) {
-    // elements over window indices [HALO, WIN)
-    uint32_t agg = 0;
-#pragma unroll
-    for (int j = 0; j < PT_BPT; ++j) agg = seg_combine(agg, elems[j]);
-    uint32_t inc = wave_incl_scan(agg, lane, seg_combine);
-    if (lane == 63) sh.wave_tot[wave] = inc;
-    uint32_t lex = __shfl_up(inc, 1, 64);
-    if (lane == 0) lex = 0;
-    __syncthreads();
-    uint32_t wpre = 0;
-    for (int v = 0; v < wave; ++v) wpre = seg_combine(wpre, sh.wave_tot[v]);
-    s0 = seg_combine(wpre, lex);
-    // each run head records itself as the end of the previous run
-    const int own_end = (int)(n - w0 < PT_HALO + PT_OWN ? n - w0 : PT_HALO + PT_OWN);
-    int last_q = -1;
-    uint32_t last_st = 0;
-    {
-      uint32_t st = s0;
-#pragma unroll
-      for (int j = 0; j < PT_BPT; ++j) {
-        const int q = qb + j;
-        const uint32_t e = elems[j];
-        if ((e & 0x80000000u) && seg_has(st)) sh.ph.a.run_end[seg_head(st)] = (int16_t)q;
-        st = seg_combine(st, e);
-        if (q >= PT_HALO && q < own_end && e != 0u) {
-          last_q = q;
-          last_st = st;
-        }
-      }
-    }
-    // summary of the tile's trailing run (own range), published before waiting
-    // on any other block; the thread holding the last own character publishes
-    if (tid == 0) sh.last_own = -1;
-    __syncthreads();
-    if (last_q >= 0) atomicMax(&sh.last_own, last_q);
-    __syncthreads();
-    const int s_last = sh.last_own;
-    if (s_last < 0) {
-      if (tid == 0) st_word(&w.tile_sum[t], ((uint64_t)w.epoch << 32) | SUM_RUNALL);
-    } else if (s_last == last_q) {
-      uint32_t sum = (seg_cnt(last_st) % 3u) << 1;
-      if (seg_has(last_st)) {
-        int hp = prev(seg_head(last_st));
-        sum |= (hp >= 0 ? cls(hp) : (uint32_t)C_NONE) << 3;
-      } else {
-        sum |= SUM_RUNALL;
-      }
-      st_word(&w.tile_sum[t], ((uint64_t)w.epoch << 32) | sum);
-    }
-    // carries for a run entering the tile from the left
-    if (tid == 0) {
-      sh.carry_n = 0;
-      sh.carry_nlpre = C_NONE;
-    }
-    __syncthreads();
-    if (wave == 0) {
-      int f = -1;  // first own character
-      for (int q = PT_HALO; q < PT_HALO + PT_OWN; ++q)
-        if (is_char(q)) {
-          f = q;
-          break;
-        }
-      // a number run continuing into the tile needs its length so far; a
-      // CR/LF stretch ending at or after the tile start needs the class
-      // before it (the first own character may be the whitespace after it)
-      bool need = false;
-      if (f >= 0 && t > 0) {
-        int p = prev(f);
-        need = p >= 0 && ((cls(p) == C_N && cls(f) == C_N) || cls(p) == C_NL);
-      }
-      // walk back tile by tile (usually one step) until a tile whose trailing
-      // run does not span it
-      if (need && lane == 0) {
-        uint32_t acc = 0, pre = C_NONE;
-        for (int64_t j = (int64_t)t - 1; j >= 0; --j) {
-          const uint64_t x = wait_word(&w.tile_sum[j], w.epoch);
-          const uint32_t v = (uint32_t)x;
-          acc += (v >> 1) & 3u;
-          if (!(v & SUM_RUNALL)) {
-            pre = (v >> 3) & 7u;
-            break;
-          }
-        }
-        sh.carry_n = acc % 3u;
-        sh.carry_nlpre = pre;
-      }
-    }
-    __syncthreads();
-  }
-
-  // rule 2 of cl100k: is the whitespace stretch starting at q (after CR/LF)
-  // the last stretch of its whitespace run?  1 yes, 0 no, -1 when the stretch
-  // reaches the window's end and the answer lies in the text after it (the
-  // block reads on there together, below)
-  auto ws_stretch_is_last = [&](int q) -> int {
-    int e = sh.ph.a.run_end[q];
-    if (e >= 0) return ((code_at(e) & CODE_DOCSTART) || cls(e) != C_NL) ? 1 : 0;
-    if (w0 + PT_WIN >= n) return 1;  // the run reaches the end of the text
-    return -1;
-  };
-
+  const int qb = tid * PT_BPT;  // the thread's first position
+  uint32_t flags = 0;           // bit j: a piece (then: a unit) starts at qb + j
   TT_PHASE(4);
-  // ---- piece-start predicate ----------------------------------------------
-  // The run-local rules, from the codes of the position, of the characters
-  // before and after it (register window) and, for cl100k, the run scan.  The
-  // cheap cases are selects; contractions (an apostrophe one to three bytes
-  // back), whitespace after CR/LF and a letter after a lone symbol branch.
-  uint32_t flags = 0;
-  if (WALK) {
+  // ---- piece starts ---------------------------------------------------------
+  if constexpr (WALK) {
+    // cr(r) is the code of window position qb + r for r in [-8, 8)
+    const uint32_t* cwp = reinterpret_cast<const uint32_t*>(&sh.ph.a.code[PT_PAD + qb - 8]);
+    const uint32_t cw0 = cwp[0], cw1 = cwp[1], cw2 = cwp[2], cw3 = cwp[3];
+    auto cr = [&](int r) -> uint32_t {
+      const int i = r + 8;
+      const uint32_t lo = (i & 4) ? cw1 : cw0, hi = (i & 4) ? cw3 : cw2;
+      return (((i & 8) ? hi : lo) >> ((i & 3) * 8)) & 255u;
+    };
     // o200k- and DeepSeek-style: segment starts are document starts,
     // synchronizing positions (their two neighbouring characters form a
     // transition of o2_sync or ds_sync) and two whitespace cases that start a
@@ -1037,7 +842,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
         xc = lead ? (cr(j - d) & 15u) : xc;
         xb = lead ? (d == 1 ? wbyte(j - 1) : 0x80u) : xb;
       }
-      const bool pair = (k > 0) & (q - k >= 0) &
+      const bool pair = (k > 0) && (q - k >= 0) &&
                         (DS ? ds_sync_bits(xc, cl) : o2_sync_bits(xc, cl, xb, wbyte(j)));
       // one-byte whitespace before a character that is not whitespace, in
       // the same document (and, DeepSeek-style, the same group stretch): no
@@ -1060,20 +865,10 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
         nib[kb] |= (uint32_t)(in_b & bit) << j;
       }
     }
-    // A bitmap word holds the four positions of eight consecutive lanes: the
-    // last lane of the eight stores the word, ORed together over DPP row
-    // shifts (no atomics, and no clearing beforehand).
     static_assert(PT_BPT == 4 && PT_THREADS * PT_BPT == PT_WIN, "eight lanes per bitmap word");
-    auto store_word = [&](uint32_t* words, uint32_t nib4) {
-      int x = (int)(nib4 << (qb & 31));
-      x |= __builtin_amdgcn_update_dpp(0, x, 0x111, 0xF, 0xF, true);  // row_shr:1
-      x |= __builtin_amdgcn_update_dpp(0, x, 0x112, 0xF, 0xF, true);  // row_shr:2
-      x |= __builtin_amdgcn_update_dpp(0, x, 0x114, 0xF, 0xF, true);  // row_shr:4
-      if ((lane & 7) == 7) words[qb >> 5] = (uint32_t)x;
-    };
-    store_word(sh.ph.a.o2seg, seg);
+    store_nibbles(sh.ph.a.o2seg, qb, lane, seg);
 #pragma unroll
-    for (int kb = 0; kb < WALK_BITMAPS; ++kb) store_word(&sh.ph.a.o2bits[kb * WIN_WORDS], nib[kb]);
+    for (int kb = 0; kb < WALK_BITMAPS; ++kb) store_nibbles(&sh.ph.a.o2bits[kb * WIN_WORDS], qb, lane, nib[kb]);
     if (tid == 0) {  // the tile's last piece, until a walk finds it (kept only for invalid text)
       sh.o2_last_s = PT_HALO;
       sh.o2_last_e = n - w0 < PT_HALO + PT_OWN ? n - w0 : PT_HALO + PT_OWN;
@@ -1244,137 +1039,119 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
     if (tid == 0 && sh.o2_pub == 0u) publish_last(sh.o2_last_s, sh.o2_last_e);
   }
   if (WALK) TT_PHASE(19);
-  uint32_t scan_st = s0;  // cl100k: scan state before position q
-#pragma unroll
-  for (int j = 0; j < (WALK ? 0 : PT_BPT); ++j) {
-    const int q = qb + j;
-    const uint32_t ex = scan_st;
-    if (PAT == TT_PATTERN_CL100K) scan_st = seg_combine(scan_st, elems[j]);
-    const uint32_t cq = cr(j);
-    const uint32_t c0 = code_cls(cq);
-    if (q < PT_HALO || q >= PT_HALO + PT_OWN || c0 == C_NONE) continue;
-    uint32_t cp1 = 0, cn1 = 0;
-    const uint32_t d1 = prev_reg(j, cp1);
-    const bool hn = next_reg(j, cn1);
-    const uint32_t c1 = code_cls(cp1);
-    const bool w0c = is_w(c0), w1c = is_w(c1);
-    const bool sp1 = code_id(cp1) == I_SP;
-    const bool run_last = hn && !is_w(code_cls(cn1));  // a following character that is not whitespace
-    const bool apo1 = apo_at(j - 1), apo23 = apo_at(j - 2) || apo_at(j - 3);
-    bool start;
-    if (PAT == TT_PATTERN_GPT2) {
-      start = w0c ? (!w1c || run_last) : (c1 != c0 && !sp1);
-      if (!w0c && c0 == C_L && (apo1 || apo23)) {
-        if (c1 == c0) start = apo23 && contraction_ends_here(q);
-        else if (!sp1 && apo1 && contraction_len_at(q) > 0) start = false;
+  if constexpr (!WALK) {
+    // one wave evaluates the rules on the bitmaps and, where no vocabulary
+    // probe comes between, cuts the pieces into units and numbers them
+    if (wave == 0) {
+      const uint32_t* bm = &sh.ph.a.bm[lane];
+      RunBits b;
+      b.L = bm[BM_L * BM_STRIDE];
+      b.N = bm[BM_N * BM_STRIDE];
+      b.O = bm[BM_O * BM_STRIDE];
+      b.WS = bm[BM_WS * BM_STRIDE];
+      b.NL = bm[BM_NL * BM_STRIDE];
+      b.SP = bm[BM_SP * BM_STRIDE];
+      b.APO = bm[BM_APO * BM_STRIDE];
+      b.D = BATCH ? sh.ph.a.bm_doc[lane] : (t == 0 && lane == PT_HALO / 32 ? 1u : 0u);
+      b.C = b.L | b.N | b.O | b.WS | b.NL;
+      const int in_end = n - w0 < PT_WIN ? (int)(n - w0) : PT_WIN;
+      b.K = bm_range(t == 0 ? PT_HALO : 0, in_end, lane) & ~b.C;
+      b.multi = __ballot(b.K != 0u) != 0ull;
+      const uint32_t own = bm_range(PT_HALO, min(in_end, PT_HALO + PT_OWN), lane);
+      const uint8_t* ds = BATCH ? sh.dstart : nullptr;
+      uint32_t st;
+      if (PAT == TT_PATTERN_GPT2) {
+        st = gpt2_starts(b, sh.buf, ds, lane);
+      } else {
+        st = cl100k_starts(
+            b, own, sh.buf, ds, lane, t == 0,
+            [&](uint32_t sum) {
+              if (lane == 0) st_word(&w.tile_sum[t], ((uint64_t)w.epoch << 32) | sum);
+            },
+            [&]() -> RunCarry {
+              // back tile by tile (usually one step) to a tile whose trailing
+              // run does not span it
+              uint32_t acc = 0, sym = 0;
+              if (lane == 0) {
+                for (int64_t j = (int64_t)t - 1; j >= 0; --j) {
+                  const uint32_t v = (uint32_t)wait_word(&w.tile_sum[j], w.epoch);
+                  acc += (v >> 1) & 3u;
+                  if (!(v & SUM_RUNALL)) {
+                    sym = (v >> 3) & 1u;
+                    break;
+                  }
+                }
+              }
+              return RunCarry{wave_uniform(acc) % 3u, wave_uniform(sym) != 0u};
+            },
+            [&]() -> bool {
+              // The wave reads on, 16 bytes per lane per step, to the first byte
+              // that is not plain ASCII whitespace (space, tab, VT, FF) and
+              // decodes the character there (CR/LF: not the run's last stretch;
+              // other whitespace: read on after it; anything else, or the end
+              // of the text or document: the last).  Every lane holds the same
+              // position and answer; offsets are from the window's end.
+              if (w0 + PT_WIN >= n) return true;
+              const uint8_t* base = w.text + (w0 + PT_WIN);
+              int64_t lim = n;
+              if (BATCH) {
+                int lo = 0, hi = w.n_docs;
+                while (lo < hi) {
+                  int mid = (lo + hi) >> 1;
+                  if (w.doc_off[mid] < w0 + PT_WIN) lo = mid + 1;
+                  else hi = mid;
+                }
+                if (lo < w.n_docs && w.doc_off[lo] < lim) lim = w.doc_off[lo];
+              }
+              const uint32_t end = (uint32_t)(lim - (w0 + PT_WIN));
+              uint32_t pos = 0;
+              while (pos < end && (base[pos] & 0xC0u) == 0x80u) ++pos;
+#pragma unroll 1
+              for (;;) {
+                uint32_t first = 16u;
+#pragma unroll 4
+                for (int k = 15; k >= 0; --k) {
+                  const uint32_t p = pos + 16u * (uint32_t)lane + (uint32_t)k;
+                  const uint32_t c = p < end ? (uint32_t)base[p] : 0u;  // (the end counts as a stop)
+                  if (c != 0x20u && c != 0x09u && c != 0x0Bu && c != 0x0Cu) first = (uint32_t)k;
+                }
+                const uint64_t m = __ballot(first < 16u);
+                if (m == 0ull) {
+                  pos += 16u * 64u;
+                  continue;
+                }
+                const int src = __builtin_ctzll(m);
+                const uint32_t p = pos + 16u * (uint32_t)src + (uint32_t)__builtin_amdgcn_readlane((int)first, src);
+                if (p >= end) return true;
+                const uint32_t avail = end - p < 4u ? end - p : 4u;
+                auto at = [&](uint32_t k) -> uint32_t { return k < avail ? (uint32_t)base[p + k] : 0u; };
+                uint32_t cp = 0;
+                const uint32_t len = decode_sel(at(0), at(1), at(2), at(3), avail, cp);
+                if (len == 0u) return true;  // invalid input; reported elsewhere
+                if (cp == 10u || cp == 13u) return false;
+                if (cp < 128u || table_class(sh.ph.a.cls, cp) != 3u) return true;
+                pos = p + len;
+              }
+            });
       }
-    } else {
-      if (w0c) {
-        start = !w1c ? !(c1 == C_O && c0 == C_NL) : (c0 == C_NL ? false : run_last);
-        if (w1c && c0 != C_NL && c1 == C_NL) {
-          // first whitespace after a CR/LF stretch
-          uint32_t pre;
-          if (seg_has(ex)) {
-            int hp = prev(seg_head(ex));
-            pre = hp >= 0 ? cls(hp) : (uint32_t)C_NONE;
-          } else {
-            pre = sh.carry_nlpre;
-          }
-          if (pre == C_O) {
-            start = true;
-          } else {
-            const int r = ws_stretch_is_last(q);
-            start = r > 0;
-            if (r < 0) sh.ws_pend = q;  // (one stretch at most reaches the window's end)
-          }
-        }
-      } else if (c0 == C_N) {
-        const uint32_t off = seg_cnt(ex) + (seg_has(ex) ? 0u : sh.carry_n);
-        start = c1 != C_N || off % 3u == 0u;
-      } else if (c0 == C_O) {
-        start = c1 != C_O && !sp1;
-      } else {  // letter
-        start = c1 != C_L && c1 != C_WS;
-        if (c1 == C_O) {
-          // a lone symbol not preceded by U+0020 is the letter run's prefix
-          uint32_t cp2 = 0;
-          const uint32_t d2 = d1 == 1u ? prev_reg(j - 1, cp2) : d1 == 2u ? prev_reg(j - 2, cp2)
-                            : d1 == 3u ? prev_reg(j - 3, cp2) : prev_reg(j - 4, cp2);
-          start = d2 != 0u && (code_cls(cp2) == C_O || code_id(cp2) == I_SP);
-        }
-        if (apo1 || apo23) {
-          if (c1 == C_L) start = apo23 && contraction_ends_here(q);
-          else if (apo1 && contraction_len_at(q) > 0) start = false;
-        }
+      uint32_t u = st & own;
+      if (SEG && !IGN) u |= bm[BM_CUT * BM_STRIDE] & own & ~b.D;
+      const uint32_t c = (uint32_t)__popc(u);
+      const uint32_t incl = wave_incl_sum(c);
+      sh.uw[lane] = u;
+      sh.upre[lane] = incl - c;
+      if (lane == 63) sh.m = incl;
+      if (SEG && !IGN) {
+        // the tile's last unit start, published before this block waits on
+        // anything (a carry only waits for words published before any wait)
+        const int l = bm_last(u);
+        if (lane == 0) st_word(&w.tile_last[t], ((uint64_t)w.epoch << 32) | (l < 0 ? NO_START : (uint32_t)(w0 + l)));
       }
     }
-    if (d1 == 0u) start = true;
-    if (start) flags |= 1u << j;
+    __syncthreads();
+    flags = (sh.uw[tid >> 3] >> (qb & 31)) & 15u;
   }
   TT_PHASE(21);
-  if (PAT == TT_PATTERN_CL100K) {
-    // the whitespace stretch after CR/LF that reaches the window's end, if
-    // any: the block reads on past the window
-    __syncthreads();
-    const int pend = sh.ws_pend;
-    if (pend >= 0) {
-      // Wave 0 reads on, 16 bytes per lane per step, to the first byte that is
-      // not plain ASCII whitespace (space, tab, VT, FF) and decodes the
-      // character there (CR/LF: not the run's last stretch; other whitespace:
-      // read on after it; anything else, or the end of the text or document:
-      // the last).  Every lane holds the same position and answer; offsets
-      // are from the window's end.
-      if (wave == 0) {
-        const uint8_t* base = w.text + (w0 + PT_WIN);
-        int64_t lim = n;
-        if (BATCH) {
-          int lo = 0, hi = w.n_docs;
-          while (lo < hi) {
-            int mid = (lo + hi) >> 1;
-            if (w.doc_off[mid] < w0 + PT_WIN) lo = mid + 1;
-            else hi = mid;
-          }
-          if (lo < w.n_docs && w.doc_off[lo] < lim) lim = w.doc_off[lo];
-        }
-        const uint32_t end = (uint32_t)(lim - (w0 + PT_WIN));
-        uint32_t pos = 0, res = 2u;
-        while (pos < end && (base[pos] & 0xC0u) == 0x80u) ++pos;
-#pragma unroll 1
-        while (res == 2u) {
-          uint32_t first = 16u;
-#pragma unroll 4
-          for (int k = 15; k >= 0; --k) {
-            const uint32_t p = pos + 16u * (uint32_t)lane + (uint32_t)k;
-            const uint32_t b = p < end ? (uint32_t)base[p] : 0u;  // (the end counts as a stop)
-            if (b != 0x20u && b != 0x09u && b != 0x0Bu && b != 0x0Cu) first = (uint32_t)k;
-          }
-          const uint64_t m = __ballot(first < 16u);
-          if (m == 0ull) {
-            pos += 16u * 64u;
-            continue;
-          }
-          const int src = __builtin_ctzll(m);
-          const uint32_t p = pos + 16u * (uint32_t)src + (uint32_t)__builtin_amdgcn_readlane((int)first, src);
-          if (p >= end) {
-            res = 1u;
-            break;
-          }
-          const uint32_t avail = end - p < 4u ? end - p : 4u;
-          auto at = [&](uint32_t k) -> uint32_t { return k < avail ? (uint32_t)base[p + k] : 0u; };
-          uint32_t cp = 0;
-          const uint32_t len = decode_sel(at(0), at(1), at(2), at(3), avail, cp);
-          const uint32_t c = len == 0u ? (uint32_t)C_O : code_cls(char_code_sel<PAT>(sh.ph.a.cls, cp));
-          if (len == 0u) res = 1u;  // invalid input; reported elsewhere
-          else if (c == C_NL) res = 0u;
-          else if (c != C_WS) res = 1u;
-          else pos = p + len;
-        }
-        if (lane == 0) sh.ws_res = res;
-      }
-      __syncthreads();
-      if (sh.ws_res == 1u && tid == pend / PT_BPT) flags |= 1u << (pend % PT_BPT);
-    }
-  }
   const bool last = t == n_tiles - 1;
   if (IGN) {
     // ignore_merges: a piece that is a vocabulary entry is that entry's ID
@@ -1428,7 +1205,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
     __syncthreads();
   }
   TT_PHASE(22);
-  if (SEG) {
+  if (SEG && (WALK || IGN)) {
     // BPE segments: add the byte positions inside pieces that no merge spans
     // (q is not a piece start, so q - 1 lies in the same piece)
     const uint32_t* bwp = reinterpret_cast<const uint32_t*>(&sh.buf[PT_PAD + qb - 4]);
@@ -1440,7 +1217,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
       const uint32_t k2 = ((key & 255u) << 8) | (key >> 8);
       const bool joined = (sh.ph.a.join[k2 >> 5] >> (k2 & 31u)) & 1u;
       const bool eligible = q >= PT_HALO && q < PT_HALO + PT_OWN && inside(q) && inside(q - 1) &&
-                            !(flags & (1u << j)) && !(cr(j) & CODE_DOCSTART) &&
+                            !(flags & (1u << j)) && !((WALK || BATCH) && sh.dstart[PT_PAD + q]) &&
                             !(IGN && ((sh.ph.a.nocut[q >> 5] >> (q & 31)) & 1u));
       if (eligible && !joined) flags |= 1u << j;
     }
@@ -1448,20 +1225,27 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
 
   TT_PHASE(5);
   TT_PHASE_BY(24 + wave, lane == 0);
-  // ---- units: block scan of the start flags --------------------------------
+  // ---- units: numbered by the wave that found them, or by a block scan of the
+  // start flags
   const uint32_t cnt = __popc(flags);
-  const uint32_t inc = wave_incl_sum(cnt);
-  __syncthreads();
-  if (lane == 63) sh.wave_tot[wave] = inc;
-  __syncthreads();
-  uint32_t wpre = 0, m = 0;
-  for (int v = 0; v < PT_THREADS / 64; ++v) {
-    if (v < wave) wpre += sh.wave_tot[v];
-    m += sh.wave_tot[v];
+  uint32_t m, texcl;  // unit starts of the tile, and those before this thread's positions
+  if constexpr (WALK || IGN) {
+    const uint32_t inc = wave_incl_sum(cnt);
+    __syncthreads();
+    if (lane == 63) sh.wave_tot[wave] = inc;
+    __syncthreads();
+    uint32_t wpre = 0;
+    m = 0;
+    for (int v = 0; v < PT_THREADS / 64; ++v) {
+      if (v < wave) wpre += sh.wave_tot[v];
+      m += sh.wave_tot[v];
+    }
+    m = wave_uniform(m);
+    texcl = wave_uniform(wpre) + inc - cnt;
+  } else {
+    m = wave_uniform(sh.m);
+    texcl = sh.upre[tid >> 3] + (uint32_t)__popc(sh.uw[tid >> 3] & ((1u << (qb & 31)) - 1u));
   }
-  wpre = wave_uniform(wpre);
-  m = wave_uniform(m);
-  const uint32_t texcl = wpre + inc - cnt;  // unit starts before this thread's positions
 
   if (MODE == 0) {
     // split export: the tile's piece offsets go straight to their place
@@ -1475,7 +1259,9 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(6)))
 
   TT_PHASE(11);
   // the tile's last unit start, published before this block waits on anything
-  if (m == 0) {
+  if constexpr (!(WALK || IGN)) {
+    // (published with the starts)
+  } else if (m == 0) {
     if (tid == 0) st_word(&w.tile_last[t], ((uint64_t)w.epoch << 32) | NO_START);
   } else if (cnt != 0u && texcl + cnt == m) {
     st_word(&w.tile_last[t], ((uint64_t)w.epoch << 32) | (uint32_t)(w0 + qb + 31 - __builtin_clz(flags)));

@@ -1,0 +1,94 @@
+"""Piece starts from window bitmaps (``tt_runs.h``), at the places where a run
+or a character meets the edge of a bitmap word (32 bytes), of the window or of a
+tile (1,984 bytes, with 32 bytes of context): split level against the oracle."""
+
+import random
+
+import numpy as np
+import pytest
+
+from oracle.pretok import piece_byte_starts
+
+pytestmark = pytest.mark.gpu
+
+OWN = 1984
+# pieces of text whose rules look along a run or at neighbouring characters;
+# numbers, whitespace and symbols of one to four bytes among them
+PARTS = ["x's", "x'S", "x're y", "x'LL", "'ſt", "a'ſb", ".'s", " 's", "'", "''ll", "don't", "x'véa", "1", "12", "1234567",
+         "١٢٣٤٥", "１２３", "1²3", " ", "  ", "\t", " ", "　　", "\n", "\r\n", "\n\n \n", "\n  ", "!\n", "!\n\n  x", "?\r\n \t",
+         "a\n 　\n", "é", "中文", "Ж", "😀", "…", ".", "...", " .", "_x", "-é", "…a", " …a", "​"]
+
+
+def _tok(pattern, table=1):
+    from paper_2607_29678_amd import Tokenizer
+    from workloads.tables import load_table
+
+    return Tokenizer(*load_table(table), pattern)
+
+
+def _same(tok, text, pattern):
+    assert tok.pretokenize(text.encode()).tolist() == piece_byte_starts(text, pattern), repr(text[:80])
+
+
+@pytest.mark.parametrize("pattern", ["gpt2", "cl100k"])
+def test_parts_at_word_and_tile_edges(gpu, pattern):
+    rng = random.Random(5)
+    with _tok(pattern) as tok:
+        for edge in (32, OWN - 32, OWN, OWN + 32, 2 * OWN):
+            for _ in range(25):
+                before = "".join(rng.choice(PARTS) for _ in range(12))
+                after = "".join(rng.choice(PARTS) for _ in range(12))
+                pad = edge - rng.randint(0, 24) - len(before.encode())
+                fill = "ab " * (max(pad, 0) // 3 + 1)
+                _same(tok, fill[:max(pad, 0)] + before + after + " tail" * rng.randint(0, 20), pattern)
+
+
+@pytest.mark.parametrize("pattern", ["gpt2", "cl100k"])
+@pytest.mark.parametrize("run", ["7", "٣", "９", "\n", "\r\n", " ", "　", "\n ", "é", "?"])
+@pytest.mark.parametrize("n", [31, 33, 64, 700, 2200, 4100])
+def test_runs_across_tiles(gpu, pattern, run, n):
+    """Runs longer than the context before a tile, and longer than whole tiles,
+    after a symbol and after a letter."""
+    with _tok(pattern) as tok:
+        for lead in ("", "a", "!", " !", "1a\n"):
+            for off in (OWN - 40, OWN - 1, OWN):
+                for end in ("", "x", "\nx", "!", " x"):
+                    _same(tok, ("w " * OWN)[:off - len(lead)] + lead + run * n + end, pattern)
+
+
+@pytest.mark.parametrize("pattern", ["gpt2", "cl100k"])
+def test_documents_cut_every_rule(gpu, pattern):
+    """Short documents side by side: no rule looks across a document's start."""
+    from oracle.bpe import bpe
+    from oracle.pretok import pretokenize
+    from tests.conftest import oracle_table
+
+    rng = random.Random(9)
+    docs = ["".join(rng.choice(PARTS) for _ in range(rng.randint(0, 6))) for _ in range(1500)]
+    table = oracle_table(1)
+    with _tok(pattern) as tok:
+        for d, g in zip(docs, tok.encode_batch([d.encode() for d in docs])):
+            want = []
+            for a, b in pretokenize(d, pattern):
+                want += bpe(d[a:b].encode(), table)
+            assert g.tolist() == want, repr(d)
+
+
+@pytest.mark.parametrize("bad", [b"\x80", b"\xc3", b"\xe4\xb8", b"\xf0\x9f\x98", b"\xc1\xbf", b"\xe0\x9f\xbf", b"\xed\xa0\x80",
+                                 b"\xf4\x90\x80\x80", b"\xf5\x80\x80\x80", b"\xc3\xa9\xa9", b"\xff"])
+def test_invalid_bytes_at_every_place_of_a_word(gpu, bad):
+    """Also where the text or a document ends inside a character."""
+    from paper_2607_29678_amd import TokTierError
+
+    with _tok("cl100k") as tok:
+        for at in [0, 1, 2, 3, 30, 31, 32] + list(range(OWN - 5, OWN + 3)):
+            for tail in (b"", b"x", "é".encode(), b"x" * 40, b"y" * OWN):
+                with pytest.raises(TokTierError):
+                    tok.pretokenize(b"a" * at + bad + tail)
+            with pytest.raises(TokTierError):
+                tok.encode_batch([b"a" * at + bad, "é".encode(), b"x"])
+        cut = "x" * 7 + "😀"
+        for k in (1, 2, 3):  # a character split between two documents
+            with pytest.raises(TokTierError):
+                tok.encode_batch([cut.encode()[:-k], cut.encode()[-k:]])
+        assert np.array_equal(tok.pretokenize(cut.encode()), piece_byte_starts(cut, "cl100k"))
