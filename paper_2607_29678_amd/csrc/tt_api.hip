@@ -233,7 +233,6 @@ int ws_reserve(Workspace* s, uint64_t need, hipStream_t st) {
   size_t o_utile = take(4 * N);
   size_t o_upos = take(4 * N);
   size_t o_scr = take(4 * 4 * N + 8 * (N / 16 + 8));
-  size_t o_ccount = take(4 * (N / 4 + 2));
   size_t o_in = take(N + 64);
   size_t o_out = take(4 * N);
   size_t o_len = take(8);
@@ -256,7 +255,6 @@ int ws_reserve(Workspace* s, uint64_t need, hipStream_t st) {
   w.tile_last = reinterpret_cast<uint64_t*>(b + o_tlast);
   w.tile_agg = reinterpret_cast<uint64_t*>(b + o_tagg);
   w.tile_cagg = reinterpret_cast<uint64_t*>(b + o_tcagg);
-  w.ccount = reinterpret_cast<uint32_t*>(b + o_ccount);
   w.tile_pre = reinterpret_cast<uint32_t*>(b + o_tpre);
   w.stage = reinterpret_cast<uint32_t*>(b + o_stage);
   w.unit_tile = reinterpret_cast<uint32_t*>(b + o_utile);
@@ -406,7 +404,6 @@ int run_chain(tt_tokenizer* h, Workspace* s, const uint8_t* text, uint32_t n, co
   if (launch_tile(w, tb, h->pattern, mode, h->ignore && mode != 0, st) != hipSuccess) return TT_ERR_HIP;
   s->ticket_base += w.n_tiles;  // the tiles took their tickets
   if (d_docs && launch_doc_offsets(w, st) != hipSuccess) return TT_ERR_HIP;
-  if (mode == 2 && launch_spans(w, st) != hipSuccess) return TT_ERR_HIP;
   if (!mark()) return TT_ERR_HIP;
   if (ring) ++s->n_calls;
   return TT_OK;

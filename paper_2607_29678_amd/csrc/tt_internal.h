@@ -245,7 +245,6 @@ struct Work {
   uint32_t* unit_tile;      // batch: [n] processing tile of the unit starting at a byte
   uint32_t* unit_pos;       // batch: [n] its first output within that tile's outputs
   uint32_t* scratch;        // rows of units longer than 64 bytes: 4 * n words, then n / 16 + 8 masks
-  uint32_t* ccount;         // span export: [n/4 + 1] non-continuation bytes before byte 4w
   int32_t* out_spans;       // span export: [T][4] byte begin, byte end, char begin, char end
   int32_t* out_ids;         // output (caller IDs, or piece offsets for the split export)
   uint16_t* out16;          // encode without span export: when set, the IDs go here as 16-bit
@@ -275,8 +274,6 @@ inline uint32_t n_tiles_for(uint32_t n) { return (n + PT_OWN - 1) / PT_OWN; }
 // ignore: probe whole pieces in the vocabulary first (modes 1 and 2)
 hipError_t launch_tile(const Work& w, const DevTables& t, int pattern, int mode, bool ignore, hipStream_t s);
 hipError_t launch_doc_offsets(const Work& w, hipStream_t s);
-// span export, after the tile kernel: byte ends and character spans
-hipError_t launch_spans(const Work& w, hipStream_t s);
 
 // Facts of a handle for the host-side session code and the entry points
 // outside tt_api.hip.

@@ -274,6 +274,10 @@ union PhaseMem {
       } rows;
     } x;
   } b;
+  struct {                    // the tile's own outputs, in order
+    uint32_t id[PT_WIN];      // (over tok[]: written after it is read)
+    uint32_t span[PT_WIN];    // span export: byte start in the window | byte length << 16
+  } c;
 };
 
 template <bool WALK>
@@ -303,6 +307,7 @@ struct PtShared {
   int64_t o2_last_s, o2_last_e;  // walked patterns: the tile's last piece (window indices)
   uint32_t o2_pub;               //   and whether it is published yet
   uint32_t whole[PT_WIN / 32];  // ignore_merges: starts of pieces that are vocabulary entries
+  uint32_t ncw[BM_WORDS], ncpre[BM_WORDS];  // span export: non-continuation bytes, and those before each word
   uint32_t cbase;             // span export: non-continuation bytes before the tile
   uint32_t ctile;             // span export: non-continuation bytes the tile owns
   int64_t doc_lo_idx;         // batch: first document start index touching the window
@@ -314,6 +319,10 @@ struct PtShared {
 
 }  // namespace
 
+// A token's span as one store (the caller's array is aligned to its int32
+// elements only).
+typedef int Span __attribute__((ext_vector_type(4), aligned(4)));
+
 // Word a tile publishes for the placement of its outputs:
 //   bits 0..30 a count, bit 31 set when the count is inclusive (all outputs of
 //   the tiles up to this one) rather than this tile's own, bit 32 set when
@@ -322,9 +331,9 @@ struct PtShared {
 constexpr uint64_t PL_INC = 1ull << 31, PL_ERR = 1ull << 32;
 constexpr int PL_EPOCH_SHIFT = 33;
 
-// Decoupled look-back over the tiles' output counts (wave 0): publish this
-// tile's count, then sum the counts of earlier tiles, newest first, until a
-// tile whose published count is already inclusive.  A window of 64 earlier
+// Decoupled look-back over the tiles' output counts (wave 0; the tile's own
+// count is published before): sum the counts of earlier tiles, newest first,
+// until a tile whose published count is already inclusive.  A window of 64 earlier
 // tiles is read at once and read again until every tile the sum needs has
 // published (earlier tiles publish their own count before they look back, so
 // the walk never waits on a tile that is itself waiting).  Returns the number
@@ -360,6 +369,12 @@ __device__ __forceinline__ uint32_t lookback_counts(uint64_t* words, uint32_t t,
   return prefix;
 }
 
+// The tile's own count, published as soon as it is known (one thread).
+__device__ __forceinline__ void publish_count(const Work& w, uint32_t t, uint32_t count, bool bad) {
+  const uint64_t ep = (uint64_t)w.epoch << PL_EPOCH_SHIFT;
+  st_word(&w.tile_agg[t], ep | (t == 0 ? PL_INC : 0ull) | (bad ? PL_ERR : 0ull) | count);
+}
+
 template <class Sh>
 __device__ uint32_t place_tile(const Work& w, Sh& sh, uint32_t t, uint32_t count, bool bad, int tid, int lane,
                                int wave, uint64_t* cagg = nullptr, uint32_t c_tile = 0) {
@@ -381,41 +396,37 @@ __device__ uint32_t place_tile(const Work& w, Sh& sh, uint32_t t, uint32_t count
   uint64_t* pl = w.tile_agg;
   if (t == 0) {
     if (tid == 0) {
-      st_word(&pl[0], ep | PL_INC | (bad ? PL_ERR : 0ull) | count);
       sh.prefix = 0;
       sh.err = bad ? 1u : 0u;
     }
-  } else {
-    if (tid == 0) st_word(&pl[t], ep | (bad ? PL_ERR : 0ull) | count);
-    if (wave == 0) {
-      uint32_t prefix = 0;
-      bool err = bad;
-      int64_t base = (int64_t)t - 1;
-      for (;;) {
-        const int64_t j = base - lane;
-        uint64_t x = ep | PL_INC;  // before the first tile: an inclusive zero
-        if (j >= 0) x = ld_word(&pl[j]);
-        const bool ready = (x >> PL_EPOCH_SHIFT) == (uint64_t)w.epoch;
-        const uint64_t m_inc = __ballot(ready && (x & PL_INC));
-        const uint64_t m_rdy = __ballot(ready);
-        const int first = m_inc ? __ffsll((unsigned long long)m_inc) - 1 : 63;
-        const uint64_t need = first >= 63 ? ~0ull : ((2ull << first) - 1ull);
-        if ((m_rdy & need) != need) {
-          __builtin_amdgcn_s_sleep(1);
-          continue;
-        }
-        const bool use = lane <= first;
-        const uint32_t c = use ? (uint32_t)(x & 0x7FFFFFFFull) : 0u;
-        prefix += (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum(c), 63);
-        err = err || __ballot(use && (x & PL_ERR)) != 0ull;
-        if (m_inc) break;
-        base -= 64;
+  } else if (wave == 0) {
+    uint32_t prefix = 0;
+    bool err = bad;
+    int64_t base = (int64_t)t - 1;
+    for (;;) {
+      const int64_t j = base - lane;
+      uint64_t x = ep | PL_INC;  // before the first tile: an inclusive zero
+      if (j >= 0) x = ld_word(&pl[j]);
+      const bool ready = (x >> PL_EPOCH_SHIFT) == (uint64_t)w.epoch;
+      const uint64_t m_inc = __ballot(ready && (x & PL_INC));
+      const uint64_t m_rdy = __ballot(ready);
+      const int first = m_inc ? __ffsll((unsigned long long)m_inc) - 1 : 63;
+      const uint64_t need = first >= 63 ? ~0ull : ((2ull << first) - 1ull);
+      if ((m_rdy & need) != need) {
+        __builtin_amdgcn_s_sleep(1);
+        continue;
       }
-      if (lane == 0) {
-        st_word(&pl[t], ep | PL_INC | (err ? PL_ERR : 0ull) | (prefix + count));
-        sh.prefix = prefix;
-        sh.err = err ? 1u : 0u;
-      }
+      const bool use = lane <= first;
+      const uint32_t c = use ? (uint32_t)(x & 0x7FFFFFFFull) : 0u;
+      prefix += (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum(c), 63);
+      err = err || __ballot(use && (x & PL_ERR)) != 0ull;
+      if (m_inc) break;
+      base -= 64;
+    }
+    if (lane == 0) {
+      st_word(&pl[t], ep | PL_INC | (err ? PL_ERR : 0ull) | (prefix + count));
+      sh.prefix = prefix;
+      sh.err = err ? 1u : 0u;
     }
   }
   __syncthreads();
@@ -458,8 +469,8 @@ __device__ unsigned long long tt_phase_buf[TT_PHASE_TILES * TT_PHASE_SLOTS];
 
 // MODE 0: split-level export; the outputs are the byte offsets of the pieces.
 // MODE 1: encoding; the outputs are the (internal) IDs of the units' tokens.
-// MODE 2: encoding with span export: also the byte start of every token and the
-//         non-continuation byte count at every 4-byte word of the request.
+// MODE 2: encoding with span export: also the byte and character span of every
+//         token (Appendix, Route C; the records of Definition d:records).
 // WAVES:  wavefronts per SIMD the registers are allotted for: 6 (three blocks on
 //         a compute unit) or 8 (four; launch_pat says when).
 template <int PAT, bool BATCH, int MODE, bool IGN, int WAVES>
@@ -635,19 +646,17 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
   // at most (decoding at all four positions took 4.2, 10.4 at most).
   static_assert(PT_BPT == 4 && PT_PAD % 4 == 0, "classification works on aligned 4-byte words");
   bool bad = false;
-  uint32_t nc_own = 0;  // span export: non-continuation bytes among the thread's own positions
-  // (also counted again at the end, from the window bytes, instead of being kept)
-  auto own_noncont = [&](uint32_t bytes, int q0, int64_t p0) -> uint32_t {
-    const uint32_t cont = bytes & ~(bytes << 1) & 0x80808080u;  // bit 7 of each continuation byte
-    uint32_t c = 0;
-#pragma unroll
-    for (int j = 0; j < PT_BPT; ++j) {
-      const int q = q0 + j;
-      const bool own = q >= PT_HALO && q < PT_HALO + PT_OWN && p0 + j >= 0 && p0 + j < n;
-      c += (own && !((cont >> (8 * j + 7)) & 1u)) ? 1u : 0u;
-    }
-    return c;
-  };
+  if (SPANS) {
+    // the bitmap of non-continuation bytes (bytes that begin a character)
+    const int q0 = tid * PT_BPT;
+    const int64_t p0 = w0 + q0;
+    const uint32_t x = *reinterpret_cast<const uint32_t*>(&sh.buf[PT_PAD + q0]);
+    uint32_t nib = __builtin_amdgcn_udot4((~(x & ~(x << 1)) >> 7) & 0x01010101u, 0x08040201u, 0u, false);
+    if (p0 < 0 || p0 + PT_BPT > n)
+      for (int j = 0; j < PT_BPT; ++j)
+        if (p0 + j < 0 || p0 + j >= n) nib &= ~(1u << j);
+    store_nibbles(sh.ncw, q0, lane, nib);
+  }
   if constexpr (WALK) {
     const int q0 = tid * PT_BPT;
     const uint32_t* bw = reinterpret_cast<const uint32_t*>(&sh.buf[PT_PAD + q0 - 4]);
@@ -655,7 +664,6 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
     const uint32_t bw0 = bw[0], bw1 = bw[1], bw2 = bw[2];
     const uint32_t dw0 = dw[0], dw1 = dw[1], dw2 = dw[2];
     const int64_t p0 = w0 + q0;  // text position of the first of the four
-    if (SPANS) nc_own = own_noncont(bw1, q0, p0);
     uint32_t codes;
     if ((bw1 & 0x80808080u) == 0u && p0 >= 0 && p0 + PT_BPT <= n) {
       const uint8_t* asc = sh.ph.a.o2.asc;
@@ -718,7 +726,6 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
     const int64_t p0 = w0 + q0;  // text position of the first of the four
     const uint32_t* bw = reinterpret_cast<const uint32_t*>(&sh.buf[PT_PAD + q0 - 4]);
     const uint32_t x0 = bw[0], x1 = bw[1], x2 = bw[2];
-    if (SPANS) nc_own = own_noncont(x1, q0, p0);
     // the low bits of four bytes as a nibble
     auto nibble = [](uint32_t x) -> uint32_t { return __builtin_amdgcn_udot4(x & 0x01010101u, 0x08040201u, 0u, false); };
     uint32_t dw1 = 0;
@@ -774,18 +781,20 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
     if (BATCH) store_nibbles(sh.ph.a.bm_doc, q0, lane, nibble(dw1));
   }
   if constexpr (WALK) *reinterpret_cast<uint32_t*>(&sh.ph.a.o2piece[tid * PT_BPT]) = 0u;
-  if (SPANS) {
-    const uint32_t nc_incl = wave_incl_sum(nc_own);
-    if (lane == 63) sh.cwave[wave] = nc_incl;
-  }
   const bool tile_bad = __syncthreads_or(bad) != 0;
-  // span export: the tile's count is published before this block waits on
-  // anything (the look-back that sums it runs at the end)
-  if (SPANS && tid == 0) {
-    uint32_t c_tile = 0;
-    for (int v = 0; v < PT_THREADS / 64; ++v) c_tile += sh.cwave[v];
-    sh.ctile = c_tile;
-    st_word(&w.tile_cagg[t], ((uint64_t)w.epoch << PL_EPOCH_SHIFT) | c_tile);
+  // span export: the characters that begin before each word of the window, and
+  // the tile's own, published before this block waits on anything (the
+  // look-back that sums them runs at the end)
+  if (SPANS && wave == 1) {
+    const uint32_t x = sh.ncw[lane];
+    const uint32_t c = (uint32_t)__popc(x), incl = wave_incl_sum(c);
+    sh.ncpre[lane] = incl - c;
+    const uint32_t own = (uint32_t)__popc(x & bm_range(PT_HALO, PT_HALO + PT_OWN, lane));
+    const uint32_t c_tile = (uint32_t)__builtin_amdgcn_readlane((int)wave_incl_sum(own), 63);
+    if (lane == 0) {
+      sh.ctile = c_tile;
+      st_word(&w.tile_cagg[t], ((uint64_t)w.epoch << PL_EPOCH_SHIFT) | c_tile);
+    }
   }
 
   TT_PHASE(3);
@@ -1251,6 +1260,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
 
   if (MODE == 0) {
     // split export: the tile's piece offsets go straight to their place
+    if (tid == 0) publish_count(w, t, m, tile_bad);
     const uint32_t prefix = place_tile(w, sh, t, m, tile_bad, tid, lane, wave);
     uint32_t k = prefix + texcl;
 #pragma unroll 1
@@ -1578,6 +1588,10 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
     if (v < wave) cpre += sh.wave_tot[v];
     ctot += sh.wave_tot[v];
   }
+  // The count is published before the tokens are put in order, so that later
+  // tiles wait for neither that nor this tile's own look-back.
+  const uint32_t inc_cnt = has_inc ? sh.inc_cnt : 0u;
+  if (tid == 0) publish_count(w, t, inc_cnt + ctot, tile_bad);
   {
     uint32_t o = cpre + cinc - csum;
 #pragma unroll 1
@@ -1589,8 +1603,83 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
       }
     }
   }
-  const uint32_t inc_cnt = has_inc ? sh.inc_cnt : 0u;
-  // (place_tile ends with a barrier, which also publishes uoff to the block)
+  __syncthreads();
+  // Token o of unit k sits at position ustart[k] + o.  The tokens become the
+  // caller's IDs and are packed in order while the look-back's words arrive, so
+  // that after it every store is a full line of consecutive outputs (which
+  // matters most when the output is pinned host memory).
+  // Packing per wave after the look-back, with the count published only there,
+  // took 267 us for a 16M corpus (now 246), 47.6 us for 1M multilingual
+  // characters (45.2) and 18.7 us for 100K (17.5).
+  const int32_t* __restrict__ ext = tb.ext_id;
+  auto ext_of = [&](uint32_t v) -> int32_t { return v < tb.n_ids ? ext[v] : -1; };
+  auto len_of = [&](uint32_t v) -> uint32_t { return v < tb.n_ids ? tb.tok_len[v] : 0u; };
+  {
+    uint32_t before = texcl;  // unit starts at or before position q
+    uint32_t val[PT_BPT], at_of[PT_BPT], span[PT_BPT];
+    uint32_t has = 0;
+#pragma unroll
+    for (int j = 0; j < PT_BPT; ++j) {
+      const int q = qb + j;
+      const bool st = (flags >> j) & 1u;
+      before += st ? 1u : 0u;
+      val[j] = 0;
+      at_of[j] = 0;
+      span[j] = 0;
+      if (before == 0u || before - 1u >= m_proc) continue;
+      const uint32_t k = before - 1u;
+      const uint32_t o = (uint32_t)q - sh.ustart[k];
+      if (o < sh.ucnt[k]) {
+        const uint32_t tok = sh.ph.b.tok[q];
+        val[j] = (uint32_t)ext_of(tok);
+        at_of[j] = sh.ph.b.uoff[k] + o;
+        has |= 1u << j;
+        if (SPANS) span[j] = len_of(tok);
+      }
+      if (BATCH && st && sh.dstart[PT_PAD + q]) {
+        w.unit_tile[w0 + q] = t;
+        w.unit_pos[w0 + q] = inc_cnt + sh.ph.b.uoff[k];
+      }
+    }
+    if (SPANS) {
+      // byte start of every token: its unit's start plus the byte lengths of
+      // the unit's earlier tokens (byte-level BPE fixes every token's length):
+      // a scan over the positions, restarted at every unit start
+      constexpr uint32_t HEAD = 0x80000000u;
+      auto seg_add = [](uint32_t a, uint32_t b) -> uint32_t {
+        return (b & HEAD) ? b : ((a & HEAD) | ((a + b) & ~HEAD));
+      };
+      uint32_t agg = 0;
+#pragma unroll
+      for (int j = 0; j < PT_BPT; ++j) agg = seg_add(agg, (((flags >> j) & 1u) ? HEAD : 0u) | span[j]);
+      const uint32_t winc = wave_incl_scan(agg, lane, seg_add);
+      if (lane == 63) sh.cwave[wave] = winc;
+      uint32_t st = (uint32_t)__shfl_up((int)winc, 1, 64);
+      if (lane == 0) st = 0;
+      __syncthreads();
+      uint32_t wpre = 0;
+      for (int v = 0; v < wave; ++v) wpre = seg_add(wpre, sh.cwave[v]);
+      st = seg_add(wpre, st);
+      uint32_t bf = texcl;
+#pragma unroll
+      for (int j = 0; j < PT_BPT; ++j) {
+        const uint32_t hd = (flags >> j) & 1u, len = span[j];
+        bf += hd;
+        if ((has >> j) & 1u) span[j] = (sh.ustart[bf - 1u] + (hd ? 0u : (st & ~HEAD))) | (len << 16);
+        st = seg_add(st, (hd ? HEAD : 0u) | len);
+      }
+    }
+    __syncthreads();  // every read of tok[] and uoff[] is done
+#pragma unroll
+    for (int j = 0; j < PT_BPT; ++j)
+      if ((has >> j) & 1u) {
+        sh.ph.c.id[at_of[j]] = val[j];
+        if (SPANS) sh.ph.c.span[at_of[j]] = span[j];
+      }
+  }
+  uint32_t inc_val = 0;
+  if ((uint32_t)tid < inc_cnt) inc_val = (uint32_t)ext_of(w.stage[s_prev + (uint32_t)tid]);
+  // (place_tile ends with a barrier, which also publishes the packed outputs)
   const uint32_t prefix = place_tile(w, sh, t, inc_cnt + ctot, tile_bad, tid, lane, wave,
                                      SPANS ? w.tile_cagg : nullptr, SPANS ? sh.ctile : 0u);
   TT_PHASE(9);
@@ -1599,168 +1688,95 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
   // is discarded) can break that; the bound keeps it inside the buffer.
   const uint32_t lim = (uint32_t)n;
   int32_t* __restrict__ out = w.out_ids;
-  const int32_t* __restrict__ ext = tb.ext_id;
-  auto ext_of = [&](uint32_t v) -> int32_t { return v < tb.n_ids ? ext[v] : -1; };
-  // (narrow IDs: single requests of tt_encode only)
-  uint16_t* __restrict__ out16 = (SPANS || BATCH) ? nullptr : w.out16;
-  uint8_t* __restrict__ out_hi = (SPANS || BATCH) ? nullptr : w.out_hi;
-  for (uint32_t i = (uint32_t)tid; i < inc_cnt; i += PT_THREADS) {
-    if (prefix + i >= lim) continue;
-    const int32_t v = ext_of(w.stage[s_prev + i]);
+  uint16_t* __restrict__ out16 = SPANS ? nullptr : w.out16;
+  uint8_t* __restrict__ out_hi = SPANS ? nullptr : w.out_hi;
+  auto put = [&](uint32_t at, uint32_t v) {
+    if (at >= lim) return;
     if (out16) {
-      out16[prefix + i] = (uint16_t)v;
-      if (out_hi) out_hi[prefix + i] = (uint8_t)((uint32_t)v >> 16);
+      out16[at] = (uint16_t)v;
+      if (out_hi) out_hi[at] = (uint8_t)(v >> 16);
     } else {
-      out[prefix + i] = v;
+      out[at] = (int32_t)v;
     }
-  }
+  };
+  for (uint32_t i = (uint32_t)tid; i < inc_cnt; i += PT_THREADS)
+    put(prefix + i, i == (uint32_t)tid ? inc_val : (uint32_t)ext_of(w.stage[s_prev + i]));
   const uint32_t obase = prefix + inc_cnt;
-  // Token o of unit k sits at position ustart[k] + o, so the tokens of a
-  // wave's positions go to one contiguous range of the output, in position
-  // order.  Without span export (which reads tok[] again) each wave first
-  // packs its tokens at the front of its own part of tok[] and then writes
-  // the range with consecutive lanes on consecutive words: whole lines, which
-  // matters most when the output is pinned host memory.
-  uint32_t before = texcl;  // unit starts at or before position q
-  int32_t val[PT_BPT];
-  uint32_t at_of[PT_BPT];
-  uint32_t has = 0;
-#pragma unroll
-  for (int j = 0; j < PT_BPT; ++j) {
-    const int q = qb + j;
-    const bool st = (flags >> j) & 1u;
-    before += st ? 1u : 0u;
-    val[j] = 0;
-    at_of[j] = 0;
-    if (before == 0u || before - 1u >= m_proc) continue;
-    const uint32_t k = before - 1u;
-    const uint32_t o = (uint32_t)q - sh.ustart[k];
-    const uint32_t at = obase + sh.ph.b.uoff[k] + o;
-    if (o < sh.ucnt[k] && at < lim) {
-      val[j] = ext_of(sh.ph.b.tok[q]);
-      at_of[j] = at;
-      has |= 1u << j;
-    }
-    if (BATCH && st && sh.dstart[PT_PAD + q]) {
-      w.unit_tile[w0 + q] = t;
-      w.unit_pos[w0 + q] = inc_cnt + sh.ph.b.uoff[k];
-    }
-  }
-  if (SPANS) {
-#pragma unroll
-    for (int j = 0; j < PT_BPT; ++j)
-      if ((has >> j) & 1u) out[at_of[j]] = val[j];
-  } else {
-    const uint32_t mine = (uint32_t)__builtin_popcount(has);
-    const uint32_t incl = wave_incl_sum(mine);
-    const uint32_t n_wave = (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
-    const uint64_t holders = __ballot(mine != 0u);
-    // the wave's first output index (the lowest lane holding a token, its
-    // lowest position with one)
-    const uint32_t first = (has & 1u) ? at_of[0] : (has & 2u) ? at_of[1] : (has & 4u) ? at_of[2] : at_of[3];
-    const uint32_t base = holders ? (uint32_t)__builtin_amdgcn_readlane((int)first, (int)__builtin_ctzll(holders)) : 0u;
-    uint32_t* pack = &sh.ph.b.tok[wave * 64 * PT_BPT];
-    __syncthreads();  // every read of tok[] above is done
-    uint32_t r = incl - mine;
-#pragma unroll
-    for (int j = 0; j < PT_BPT; ++j)
-      if ((has >> j) & 1u) pack[r++] = (uint32_t)val[j];
-    __syncthreads();
-    // (valid text: the wave's indices are exactly base .. base + n_wave - 1)
-    if (out16) {
-      for (uint32_t i = (uint32_t)lane; i < n_wave; i += 64)
-        if (base + i < lim) out16[base + i] = (uint16_t)pack[i];
-      if (out_hi)
-        for (uint32_t i = (uint32_t)lane; i < n_wave; i += 64)
-          if (base + i < lim) out_hi[base + i] = (uint8_t)(pack[i] >> 16);
-    } else {
-      for (uint32_t i = (uint32_t)lane; i < n_wave; i += 64)
-        if (base + i < lim) out[base + i] = (int32_t)pack[i];
-    }
-  }
+  for (uint32_t i = (uint32_t)tid; i < ctot; i += PT_THREADS) put(obase + i, sh.ph.c.id[i]);
   if (BATCH && tid == 0 && has_inc) {
     w.unit_tile[s_prev] = t;
     w.unit_pos[s_prev] = 0;
   }
   if (SPANS) {
-    // byte start of every token: its unit's start plus the byte lengths of the
-    // unit's earlier tokens (byte-level BPE fixes every token's length)
-    auto len_of = [&](uint32_t v) -> uint32_t { return v < tb.n_ids ? tb.tok_len[v] : 0u; };
-    // the incoming unit's tokens, PT_THREADS at a time
-    uint32_t carry = 0;
-#pragma unroll 1
-    for (uint32_t base = 0; base < inc_cnt; base += PT_THREADS) {
-      const uint32_t i = base + (uint32_t)tid;
-      const uint32_t len = i < inc_cnt ? len_of(w.stage[s_prev + i]) : 0u;
-      const uint32_t wi = wave_incl_sum(len);
-      if (lane == 63) sh.cwave[wave] = wi;
-      __syncthreads();
-      uint32_t pre = 0, tot = 0;
-      for (int v = 0; v < PT_THREADS / 64; ++v) {
-        if (v < wave) pre += sh.cwave[v];
-        tot += sh.cwave[v];
-      }
-      if (i < inc_cnt && prefix + i < lim) w.out_spans[4 * (size_t)(prefix + i)] = (int32_t)(s_prev + carry + pre + wi - len);
-      carry += tot;
-      __syncthreads();
-    }
-    // the tile's own units: a scan over the window positions, restarted at
-    // every unit start, of the lengths of the tokens held there
-    constexpr uint32_t HEAD = 0x80000000u;
-    auto seg_add = [](uint32_t a, uint32_t b) -> uint32_t {
-      return (b & HEAD) ? b : ((a & HEAD) | ((a + b) & ~HEAD));
+    // Character spans from the count of non-continuation bytes before a byte:
+    // begin is the character that holds the token's first byte, end one past
+    // the character that holds its last.
+    Span* __restrict__ spans = reinterpret_cast<Span*>(w.out_spans);
+    const uint32_t c0 = sh.cbase - sh.ncpre[PT_HALO / 32];  // characters that begin before the window
+    auto chars_before = [&](uint32_t q) -> uint32_t {       // window position, below PT_WIN
+      return c0 + sh.ncpre[q >> 5] + (uint32_t)__popc(sh.ncw[q >> 5] & ((1u << (q & 31u)) - 1u));
     };
-    uint32_t e[PT_BPT];
-    uint32_t agg = 0;
-    {
-      uint32_t bf = texcl;
-#pragma unroll
-      for (int j = 0; j < PT_BPT; ++j) {
-        const int q = qb + j;
-        const uint32_t hd = (flags >> j) & 1u;
-        bf += hd;
-        const uint32_t k = bf - 1u;
-        const bool tokq = bf != 0u && k < m_proc && (uint32_t)q - sh.ustart[k] < sh.ucnt[k];
-        e[j] = tokq ? len_of(sh.ph.b.tok[q]) : 0u;
-        agg = seg_add(agg, (hd ? HEAD : 0u) | e[j]);
+    auto put_span = [&](uint32_t at, uint32_t b, uint32_t len) {  // b: byte start in the window
+      const uint32_t e = min(b + len, (uint32_t)PT_WIN - 1u);     // (a unit of the tile ends inside the window)
+      if (at < lim)
+        spans[at] = Span{(int)(w0 + b), (int)(w0 + e), (int)(chars_before(b + 1u) - 1u), (int)chars_before(e)};
+    };
+    for (uint32_t i = (uint32_t)tid; i < ctot; i += PT_THREADS) {
+      const uint32_t v = sh.ph.c.span[i];
+      put_span(obase + i, v & 0xFFFFu, v >> 16);
+    }
+    if (inc_cnt == 0u) {
+      // (no incoming unit)
+    } else if ((int64_t)s_prev >= w0) {
+      // the incoming unit lies in the window: one wave, 64 tokens at a time
+      if (wave == PT_THREADS / 64 - 1) {
+        uint32_t b = (uint32_t)((int64_t)s_prev - w0);
+#pragma unroll 1
+        for (uint32_t base = 0; base < inc_cnt; base += 64) {
+          const uint32_t i = base + (uint32_t)lane;
+          const uint32_t len = i < inc_cnt ? len_of(w.stage[s_prev + i]) : 0u;
+          const uint32_t incl = wave_incl_sum(len);
+          if (i < inc_cnt) put_span(prefix + i, b + incl - len, len);
+          b += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+        }
+      }
+    } else {
+      // a unit that starts before the window: the characters that begin between
+      // its start and the window, then a scan over its tokens, PT_THREADS at a
+      // time, of their lengths and of the characters that begin in them
+      auto begins = [&](uint32_t p) -> uint32_t { return (byte_abs(p) & 0xC0u) != 0x80u ? 1u : 0u; };
+      auto block_scan = [&](uint32_t v, uint32_t& total) -> uint32_t {  // exclusive
+        const uint32_t incl = wave_incl_sum(v);
+        __syncthreads();
+        if (lane == 63) sh.cwave[wave] = incl;
+        __syncthreads();
+        uint32_t pre = 0;
+        total = 0;
+        for (int k = 0; k < PT_THREADS / 64; ++k) {
+          if (k < wave) pre += sh.cwave[k];
+          total += sh.cwave[k];
+        }
+        return pre + incl - v;
+      };
+      uint32_t c = 0, total;
+      for (int64_t p = (int64_t)s_prev + tid; p < w0; p += PT_THREADS) c += begins((uint32_t)p);
+      block_scan(c, total);
+      uint32_t chars = c0 - total, byte = s_prev;  // before the unit's next tokens
+#pragma unroll 1
+      for (uint32_t base = 0; base < inc_cnt; base += PT_THREADS) {
+        const uint32_t i = base + (uint32_t)tid;
+        const uint32_t len = i < inc_cnt ? len_of(w.stage[s_prev + i]) : 0u;
+        uint32_t tb_all, tc_all;
+        const uint32_t b = byte + block_scan(len, tb_all);
+        uint32_t own = 0;
+        for (uint32_t k = 0; k < len && b + k < (uint32_t)n; ++k) own += begins(b + k);
+        const uint32_t cb = chars + block_scan(own, tc_all);
+        if (i < inc_cnt && prefix + i < lim)
+          spans[prefix + i] = Span{(int)b, (int)(b + len), (int)(cb - (b < (uint32_t)n && !begins(b) ? 1u : 0u)), (int)(cb + own)};
+        byte += tb_all;
+        chars += tc_all;
       }
     }
-    const uint32_t winc = wave_incl_scan(agg, lane, seg_add);
-    if (lane == 63) sh.cwave[wave] = winc;
-    uint32_t st = (uint32_t)__shfl_up((int)winc, 1, 64);
-    if (lane == 0) st = 0;
-    __syncthreads();
-    uint32_t wpre = 0;
-    for (int v = 0; v < wave; ++v) wpre = seg_add(wpre, sh.cwave[v]);
-    st = seg_add(wpre, st);
-    uint32_t bf = texcl;
-#pragma unroll
-    for (int j = 0; j < PT_BPT; ++j) {
-      const int q = qb + j;
-      const uint32_t hd = (flags >> j) & 1u;
-      bf += hd;
-      const uint32_t k = bf - 1u;
-      if (bf != 0u && k < m_proc) {
-        const uint32_t o = (uint32_t)q - sh.ustart[k];
-        const uint32_t at = obase + sh.ph.b.uoff[k] + o;
-        const uint32_t within = hd ? 0u : (st & ~HEAD);
-        if (o < sh.ucnt[k] && at < lim) w.out_spans[4 * (size_t)at] = (int32_t)(w0 + sh.ustart[k] + within);
-      }
-      st = seg_add(st, (hd ? HEAD : 0u) | e[j]);
-    }
-    // non-continuation bytes before every 4-byte word of the tile's own range
-    // (and before the end of the text), for the character spans
-    const int q0 = tid * PT_BPT;
-    const int64_t p0 = w0 + q0;
-    const uint32_t nc = own_noncont(*reinterpret_cast<const uint32_t*>(&sh.buf[PT_PAD + q0]), q0, p0);
-    const uint32_t nci = wave_incl_sum(nc);
-    __syncthreads();  // (the scan above has read sh.cwave)
-    if (lane == 63) sh.cwave[wave] = nci;
-    __syncthreads();
-    uint32_t c_excl = nci - nc;
-    for (int v = 0; v < wave; ++v) c_excl += sh.cwave[v];
-    if (q0 >= PT_HALO && q0 < PT_HALO + PT_OWN && p0 < n) w.ccount[p0 >> 2] = sh.cbase + c_excl;
-    if (last && tid == 0 && (n & 3) == 0) w.ccount[n >> 2] = sh.cbase + sh.ctile;
   }
 #ifdef TT_PHASE_STAMPS
   __syncthreads();
