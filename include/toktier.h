@@ -26,14 +26,15 @@
  *    immutable after registration).  Calls on one handle from several host
  *    threads are allowed if each thread uses its own stream; the handle keeps
  *    one workspace per stream.
- *  - Memory: a stream's workspace takes about 35 bytes of device memory per
+ *  - Memory: a stream's workspace takes about 26 bytes of device memory per
  *    byte of request capacity (epoch-tagged tile words, staging of tokens,
  *    rows of long units, the request bytes and IDs of host calls).  Host
- *    calls of tt_encode_spans add 16 bytes of device memory per byte, and
- *    host calls of tt_encode 5 bytes of pinned host memory per byte.  The
- *    capacity grows in powers of two from 64 KiB to the largest request seen
- *    on the stream (about 37 GB of device memory at TT_MAX_BYTES) and is freed
- *    by tt_destroy.
+ *    calls add 5 bytes of pinned host memory per byte; span export (and
+ *    sessions) 16 bytes of pinned host memory per byte up to 4 MiB, and past
+ *    that 16 bytes of device memory per byte; batches 16 bytes of pinned host
+ *    memory per document.  The capacity grows in powers of two from 64 KiB to
+ *    the largest request seen on the stream (about 28 GB of device memory at
+ *    TT_MAX_BYTES) and is freed by tt_destroy.
  */
 #ifndef TOKTIER_H
 #define TOKTIER_H
@@ -218,8 +219,9 @@ int tt_encode_device_noalloc(tt_tokenizer* h, const uint8_t* d_utf8, int64_t len
  *  out_ids        host buffer of at least max(doc_offsets[n_docs], 1) IDs.
  *  out_doc_offsets  n_docs+1 entries: document j's IDs are
  *                 out_ids[out_doc_offsets[j] .. out_doc_offsets[j+1]).
- * Every document must be valid UTF-8 on its own; otherwise
- * TT_ERR_INVALID_UTF8 and no output. */
+ * Blocks until the outputs are valid, with one synchronisation for up to
+ * 256 MiB (the way of tt_encode with pageable arrays).  Every document must be
+ * valid UTF-8 on its own; otherwise TT_ERR_INVALID_UTF8 and no output. */
 int tt_encode_batch(tt_tokenizer* h, const uint8_t* concat, const int64_t* doc_offsets,
                     int32_t n_docs, int32_t* out_ids, int64_t* out_doc_offsets, void* stream);
 
@@ -242,10 +244,11 @@ int tt_encode_batch(tt_tokenizer* h, const uint8_t* concat, const int64_t* doc_o
  *  out_ids        host buffer of at least max(len, 1) IDs.
  *  out_spans      host buffer of at least 4 * max(len, 1) int32 values.
  *  out_len        receives the number of IDs (and spans).
- * Blocks until the outputs are valid (two synchronisations; IDs and spans are
- * copied back together).  Invalid UTF-8 returns TT_ERR_INVALID_UTF8 and no
- * output.  The spans buffer of a stream's workspace is allocated on the first
- * call (16 bytes per byte of capacity). */
+ * Blocks until the outputs are valid: with one synchronisation for requests up
+ * to 4 MiB (IDs and spans are written into pinned staging and copied from
+ * there), with two past that.  Invalid UTF-8 returns TT_ERR_INVALID_UTF8 and no
+ * output.  The spans buffers of a stream's workspace are allocated on the first
+ * call. */
 int tt_encode_spans(tt_tokenizer* h, const uint8_t* utf8, int64_t len, int32_t* out_ids, int32_t* out_spans,
                     int64_t* out_len, void* stream);
 
@@ -376,8 +379,7 @@ int tt_info(const tt_tokenizer* h, int32_t* n_merges, int32_t* vocab_size, int32
 
 /* ---- measurement ------------------------------------------------------- */
 /* Stages of a call: one, the tile kernel (pre-tokenization, BPE and the
- * placement of every tile's outputs, Sec. 4.1-4.2), with the per-document
- * offsets of a batch. */
+ * placement of every tile's outputs, Sec. 4.1-4.2). */
 #define TT_N_STAGES 1
 
 /* Record HIP events between the stages of every later call on this handle and

@@ -4,10 +4,10 @@
 // Chain of one request (all on the caller's stream, no host round trip
 // between kernels; Sec. 4.3 keeps piece counts, dispatch lists and the output
 // length on the device and sizes launches from buffer capacity):
-//   tile kernel (pre-tokenize + BPE + placement of every tile's outputs)
-//   [-> document offsets, for batches]
-// The host synchronises twice per blocking call: once for the output length,
-// once for the IDs.
+//   tile kernel (pre-tokenize + BPE + placement of every tile's outputs, with
+//   the documents' offsets of a batch and the tokens' spans of a span export)
+// Blocking calls synchronise once (requests past 256 MiB, spans past 4 MiB and
+// the split export twice: for the length, then for the outputs).
 #include <algorithm>
 #include <cstdint>
 #include <cstdlib>
@@ -29,7 +29,6 @@ enum { ST_TILE, N_STAGES };
 
 struct Workspace {
   uint64_t cap = 0;           // bytes of request this workspace holds
-  int64_t doc_cap = 0;        // documents the batch buffers hold
   void* dmem = nullptr;       // one device allocation for everything below
   Work w{};                   // device pointers (text/out set per call)
   uint32_t epoch = 0;         // epoch of the latest call
@@ -38,8 +37,6 @@ struct Workspace {
   uint8_t* d_in = nullptr;    // staged request bytes (host calls)
   int32_t* d_out = nullptr;   // IDs (host calls)
   int64_t* d_len = nullptr;   // output length (host calls)
-  int64_t* d_docs = nullptr;  // batch: document byte offsets
-  int64_t* d_out_docs = nullptr;
   int32_t* d_spans = nullptr;  // span export (host calls): [span_cap][4], allocated on first use
   uint64_t span_cap = 0;
   int64_t* h_len = nullptr;   // pinned readback word
@@ -47,6 +44,12 @@ struct Workspace {
   uint64_t pin_cap = 0;        // bytes of request it holds
   uint8_t* h_in = nullptr;     // request bytes for the DMA (pageable callers)
   int32_t* h_ids = nullptr;    // IDs from the device (pageable callers)
+  int32_t* h_spans = nullptr;  // span export: [span_pin_cap][4], allocated on first use
+  uint64_t span_pin_cap = 0;
+  // batch: document byte offsets, the tiles' documents, and the output offsets
+  // (pinned; read and written by the device in place)
+  uint64_t* h_docs = nullptr;
+  uint64_t doc_cap = 0;        // 8-byte words it holds
   // profiling: stage boundaries of the most recent calls, a ring of
   // `ring` calls with N_STAGES + 1 events each
   std::vector<hipEvent_t> ev;
@@ -187,11 +190,12 @@ inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 void free_ws(Workspace* s) {
   if (!s) return;
   if (s->dmem) (void)hipFree(s->dmem);
-  if (s->d_docs) (void)hipFree(s->d_docs);
   if (s->d_spans) (void)hipFree(s->d_spans);
   if (s->h_len) (void)hipHostFree(s->h_len);
   if (s->h_in) (void)hipHostFree(s->h_in);
   if (s->h_ids) (void)hipHostFree(s->h_ids);
+  if (s->h_spans) (void)hipHostFree(s->h_spans);
+  if (s->h_docs) (void)hipHostFree(s->h_docs);
   for (auto e : s->ev)
     if (e) (void)hipEventDestroy(e);
   delete s;
@@ -228,10 +232,7 @@ int ws_reserve(Workspace* s, uint64_t need, hipStream_t st) {
   size_t o_tagg = take(8 * NT);
   size_t o_tcagg = take(8 * NT);
   const size_t ctl_bytes = off;
-  size_t o_tpre = take(4 * NT);
   size_t o_stage = take(4 * N);
-  size_t o_utile = take(4 * N);
-  size_t o_upos = take(4 * N);
   size_t o_scr = take(4 * 4 * N + 8 * (N / 16 + 8));
   size_t o_in = take(N + 64);
   size_t o_out = take(4 * N);
@@ -255,10 +256,7 @@ int ws_reserve(Workspace* s, uint64_t need, hipStream_t st) {
   w.tile_last = reinterpret_cast<uint64_t*>(b + o_tlast);
   w.tile_agg = reinterpret_cast<uint64_t*>(b + o_tagg);
   w.tile_cagg = reinterpret_cast<uint64_t*>(b + o_tcagg);
-  w.tile_pre = reinterpret_cast<uint32_t*>(b + o_tpre);
   w.stage = reinterpret_cast<uint32_t*>(b + o_stage);
-  w.unit_tile = reinterpret_cast<uint32_t*>(b + o_utile);
-  w.unit_pos = reinterpret_cast<uint32_t*>(b + o_upos);
   w.scratch = reinterpret_cast<uint32_t*>(b + o_scr);
   s->d_in = b + o_in;
   s->d_out = reinterpret_cast<int32_t*>(b + o_out);
@@ -266,17 +264,15 @@ int ws_reserve(Workspace* s, uint64_t need, hipStream_t st) {
   return TT_OK;
 }
 
-int ws_reserve_docs(Workspace* s, int64_t n_docs, hipStream_t st) {
-  if (n_docs + 1 <= s->doc_cap) return TT_OK;
-  if (s->d_docs && hipStreamSynchronize(st) != hipSuccess) return TT_ERR_HIP;
-  if (s->d_docs) (void)hipFree(s->d_docs);
-  s->d_docs = nullptr;
+// The pinned words of a batch: n_docs + 1 byte offsets, one word per tile, and
+// n_docs + 1 output offsets.  Only blocking calls use them.
+int reserve_docs(Workspace* s, uint64_t words) {
+  if (words <= s->doc_cap) return TT_OK;
+  if (s->h_docs) (void)hipHostFree(s->h_docs);
+  s->h_docs = nullptr;
   s->doc_cap = 0;
-  int64_t cap = std::max<int64_t>(n_docs + 1, 64);
-  void* m = nullptr;
-  if (hipMalloc(&m, 2 * 8 * cap) != hipSuccess) return TT_ERR_OOM;
-  s->d_docs = static_cast<int64_t*>(m);
-  s->d_out_docs = s->d_docs + cap;
+  const uint64_t cap = std::max<uint64_t>(words + words / 4, 512);
+  if (hipHostMalloc(reinterpret_cast<void**>(&s->h_docs), 8 * cap, hipHostMallocDefault) != hipSuccess) return TT_ERR_OOM;
   s->doc_cap = cap;
   return TT_OK;
 }
@@ -341,6 +337,20 @@ int reserve_pinned(Workspace* s, uint64_t len) {
   return TT_OK;
 }
 
+// The pinned spans of span export, the same way (at most 16 bytes per byte of
+// SPANS_PINNED_MAX).
+int reserve_pinned_spans(Workspace* s, uint64_t len) {
+  if (len <= s->span_pin_cap) return TT_OK;
+  if (s->h_spans) (void)hipHostFree(s->h_spans);
+  s->h_spans = nullptr;
+  s->span_pin_cap = 0;
+  const uint64_t cap = std::min<uint64_t>(s->cap, (uint64_t)SPANS_PINNED_MAX);
+  if (hipHostMalloc(reinterpret_cast<void**>(&s->h_spans), 16 * cap, hipHostMallocDefault) != hipSuccess)
+    return TT_ERR_OOM;
+  s->span_pin_cap = cap;
+  return TT_OK;
+}
+
 // Whether [p, p + len) is pinned host memory the device can read directly.
 bool host_pinned(const void* p, int64_t len) {
   hipPointerAttribute_t a;
@@ -356,12 +366,20 @@ bool host_pinned(const void* p, int64_t len) {
   return a.type == hipMemoryTypeHost;
 }
 
+// The documents of a batch, in memory the device reads and writes.
+struct BatchDocs {
+  const int64_t* offsets;  // [n + 1] byte offsets
+  int32_t n;
+  const uint2* tiles;      // Work::tile_docs
+  int64_t* out;            // [n + 1] output offsets
+};
+
 // Enqueue the whole chain for `n` bytes at device address `text`.
 // mode 0: split export (out_ids receives piece offsets); mode 1: encode;
 // mode 2: encode with span export into out_spans ([n][4], single requests).
-int run_chain(tt_tokenizer* h, Workspace* s, const uint8_t* text, uint32_t n, const int64_t* d_docs,
-              int32_t n_docs, int32_t* out_ids, int64_t* out_len, int64_t* out_docs, hipStream_t st, int mode,
-              int32_t* out_spans = nullptr, uint16_t* out16 = nullptr, uint8_t* out_hi = nullptr) {
+int run_chain(tt_tokenizer* h, Workspace* s, const uint8_t* text, uint32_t n, int32_t* out_ids, int64_t* out_len,
+              hipStream_t st, int mode, int32_t* out_spans = nullptr, uint16_t* out16 = nullptr,
+              uint8_t* out_hi = nullptr, const BatchDocs* docs = nullptr) {
   if (s->epoch + 1 >= EPOCH_LIMIT) {
     // epochs wrapped: clear the words that carry them and start again
     if (hipMemsetAsync(s->dmem, 0, s->ctl_bytes, st) != hipSuccess) return TT_ERR_HIP;
@@ -371,14 +389,15 @@ int run_chain(tt_tokenizer* h, Workspace* s, const uint8_t* text, uint32_t n, co
   Work w = s->w;
   w.text = text;
   w.n = n;
-  w.doc_off = d_docs;
-  w.n_docs = n_docs;
+  w.doc_off = docs ? docs->offsets : nullptr;
+  w.n_docs = docs ? docs->n : 0;
+  w.tile_docs = docs ? docs->tiles : nullptr;
+  w.out_doc_off = docs ? docs->out : nullptr;
   w.epoch = ++s->epoch;
   w.ticket_base = s->ticket_base;
   w.n_tiles = n_tiles_for(n);
   w.out_ids = out_ids;
   w.out_len = out_len;
-  w.out_doc_off = out_docs;
   w.out_spans = out_spans;
   w.out16 = mode == 1 ? out16 : nullptr;
   w.out_hi = mode == 1 && out16 ? out_hi : nullptr;
@@ -403,7 +422,6 @@ int run_chain(tt_tokenizer* h, Workspace* s, const uint8_t* text, uint32_t n, co
   if (!mark()) return TT_ERR_HIP;
   if (launch_tile(w, tb, h->pattern, mode, h->ignore && mode != 0, st) != hipSuccess) return TT_ERR_HIP;
   s->ticket_base += w.n_tiles;  // the tiles took their tickets
-  if (d_docs && launch_doc_offsets(w, st) != hipSuccess) return TT_ERR_HIP;
   if (!mark()) return TT_ERR_HIP;
   if (ring) ++s->n_calls;
   return TT_OK;
@@ -427,38 +445,129 @@ constexpr uint64_t PINNED_MAX = 1ull << 28;
 //    bits cross the bus as 16-bit values (half the bytes), in 24 bits as a
 //    16-bit array and an array of their third bytes (three quarters), and
 //    the copy threads widen them into the caller's array.
+//
+// Batches and span export go the same way, always through the staging on the
+// way out (they promise no output for invalid input), and so do the windows of
+// sessions.  Copying between pageable memory and the device instead, with a
+// second synchronisation for the length, took 254 us for 64 documents of about
+// 16,384 characters (now 138) and 182 us for the spans of 200,000 characters
+// (now 110); a session of 100,000 characters and 12 appends, which allocated
+// pinned buffers of its own and read back room for one token per byte, 938 us
+// (now 577).
+
+// The IDs of a staged call: where the device puts them and in what width.
+struct StagedIds {
+  int32_t* wide;       // int32 IDs
+  uint16_t* lo16;      // when set: the low 16 bits instead
+  uint8_t* hi8;        // when set: bits 16..23
+  // copy `count` of them, from `at`, as int32
+  void take(int32_t* dst, size_t at, size_t count) const {
+    if (count == 0) return;
+    if (lo16) host_widen(dst, lo16 + at, hi8 ? hi8 + at : nullptr, count);
+    else host_copy(dst, wide + at, 4 * count);
+  }
+};
+
+// Staging for the IDs of a request of `len` bytes: narrow when the handle's
+// IDs are (the third bytes lie after 2 * len bytes: 3 * len <= the 4 * capacity
+// bytes of h_ids).
+StagedIds staged_ids(const tt_tokenizer* h, Workspace* s, int64_t len) {
+  StagedIds o{s->h_ids, nullptr, nullptr};
+  if (h->id_bits < 32) o.lo16 = reinterpret_cast<uint16_t*>(s->h_ids);
+  if (h->id_bits == 24) o.hi8 = reinterpret_cast<uint8_t*>(s->h_ids) + 2 * (size_t)len;
+  return o;
+}
+
+// The request in memory the device can read: the caller's when it is pinned,
+// else the pinned copy.  out_pinned: nothing will be copied on the way out.
+const uint8_t* stage_in(Workspace* s, const uint8_t* utf8, int64_t len, bool out_pinned) {
+  const bool pin_in = host_pinned(utf8, len);
+  if (!out_pinned || !pin_in) host_copy_wake((size_t)len);  // (the IDs take about as many bytes)
+  if (pin_in) return utf8;
+  host_copy(s->h_in, utf8, (size_t)len);
+  return s->h_in;
+}
+
 int encode_staged(tt_tokenizer* h, Workspace* s, const uint8_t* utf8, int64_t len, int32_t* out_ids,
                   int64_t* out_len, hipStream_t st) {
   int rc = reserve_pinned(s, (uint64_t)len);
   if (rc) return rc;
-  const uint8_t* src = utf8;
   const bool pin_out = host_pinned(out_ids, 4 * len);
-  const bool pin_in = host_pinned(utf8, len);
-  if (!pin_out || !pin_in) host_copy_wake((size_t)len);  // (the IDs take about as many bytes)
-  if (!pin_in) {
-    host_copy(s->h_in, utf8, (size_t)len);
-    src = s->h_in;
-  }
+  const uint8_t* src = stage_in(s, utf8, len, pin_out);
   *s->h_len = 0;
   // the tile kernel writes the IDs at their places in pinned host memory
-  int32_t* dst = pin_out ? out_ids : s->h_ids;
-  // narrow staging: the low 16 bits at the start of h_ids, the third bytes
-  // after 2 * len bytes (3 * len <= the 4 * capacity bytes of h_ids)
-  const bool narrow = !pin_out && h->id_bits < 32;
-  uint16_t* lo16 = reinterpret_cast<uint16_t*>(s->h_ids);
-  uint8_t* hi8 = narrow && h->id_bits == 24 ? reinterpret_cast<uint8_t*>(s->h_ids) + 2 * (size_t)len : nullptr;
-  rc = run_chain(h, s, src, (uint32_t)len, nullptr, 0, dst, s->h_len, nullptr, st, 1, nullptr,
-                 narrow ? lo16 : nullptr, hi8);
+  const StagedIds o = pin_out ? StagedIds{out_ids, nullptr, nullptr} : staged_ids(h, s, len);
+  rc = run_chain(h, s, src, (uint32_t)len, o.wide, s->h_len, st, 1, nullptr, o.lo16, o.hi8);
   if (rc) return rc;
   if (hipStreamSynchronize(st) != hipSuccess) return TT_ERR_HIP;
   const int64_t T = *s->h_len;
   if (T < 0) return (int)T;
   if (T > len) return TT_ERR_HIP;  // cannot happen: at most one ID per byte
-  if (!pin_out && T > 0) {
-    if (narrow) host_widen(out_ids, lo16, hi8, (size_t)T);
-    else host_copy(out_ids, s->h_ids, 4 * (size_t)T);
-  }
+  if (!pin_out) o.take(out_ids, 0, (size_t)T);
   *out_len = T;
+  return TT_OK;
+}
+
+// Fill a batch's words for its tiles (Work::tile_docs): both ends of the
+// windows only move forward.
+void fill_tile_docs(const int64_t* offsets, int64_t n_docs, uint32_t n_tiles, uint2* tiles) {
+  int64_t lo = 0, hi = 0;
+  for (uint32_t t = 0; t < n_tiles; ++t) {
+    const int64_t w0 = (int64_t)t * PT_OWN - PT_HALO;
+    while (lo < n_docs && offsets[lo] < w0 - PT_PAD) ++lo;
+    while (hi < n_docs && offsets[hi] < w0 + PT_WIN) ++hi;
+    tiles[t] = make_uint2((uint32_t)lo, (uint32_t)hi);
+  }
+}
+
+// One batch over host documents.  On success *od points at the documents'
+// output offsets (n_docs + 1, in the stream's pinned words) and *ids says where
+// the IDs are: in the staging, or, past PINNED_MAX, in `far`.
+int batch_staged(tt_tokenizer* h, hipStream_t st, const uint8_t* concat, int64_t len, const int64_t* offsets,
+                 int64_t n_docs, StagedIds* ids, const int64_t** od, std::vector<int32_t>& far) {
+  if (n_docs > INT32_MAX) return TT_ERR_TOO_LARGE;
+  if (hipSetDevice(h->device) != hipSuccess) return TT_ERR_HIP;
+  Workspace* s = nullptr;
+  int rc = get_ws(h, st, (uint64_t)len, &s);
+  if (rc) return rc;
+  const uint32_t n_tiles = n_tiles_for((uint32_t)len);
+  const uint64_t nd = (uint64_t)n_docs + 1;
+  rc = reserve_docs(s, 2 * nd + n_tiles);
+  if (rc) return rc;
+  int64_t* doc = reinterpret_cast<int64_t*>(s->h_docs);
+  uint2* tiles = reinterpret_cast<uint2*>(s->h_docs + nd);
+  int64_t* out = reinterpret_cast<int64_t*>(s->h_docs + nd + n_tiles);
+  const BatchDocs docs{doc, (int32_t)n_docs, tiles, out};
+  const bool staged = (uint64_t)len <= PINNED_MAX;
+  const uint8_t* src = s->d_in;
+  int64_t* length = s->d_len;
+  *ids = StagedIds{s->d_out, nullptr, nullptr};
+  if (staged) {
+    rc = reserve_pinned(s, (uint64_t)len);
+    if (rc) return rc;
+    src = stage_in(s, concat, len, false);
+    length = s->h_len;
+    *ids = staged_ids(h, s, len);
+  } else if (hipMemcpyAsync(s->d_in, concat, (size_t)len, hipMemcpyHostToDevice, st) != hipSuccess) {
+    return TT_ERR_HIP;
+  }
+  std::memcpy(doc, offsets, 8 * nd);
+  fill_tile_docs(offsets, n_docs, n_tiles, tiles);
+  out[n_docs] = 0;
+  rc = run_chain(h, s, src, (uint32_t)len, ids->wide, length, st, 1, nullptr, ids->lo16, ids->hi8, &docs);
+  if (rc) return rc;
+  if (hipStreamSynchronize(st) != hipSuccess) return TT_ERR_HIP;
+  const int64_t T = out[n_docs];
+  if (T < 0) return (int)T;
+  if (T > len) return TT_ERR_HIP;  // cannot happen: at most one ID per byte
+  if (!staged) {
+    far.resize((size_t)std::max<int64_t>(T, 1));
+    if (hipMemcpyAsync(far.data(), s->d_out, (size_t)T * 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
+        hipStreamSynchronize(st) != hipSuccess)
+      return TT_ERR_HIP;
+    ids->wide = far.data();
+  }
+  *od = out;
   return TT_OK;
 }
 
@@ -568,41 +677,6 @@ int build_dict2(const std::vector<DictEntry>& entries2, std::vector<u32x4>& dict
 
 namespace {
 
-// The batch chain over host documents, with the IDs and per-document output
-// offsets copied back into host vectors (used by the added-token paths, whose
-// documents are the text segments and the literals between them).
-int batch_host(tt_tokenizer* h, hipStream_t st, const uint8_t* concat, int64_t len,
-               const std::vector<int64_t>& docs, std::vector<int32_t>& ids, std::vector<int64_t>& out_docs) {
-  const int64_t n_docs = (int64_t)docs.size() - 1;
-  if (n_docs > INT32_MAX) return TT_ERR_TOO_LARGE;
-  out_docs.assign(docs.size(), 0);
-  ids.clear();
-  if (len == 0) return TT_OK;
-  if (hipSetDevice(h->device) != hipSuccess) return TT_ERR_HIP;
-  Workspace* s = nullptr;
-  int rc = get_ws(h, st, (uint64_t)len, &s);
-  if (rc) return rc;
-  rc = ws_reserve_docs(s, n_docs, st);
-  if (rc) return rc;
-  if (hipMemcpyAsync(s->d_in, concat, (size_t)len, hipMemcpyHostToDevice, st) != hipSuccess ||
-      hipMemcpyAsync(s->d_docs, docs.data(), 8 * docs.size(), hipMemcpyHostToDevice, st) != hipSuccess)
-    return TT_ERR_HIP;
-  rc = run_chain(h, s, s->d_in, (uint32_t)len, s->d_docs, (int32_t)n_docs, s->d_out, s->d_len, s->d_out_docs, st, 1);
-  if (rc) return rc;
-  if (hipMemcpyAsync(s->h_len, s->d_len, 8, hipMemcpyDeviceToHost, st) != hipSuccess) return TT_ERR_HIP;
-  if (hipStreamSynchronize(st) != hipSuccess) return TT_ERR_HIP;
-  const int64_t T = *s->h_len;
-  if (T < 0) return (int)T;
-  if (T > len) return TT_ERR_HIP;  // cannot happen: at most one ID per byte
-  ids.resize((size_t)std::max<int64_t>(T, 1));
-  if (hipMemcpyAsync(ids.data(), s->d_out, (size_t)T * 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
-      hipMemcpyAsync(out_docs.data(), s->d_out_docs, 8 * docs.size(), hipMemcpyDeviceToHost, st) != hipSuccess)
-    return TT_ERR_HIP;
-  if (hipStreamSynchronize(st) != hipSuccess) return TT_ERR_HIP;
-  ids.resize((size_t)T);
-  return TT_OK;
-}
-
 // Documents of one text [a, b) of `t` around its added-token literals: text
 // before the first literal, the literal, text up to the next literal, and so
 // on (text documents may be empty); appends the boundaries after a to `docs`
@@ -634,34 +708,29 @@ DevTables handle_tables(const tt_tokenizer* h) {
 bool handle_has_added(const tt_tokenizer* h) { return !h->added.empty(); }
 uint32_t handle_max_token_bytes(const tt_tokenizer* h) { return h->max_tok_bytes; }
 
-// Span export of a small host request with one synchronisation: the length,
-// and `len` ID and span slots (at least the T written, since T <= len), leave
-// the device together.  h_in, h_ids, h_spans and h_len are pinned host memory
-// of at least len, len, 4 len and 1 entries.
-int encode_spans_pinned(tt_tokenizer* h, const uint8_t* h_in, int64_t len, int32_t* h_ids, int32_t* h_spans,
-                        int64_t* h_len, void* stream) {
-  if (!h || !h_in || !h_ids || !h_spans || !h_len) return TT_ERR_NULL_ARG;
-  if (!h->added.empty()) return TT_ERR_BAD_ARG;
-  if (len <= 0) return TT_ERR_BAD_ARG;
-  if (len > TT_MAX_BYTES) return TT_ERR_TOO_LARGE;
+int encode_spans_staged(tt_tokenizer* h, const uint8_t* utf8, int64_t len, int32_t** ids, int32_t** spans, int64_t* T,
+                        void* stream) {
+  if (!h || !utf8 || !ids || !spans || !T) return TT_ERR_NULL_ARG;
+  if (!h->added.empty() || len <= 0 || len > SPANS_PINNED_MAX) return TT_ERR_BAD_ARG;
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (hipSetDevice(h->device) != hipSuccess) return TT_ERR_HIP;
   Workspace* s = nullptr;
   int rc = get_ws(h, st, (uint64_t)len, &s);
   if (rc) return rc;
-  rc = reserve_spans(s, (uint64_t)len, st);
+  rc = reserve_pinned(s, (uint64_t)len);
   if (rc) return rc;
-  if (hipMemcpyAsync(s->d_in, h_in, (size_t)len, hipMemcpyHostToDevice, st) != hipSuccess) return TT_ERR_HIP;
-  rc = run_chain(h, s, s->d_in, (uint32_t)len, nullptr, 0, s->d_out, s->d_len, nullptr, st, 2, s->d_spans);
+  rc = reserve_pinned_spans(s, (uint64_t)len);
   if (rc) return rc;
-  if (hipMemcpyAsync(h_len, s->d_len, 8, hipMemcpyDeviceToHost, st) != hipSuccess ||
-      hipMemcpyAsync(h_ids, s->d_out, (size_t)len * 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
-      hipMemcpyAsync(h_spans, s->d_spans, (size_t)len * 16, hipMemcpyDeviceToHost, st) != hipSuccess)
-    return TT_ERR_HIP;
+  const uint8_t* src = stage_in(s, utf8, len, false);
+  *s->h_len = 0;
+  rc = run_chain(h, s, src, (uint32_t)len, s->h_ids, s->h_len, st, 2, s->h_spans);
+  if (rc) return rc;
   if (hipStreamSynchronize(st) != hipSuccess) return TT_ERR_HIP;
-  const int64_t T = *h_len;
-  if (T < 0) return (int)T;
-  if (T > len) return TT_ERR_HIP;  // cannot happen: at most one ID per byte
+  if (*s->h_len < 0) return (int)*s->h_len;
+  if (*s->h_len > len) return TT_ERR_HIP;  // cannot happen: at most one ID per byte
+  *T = *s->h_len;
+  *ids = s->h_ids;
+  *spans = s->h_spans;
   return TT_OK;
 }
 }  // namespace tt
@@ -1062,7 +1131,7 @@ int tt_encode_device(tt_tokenizer* h, const uint8_t* d_utf8, int64_t len, int32_
   Workspace* s = nullptr;
   int rc = get_ws(h, st, (uint64_t)len, &s);
   if (rc) return rc;
-  return run_chain(h, s, d_utf8, (uint32_t)len, nullptr, 0, d_out_ids, d_out_len, nullptr, st, 1);
+  return run_chain(h, s, d_utf8, (uint32_t)len, d_out_ids, d_out_len, st, 1);
 }
 
 int tt_encode(tt_tokenizer* h, const uint8_t* utf8, int64_t len, int32_t* out_ids, int64_t* out_len,
@@ -1081,9 +1150,10 @@ int tt_encode(tt_tokenizer* h, const uint8_t* utf8, int64_t len, int32_t* out_id
     std::vector<AddedSet::Match> lits;
     added_documents(h->added, utf8, 0, len, docs, lits);
     if (!lits.empty()) {
-      std::vector<int32_t> ids;
-      std::vector<int64_t> od;
-      int rc = batch_host(h, st, utf8, len, docs, ids, od);
+      std::vector<int32_t> far;
+      StagedIds ids;
+      const int64_t* od;
+      int rc = batch_staged(h, st, utf8, len, docs.data(), (int64_t)docs.size() - 1, &ids, &od, far);
       if (rc) return rc;
       int64_t T = 0;
       for (size_t j = 0; j + 1 < docs.size(); ++j) {
@@ -1091,7 +1161,7 @@ int tt_encode(tt_tokenizer* h, const uint8_t* utf8, int64_t len, int32_t* out_id
           out_ids[T++] = lits[j / 2].id;
         } else {
           const int64_t c = od[j + 1] - od[j];
-          if (c > 0) std::memcpy(out_ids + T, ids.data() + od[j], 4 * (size_t)c);
+          ids.take(out_ids + T, (size_t)od[j], (size_t)c);
           T += c;
         }
       }
@@ -1107,7 +1177,7 @@ int tt_encode(tt_tokenizer* h, const uint8_t* utf8, int64_t len, int32_t* out_id
   // very long requests: the length, then the IDs, straight between the caller's
   // memory and the device
   if (hipMemcpyAsync(s->d_in, utf8, (size_t)len, hipMemcpyHostToDevice, st) != hipSuccess) return TT_ERR_HIP;
-  rc = run_chain(h, s, s->d_in, (uint32_t)len, nullptr, 0, s->d_out, s->d_len, nullptr, st, 1);
+  rc = run_chain(h, s, s->d_in, (uint32_t)len, s->d_out, s->d_len, st, 1);
   if (rc) return rc;
   if (hipMemcpyAsync(s->h_len, s->d_len, 8, hipMemcpyDeviceToHost, st) != hipSuccess) return TT_ERR_HIP;
   if (hipStreamSynchronize(st) != hipSuccess) return TT_ERR_HIP;
@@ -1138,7 +1208,7 @@ int tt_encode_spans_device(tt_tokenizer* h, const uint8_t* d_utf8, int64_t len, 
   Workspace* s = nullptr;
   int rc = get_ws(h, st, (uint64_t)len, &s);
   if (rc) return rc;
-  return run_chain(h, s, d_utf8, (uint32_t)len, nullptr, 0, d_out_ids, d_out_len, nullptr, st, 2, d_out_spans);
+  return run_chain(h, s, d_utf8, (uint32_t)len, d_out_ids, d_out_len, st, 2, d_out_spans);
 }
 
 int tt_encode_spans(tt_tokenizer* h, const uint8_t* utf8, int64_t len, int32_t* out_ids, int32_t* out_spans,
@@ -1150,6 +1220,16 @@ int tt_encode_spans(tt_tokenizer* h, const uint8_t* utf8, int64_t len, int32_t* 
   *out_len = 0;
   if (len == 0) return TT_OK;
   hipStream_t st = static_cast<hipStream_t>(stream);
+  if (len <= SPANS_PINNED_MAX) {
+    int32_t *ids, *spans;
+    int64_t T = 0;
+    const int rc = encode_spans_staged(h, utf8, len, &ids, &spans, &T, stream);
+    if (rc) return rc;
+    host_copy(out_ids, ids, 4 * (size_t)T);
+    host_copy(out_spans, spans, 16 * (size_t)T);
+    *out_len = T;
+    return TT_OK;
+  }
   if (hipSetDevice(h->device) != hipSuccess) return TT_ERR_HIP;
   Workspace* s = nullptr;
   int rc = get_ws(h, st, (uint64_t)len, &s);
@@ -1157,7 +1237,7 @@ int tt_encode_spans(tt_tokenizer* h, const uint8_t* utf8, int64_t len, int32_t* 
   rc = reserve_spans(s, (uint64_t)len, st);
   if (rc) return rc;
   if (hipMemcpyAsync(s->d_in, utf8, (size_t)len, hipMemcpyHostToDevice, st) != hipSuccess) return TT_ERR_HIP;
-  rc = run_chain(h, s, s->d_in, (uint32_t)len, nullptr, 0, s->d_out, s->d_len, nullptr, st, 2, s->d_spans);
+  rc = run_chain(h, s, s->d_in, (uint32_t)len, s->d_out, s->d_len, st, 2, s->d_spans);
   if (rc) return rc;
   if (hipMemcpyAsync(s->h_len, s->d_len, 8, hipMemcpyDeviceToHost, st) != hipSuccess) return TT_ERR_HIP;
   if (hipStreamSynchronize(st) != hipSuccess) return TT_ERR_HIP;
@@ -1201,9 +1281,10 @@ int tt_encode_batch(tt_tokenizer* h, const uint8_t* concat, const int64_t* doc_o
     }
     first_doc[(size_t)n_docs] = (int64_t)docs.size() - 1;
     first_lit[(size_t)n_docs] = (int64_t)lits.size();
-    std::vector<int32_t> ids;
-    std::vector<int64_t> od;
-    int rc = batch_host(h, st, concat, len, docs, ids, od);
+    std::vector<int32_t> far;
+    StagedIds ids;
+    const int64_t* od;
+    int rc = batch_staged(h, st, concat, len, docs.data(), (int64_t)docs.size() - 1, &ids, &od, far);
     if (rc) return rc;
     int64_t T = 0;
     for (int32_t d = 0; d < n_docs; ++d) {
@@ -1213,7 +1294,7 @@ int tt_encode_batch(tt_tokenizer* h, const uint8_t* concat, const int64_t* doc_o
           out_ids[T++] = lits[(size_t)(first_lit[(size_t)d] + (j - first_doc[(size_t)d]) / 2)].id;
         } else {
           const int64_t c = od[(size_t)j + 1] - od[(size_t)j];
-          if (c > 0) std::memcpy(out_ids + T, ids.data() + od[(size_t)j], 4 * (size_t)c);
+          ids.take(out_ids + T, (size_t)od[(size_t)j], (size_t)c);
           T += c;
         }
       }
@@ -1221,27 +1302,13 @@ int tt_encode_batch(tt_tokenizer* h, const uint8_t* concat, const int64_t* doc_o
     out_doc_offsets[n_docs] = T;
     return TT_OK;
   }
-  if (hipSetDevice(h->device) != hipSuccess) return TT_ERR_HIP;
-  Workspace* s = nullptr;
-  int rc = get_ws(h, st, (uint64_t)len, &s);
+  std::vector<int32_t> far;
+  StagedIds ids;
+  const int64_t* od;
+  int rc = batch_staged(h, st, concat, len, doc_offsets, n_docs, &ids, &od, far);
   if (rc) return rc;
-  rc = ws_reserve_docs(s, n_docs, st);
-  if (rc) return rc;
-  if (hipMemcpyAsync(s->d_in, concat, (size_t)len, hipMemcpyHostToDevice, st) != hipSuccess) return TT_ERR_HIP;
-  if (hipMemcpyAsync(s->d_docs, doc_offsets, 8 * ((size_t)n_docs + 1), hipMemcpyHostToDevice, st) != hipSuccess)
-    return TT_ERR_HIP;
-  rc = run_chain(h, s, s->d_in, (uint32_t)len, s->d_docs, n_docs, s->d_out, s->d_len, s->d_out_docs, st, 1);
-  if (rc) return rc;
-  if (hipMemcpyAsync(s->h_len, s->d_len, 8, hipMemcpyDeviceToHost, st) != hipSuccess) return TT_ERR_HIP;
-  if (hipStreamSynchronize(st) != hipSuccess) return TT_ERR_HIP;
-  int64_t T = *s->h_len;
-  if (T < 0) return (int)T;
-  if (T > len) return TT_ERR_HIP;  // cannot happen: at most one ID per byte
-  if (hipMemcpyAsync(out_ids, s->d_out, (size_t)T * 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
-      hipMemcpyAsync(out_doc_offsets, s->d_out_docs, 8 * ((size_t)n_docs + 1), hipMemcpyDeviceToHost, st) !=
-          hipSuccess)
-    return TT_ERR_HIP;
-  if (hipStreamSynchronize(st) != hipSuccess) return TT_ERR_HIP;
+  ids.take(out_ids, 0, (size_t)od[n_docs]);
+  std::memcpy(out_doc_offsets, od, 8 * ((size_t)n_docs + 1));
   return TT_OK;
 }
 
@@ -1259,7 +1326,7 @@ int tt_pretokenize(tt_tokenizer* h, const uint8_t* utf8, int64_t len, int64_t* o
   int rc = get_ws(h, st, (uint64_t)len, &s);
   if (rc) return rc;
   if (hipMemcpyAsync(s->d_in, utf8, (size_t)len, hipMemcpyHostToDevice, st) != hipSuccess) return TT_ERR_HIP;
-  rc = run_chain(h, s, s->d_in, (uint32_t)len, nullptr, 0, s->d_out, s->d_len, nullptr, st, 0);
+  rc = run_chain(h, s, s->d_in, (uint32_t)len, s->d_out, s->d_len, st, 0);
   if (rc) return rc;
   if (hipMemcpyAsync(s->h_len, s->d_len, 8, hipMemcpyDeviceToHost, st) != hipSuccess) return TT_ERR_HIP;
   if (hipStreamSynchronize(st) != hipSuccess) return TT_ERR_HIP;

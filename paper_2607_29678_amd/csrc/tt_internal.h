@@ -230,6 +230,8 @@ struct Work {
   uint32_t n;               // bytes
   const int64_t* doc_off;   // batch: n_docs+1 byte offsets, else nullptr
   int32_t n_docs;
+  const uint2* tile_docs;   // batch: [tiles] the first document at or after the first byte of the
+                            // tile's padded window, and at or after the window's end
   Ctrl* ctrl;
   uint32_t epoch;           // this call's epoch
   uint32_t ticket_base;     // first tile ticket of this call
@@ -240,10 +242,7 @@ struct Work {
   uint64_t* tile_last;      // [tiles] (epoch << 32) | last unit start in the tile, or NO_START
   uint64_t* tile_agg;       // [tiles] output counts for the placement look-back (epoch-tagged)
   uint64_t* tile_cagg;      // [tiles] span export: non-continuation byte counts, same protocol
-  uint32_t* tile_pre;       // batch: [tiles] outputs of all earlier tiles
   uint32_t* stage;          // [n] tokens of incoming units, at the unit's first byte
-  uint32_t* unit_tile;      // batch: [n] processing tile of the unit starting at a byte
-  uint32_t* unit_pos;       // batch: [n] its first output within that tile's outputs
   uint32_t* scratch;        // rows of units longer than 64 bytes: 4 * n words, then n / 16 + 8 masks
   int32_t* out_spans;       // span export: [T][4] byte begin, byte end, char begin, char end
   int32_t* out_ids;         // output (caller IDs, or piece offsets for the split export)
@@ -251,7 +250,7 @@ struct Work {
                             // values instead (their low 16 bits when out_hi is set too)
   uint8_t* out_hi;          // with out16: bits 16..23 of every ID (every caller ID is below 2^24)
   int64_t* out_len;         // output length, or -error
-  int64_t* out_doc_off;     // batch: n_docs+1 output offsets (device)
+  int64_t* out_doc_off;     // batch: n_docs+1 output offsets, the last one the total or -error
 };
 
 // Tiles and geometry --------------------------------------------------------
@@ -273,7 +272,6 @@ inline uint32_t n_tiles_for(uint32_t n) { return (n + PT_OWN - 1) / PT_OWN; }
 // mode 2: encode with span export (single requests)
 // ignore: probe whole pieces in the vocabulary first (modes 1 and 2)
 hipError_t launch_tile(const Work& w, const DevTables& t, int pattern, int mode, bool ignore, hipStream_t s);
-hipError_t launch_doc_offsets(const Work& w, hipStream_t s);
 
 // Facts of a handle for the host-side session code and the entry points
 // outside tt_api.hip.
@@ -283,8 +281,11 @@ bool handle_ignore(const tt_tokenizer* h);  // ignore_merges
 DevTables handle_tables(const tt_tokenizer* h);
 bool handle_has_added(const tt_tokenizer* h);  // added-token literals (sessions do not take them)
 uint32_t handle_max_token_bytes(const tt_tokenizer* h);  // longest token, in bytes
-// span export of a small host request with one synchronisation (pinned buffers)
-int encode_spans_pinned(tt_tokenizer* h, const uint8_t* h_in, int64_t len, int32_t* h_ids, int32_t* h_spans,
-                        int64_t* h_len, void* stream);
+// Span export of a host request through the stream's pinned staging, with one
+// synchronisation: on success *ids and *spans point at the T records there,
+// valid (and writable) until the next call on the stream.  len <= SPANS_PINNED_MAX.
+constexpr int64_t SPANS_PINNED_MAX = 1 << 22;
+int encode_spans_staged(tt_tokenizer* h, const uint8_t* utf8, int64_t len, int32_t** ids, int32_t** spans, int64_t* T,
+                        void* stream);
 
 }  // namespace tt

@@ -202,19 +202,6 @@ struct tt_session {
   std::vector<int32_t> ids;       // records of the full tokenization of `text`
   std::vector<int32_t> spans;     // 4 per token, text coordinates
   std::vector<int32_t> f_ids, f_spans;  // records of a whole-text tokenization
-  // windows go through pinned buffers (one synchronisation per window)
-  int64_t pin_cap = 0;
-  uint8_t* p_in = nullptr;
-  int32_t* p_ids = nullptr;
-  int32_t* p_spans = nullptr;
-  int64_t* p_len = nullptr;
-
-  ~tt_session() {
-    if (p_in) (void)hipHostFree(p_in);
-    if (p_ids) (void)hipHostFree(p_ids);
-    if (p_spans) (void)hipHostFree(p_spans);
-    if (p_len) (void)hipHostFree(p_len);
-  }
 };
 
 namespace {
@@ -225,45 +212,16 @@ int64_t count_chars(const uint8_t* s, int64_t n) {
   return c;
 }
 
-constexpr int64_t PIN_MAX = 1 << 20;  // largest window staged in pinned memory (bytes)
-
-int grow_pinned(tt_session* s, int64_t n) {
-  if (n <= s->pin_cap) return TT_OK;
-  int64_t cap = 65536;
-  while (cap < n) cap <<= 1;
-  if (s->p_in) (void)hipHostFree(s->p_in);
-  if (s->p_ids) (void)hipHostFree(s->p_ids);
-  if (s->p_spans) (void)hipHostFree(s->p_spans);
-  s->p_in = nullptr;
-  s->p_ids = nullptr;
-  s->p_spans = nullptr;
-  s->pin_cap = 0;
-  if (!s->p_len && hipHostMalloc(reinterpret_cast<void**>(&s->p_len), 8, hipHostMallocDefault) != hipSuccess)
-    return TT_ERR_OOM;
-  if (hipHostMalloc(reinterpret_cast<void**>(&s->p_in), (size_t)cap, hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&s->p_ids), 4 * (size_t)cap, hipHostMallocDefault) != hipSuccess ||
-      hipHostMalloc(reinterpret_cast<void**>(&s->p_spans), 16 * (size_t)cap, hipHostMallocDefault) != hipSuccess)
-    return TT_ERR_OOM;
-  s->pin_cap = cap;
-  return TT_OK;
-}
-
 // Records of text[from, end) with spans shifted to text coordinates, in
-// *ids / *spans (the session's pinned buffers for a window, its vectors for a
+// *ids / *spans (the stream's pinned staging, or the session's vectors for a
 // longer range); returns the token count or an error.
 int64_t encode_range(tt_session* s, int64_t from, int64_t chars_before, void* stream, int32_t** ids,
                      int32_t** spans) {
   const int64_t n = (int64_t)s->text.size() - from;
   int64_t T = 0;
-  if (n <= PIN_MAX) {
-    int rc = grow_pinned(s, n);
+  if (n <= tt::SPANS_PINNED_MAX) {
+    const int rc = tt::encode_spans_staged(s->h, s->text.data() + from, n, ids, spans, &T, stream);
     if (rc != TT_OK) return rc;
-    std::memcpy(s->p_in, s->text.data() + from, (size_t)n);
-    rc = tt::encode_spans_pinned(s->h, s->p_in, n, s->p_ids, s->p_spans, s->p_len, stream);
-    if (rc != TT_OK) return rc;
-    T = *s->p_len;
-    *ids = s->p_ids;
-    *spans = s->p_spans;
   } else {
     s->f_ids.resize((size_t)n);
     s->f_spans.resize(4 * (size_t)n);

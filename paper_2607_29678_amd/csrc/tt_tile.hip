@@ -310,7 +310,6 @@ struct PtShared {
   uint32_t ncw[BM_WORDS], ncpre[BM_WORDS];  // span export: non-continuation bytes, and those before each word
   uint32_t cbase;             // span export: non-continuation bytes before the tile
   uint32_t ctile;             // span export: non-continuation bytes the tile owns
-  int64_t doc_lo_idx;         // batch: first document start index touching the window
   // walked patterns: where the run of each run set through the window's end
   // ends past it, its last tracked character there, and whether wave 0 has
   // published them
@@ -431,7 +430,6 @@ __device__ uint32_t place_tile(const Work& w, Sh& sh, uint32_t t, uint32_t count
   }
   __syncthreads();
   if (tid == 0) {
-    if (w.doc_off != nullptr) w.tile_pre[t] = sh.prefix;
     if (t == w.n_tiles - 1) *w.out_len = sh.err ? (int64_t)TT_ERR_INVALID_UTF8 : (int64_t)(sh.prefix + count);
   }
   return sh.prefix;
@@ -600,30 +598,14 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
     if (tid < NCH) stage_chunk(tid);
     else if (tid < NCH + 3) stage_chunk(tid == NCH ? -1 : tid - 1);  // [-8, 0) and [PT_WIN, PT_WIN + 16)
   }
+  uint2 docs = make_uint2(0u, 0u);  // batch: the first documents at or after the window's start and end
   if (BATCH) {
-    if (tid == 0) {
-      // first document start >= w0 - PT_PAD
-      int lo = 0, hi = w.n_docs;  // search in doc_off[0..n_docs)
-      while (lo < hi) {
-        int mid = (lo + hi) >> 1;
-        if (w.doc_off[mid] < w0 - PT_PAD) lo = mid + 1;
-        else hi = mid;
-      }
-      sh.doc_lo_idx = lo;
-      if (WALK) {
-        int a = lo, b = w.n_docs;  // first document start >= w0 + PT_WIN
-        while (a < b) {
-          int mid = (a + b) >> 1;
-          if (w.doc_off[mid] < w0 + PT_WIN) a = mid + 1;
-          else b = mid;
-        }
-        sh.o2_doc_after = a < w.n_docs ? w.doc_off[a] : n;
-      }
-    }
+    docs = w.tile_docs[t];
+    if (WALK && tid == 0) sh.o2_doc_after = docs.y < (uint32_t)w.n_docs ? w.doc_off[docs.y] : n;
   }
   __syncthreads();
   if (BATCH) {
-    for (int64_t j = sh.doc_lo_idx + tid; j < w.n_docs; j += PT_THREADS) {
+    for (int64_t j = (int64_t)docs.x + tid; j < w.n_docs; j += PT_THREADS) {
       int64_t d = w.doc_off[j];
       if (d >= w0 + PT_WIN + 16) break;
       if (d >= n) continue;
@@ -1106,13 +1088,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
               const uint8_t* base = w.text + (w0 + PT_WIN);
               int64_t lim = n;
               if (BATCH) {
-                int lo = 0, hi = w.n_docs;
-                while (lo < hi) {
-                  int mid = (lo + hi) >> 1;
-                  if (w.doc_off[mid] < w0 + PT_WIN) lo = mid + 1;
-                  else hi = mid;
-                }
-                if (lo < w.n_docs && w.doc_off[lo] < lim) lim = w.doc_off[lo];
+                if (docs.y < (uint32_t)w.n_docs) lim = w.doc_off[docs.y];
               }
               const uint32_t end = (uint32_t)(lim - (w0 + PT_WIN));
               uint32_t pos = 0;
@@ -1636,10 +1612,6 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
         has |= 1u << j;
         if (SPANS) span[j] = len_of(tok);
       }
-      if (BATCH && st && sh.dstart[PT_PAD + q]) {
-        w.unit_tile[w0 + q] = t;
-        w.unit_pos[w0 + q] = inc_cnt + sh.ph.b.uoff[k];
-      }
     }
     if (SPANS) {
       // byte start of every token: its unit's start plus the byte lengths of
@@ -1703,9 +1675,43 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
     put(prefix + i, i == (uint32_t)tid ? inc_val : (uint32_t)ext_of(w.stage[s_prev + i]));
   const uint32_t obase = prefix + inc_cnt;
   for (uint32_t i = (uint32_t)tid; i < ctot; i += PT_THREADS) put(obase + i, sh.ph.c.id[i]);
-  if (BATCH && tid == 0 && has_inc) {
-    w.unit_tile[s_prev] = t;
-    w.unit_pos[s_prev] = 0;
+  if (BATCH) {
+    // The output offset of every document whose first unit this tile encodes
+    // (a document starts a unit; empty documents share the start of the next
+    // one), and in the last tile the total, or the error, for those at the end.
+    if constexpr (!(WALK || IGN)) {
+      // (the unit starts are still there)
+    } else {
+      store_nibbles(sh.uw, qb, lane, flags);
+      if ((tid & 7) == 0) sh.upre[tid >> 3] = texcl;
+      __syncthreads();
+    }
+    for (int64_t j = (int64_t)docs.x + tid; j <= w.n_docs; j += PT_THREADS) {
+      const int64_t d = w.doc_off[j];
+      if (d >= n) {
+        if (!last) break;
+        w.out_doc_off[j] = sh.err ? (int64_t)TT_ERR_INVALID_UTF8 : (int64_t)(obase + ctot);
+        continue;
+      }
+      if (d >= t0 + PT_OWN) break;
+      if (has_inc && d == (int64_t)s_prev) {
+        w.out_doc_off[j] = prefix;
+      } else if (d >= t0) {
+        const uint32_t q = (uint32_t)(d - w0);
+        const uint32_t k = sh.upre[q >> 5] + (uint32_t)__popc(sh.uw[q >> 5] & ((1u << (q & 31u)) - 1u));
+        if (k < m_proc) w.out_doc_off[j] = obase + sh.ph.b.uoff[k];
+      }
+    }
+    // an incoming unit that starts before the listed documents
+    if (has_inc && (int64_t)s_prev < w0 - PT_PAD && tid == 0) {
+      int64_t lo = 0, hi = docs.x;
+      while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (w.doc_off[mid] < (int64_t)s_prev) lo = mid + 1;
+        else hi = mid;
+      }
+      for (; lo < (int64_t)docs.x && w.doc_off[lo] == (int64_t)s_prev; ++lo) w.out_doc_off[lo] = prefix;
+    }
   }
   if (SPANS) {
     // Character spans from the count of non-continuation bytes before a byte:
