@@ -10,13 +10,6 @@
 namespace tt {
 
 // ---------------------------------------------------------------------------
-// Character codes kept per byte in LDS by the walked patterns: the class in
-// bits 0..3, and
-//   bit  7     a document starts here (no context crosses this position)
-// ---------------------------------------------------------------------------
-constexpr uint32_t CODE_DOCSTART = 0x80u;
-
-// ---------------------------------------------------------------------------
 // Token IDs inside the library.  Byte b is ID b and the result of the merge
 // of rank r is ID 256 + r; the output stage maps them to the caller's IDs.
 // A proper merge list makes this a bijection onto the IDs BPE can produce
@@ -236,9 +229,7 @@ struct Work {
   uint32_t epoch;           // this call's epoch
   uint32_t ticket_base;     // first tile ticket of this call
   uint32_t n_tiles;
-  uint64_t* tile_sum;       // [tiles] (epoch << 32) | trailing-run summary (cl100k carries), or the
-                            // start of the tile's last piece (walked patterns)
-  uint64_t* tile_end;       // [tiles] walked patterns: (epoch << 32) | end of the tile's last piece
+  uint64_t* tile_sum;       // [tiles] (epoch << 32) | what the tile's last run brings into the next one
   uint64_t* tile_last;      // [tiles] (epoch << 32) | last unit start in the tile, or NO_START
   uint64_t* tile_agg;       // [tiles] output counts for the placement look-back (epoch-tagged)
   uint64_t* tile_cagg;      // [tiles] span export: non-continuation byte counts, same protocol

@@ -11,35 +11,32 @@
 // classify, runs, predicate, scans).  A block stages a 2,048-byte window (32
 // bytes of context on each side of the bytes it owns) in LDS, every thread
 // decodes and classifies four positions, and one wave evaluates the rules of
-// the GPT-2- and cl100k-style patterns on bitmaps of the window (tt_runs.h).
+// the pattern on bitmaps of the window (tt_runs.h).
 // Runs that reach past the window are resolved without a second pass:
-//   - backwards (cl100k: a number run's length mod 3, the class before a
-//     CR/LF stretch) from run summaries that earlier blocks publish before
-//     they wait on anything;
-//   - forwards (cl100k: whether a whitespace stretch after CR/LF is the last
-//     stretch of its run) by reading the bytes after the window, which only a
-//     whitespace stretch longer than the window needs.
+//   - backwards from summaries that earlier blocks publish;
+//   - forwards by reading the bytes after the window, which only a whitespace
+//     stretch or a run of capitals that reaches its end may need.
 //
 // Units.  For encoding, a piece is also cut at every byte position whose byte
 // pair (b[q-1], b[q]) is the junction of no merge: the first merge that joins
 // across a position has its left operand ending in b[q-1] and its right one
 // starting with b[q], so no merge ever crosses such a position and the two
-// sides are independent BPE problems.  The resulting units are numbered by a
-// block scan.
+// sides are independent BPE problems.
 //
 // BPE (Sec. 4.2, "GPU BPE").  The block encodes every unit that starts in its
 // bytes except its last one, whose end lies in a later tile: that unit is the
 // "incoming" unit of the next tile that has a unit start, which learns its
 // start from the position the earlier tiles publish right after their scan.
-// Units go to the smallest execution unit that holds them (thread, wave, or
-// the whole block over rows in LDS or, past the window size, global memory).
-// Tokens are compacted in the tile and staged in global memory where the
-// tile's bytes begin, so a tile's outputs never overlap another's; the emit
-// kernel only has to place each tile's block of outputs.
+// Units go to the smallest execution unit that holds them (part of a wave, a
+// wave, or the whole block over rows in LDS or, past the window size, global
+// memory), and the tile's tokens go to their place after a look-back over the
+// counts of earlier tiles.
 //
 // Block order is taken from an atomic ticket, so a block only ever waits on
-// blocks that started before it, and every block publishes what later blocks
-// wait for before it waits on anything itself.
+// blocks that started before it.  What a block publishes before it waits on
+// anything, later blocks get at once; the rest (counts of all tiles up to this
+// one, and o200k-style summaries of tiles whose own context does not tell) only
+// ever depends on earlier tiles.
 #include "class_table.inc"
 #include "class_table_o200k.inc"
 #include "class_table_deepseek.inc"
@@ -83,14 +80,15 @@ struct ClassLds {
   uint32_t asc[128];
 };
 
-// The 4-bit class table of a pattern whose pieces are walked (o200k-style,
-// DeepSeek-style; same layout, room for the larger), staged in LDS by every
-// block of that pattern, and the code of every ASCII character.
-constexpr int WALK_NBLOCKS = TT_O2_NBLOCKS > TT_DS_NBLOCKS ? TT_O2_NBLOCKS : TT_DS_NBLOCKS;
+// The 4-bit class table of the o200k- and DeepSeek-style patterns (same layout,
+// room for the larger), staged in LDS by every block, and the bitmap bits of
+// every ASCII character and of every class.
+constexpr int O2_NBLOCKS = TT_O2_NBLOCKS > TT_DS_NBLOCKS ? TT_O2_NBLOCKS : TT_DS_NBLOCKS;
 struct O2Lds {
   uint8_t l1[4352] __attribute__((aligned(16)));
-  uint8_t l2[WALK_NBLOCKS * 128] __attribute__((aligned(16)));
-  uint8_t asc[128];
+  uint8_t l2[O2_NBLOCKS * 128] __attribute__((aligned(16)));
+  uint2 asc[128];
+  uint2 cls[16];
 };
 
 // 2-bit class of a non-ASCII code point from the probed table.
@@ -100,31 +98,60 @@ __device__ __forceinline__ uint32_t table_class(const ClassLds& ct, uint32_t cp)
   return (b >> ((cp & 3u) * 2u)) & 3u;
 }
 
-// Code of one code point for the o200k-style pattern: its class only (the
-// walks read apostrophes, "/" and contraction letters from the bytes).
-__device__ __forceinline__ uint32_t o2_code(const O2Lds& t, uint32_t cp) {
-  if (cp < 128u) {
-    if ((cp - 'A') < 26u) return O2_UP;
-    if ((cp - 'a') < 26u) return O2_LO;
-    if ((cp - '0') < 10u) return O2_N;
-    if (cp == 10u || cp == 13u) return O2_NL;
-    if (cp == 32u || (cp - 9u) < 5u) return O2_WS;
-    return O2_O;
-  }
-  return o2_table_class(t.l1, t.l2, cp);
+// Class of an ASCII code point for the o200k-style pattern.
+__device__ __forceinline__ uint32_t o2_ascii_class(uint32_t cp) {
+  if ((cp - 'A') < 26u) return O2_UP;
+  if ((cp - 'a') < 26u) return O2_LO;
+  if ((cp - '0') < 10u) return O2_N;
+  if (cp == 10u || cp == 13u) return O2_NL;
+  if (cp == 32u || (cp - 9u) < 5u) return O2_WS;
+  return O2_O;
 }
-
-// Code of one code point for the DeepSeek-style pattern: its class only.
-// ASCII classes are computed: the ASCII table is built while the class table
-// is still being staged.
-__device__ __forceinline__ uint32_t ds_code(const O2Lds& t, uint32_t cp) {
-  return cp < 128u ? ds_ascii_class(cp) : ds_table_class(t.l1, t.l2, cp);
+// Bitmap bits (tt_runs.h) of a class of the o200k- and DeepSeek-style patterns,
+// and of an ASCII character.
+__device__ __forceinline__ uint2 bit_of(int k) {
+  return k < 8 ? make_uint2(1u << (4 * k), 0u) : make_uint2(0u, 1u << (4 * (k - 8)));
 }
-
-// Code of a code point for a walked pattern.
 template <int PAT>
-__device__ __forceinline__ uint32_t walk_code(const O2Lds& t, uint32_t cp) {
-  return PAT == TT_PATTERN_DEEPSEEK ? ds_code(t, cp) : o2_code(t, cp);
+__device__ __forceinline__ uint2 o2_class_bits(uint32_t c) {
+  if (PAT == TT_PATTERN_O200K) {
+    switch (c) {
+      case O2_UP: return bit_of(BM2_U);
+      case O2_LO: return bit_of(BM2_LO);
+      case O2_BO: return bit_of(BM2_X);
+      case O2_MK: return bit_of(BM2_M);
+      case O2_N: return bit_of(BM_N);
+      case O2_WS: return bit_of(BM_WS);
+      case O2_NL: return bit_of(BM_NL);
+      case O2_O: return bit_of(BM_O);
+    }
+    return make_uint2(0u, 0u);
+  }
+  switch (c) {
+    case DS_AL: return bit_of(BMD_AL);
+    case DS_L:
+    case DS_M: return bit_of(BMD_L);
+    case DS_N: return bit_of(BM_N);
+    case DS_AP: return bit_of(BMD_AP);
+    case DS_PS: return bit_of(BMD_PS);
+    case DS_SP:
+    case DS_WS: return bit_of(BM_WS);
+    case DS_NL: return bit_of(BM_NL);
+    case DS_KL:
+    case DS_KM: return bit_of(BMD_KL);
+    case DS_KP: return bit_of(BMD_KP);
+    case DS_KO: return bit_of(BMD_KO);
+    case DS_O: return bit_of(BMD_O);
+  }
+  return make_uint2(0u, 0u);
+}
+template <int PAT>
+__device__ __forceinline__ uint2 o2_ascii_bits(uint32_t cp) {
+  uint2 e = o2_class_bits<PAT>(PAT == TT_PATTERN_O200K ? o2_ascii_class(cp) : ds_ascii_class(cp));
+  if (cp == 32u) e.x |= bit_of(BM_SP).x;
+  if (PAT == TT_PATTERN_O200K && cp == 39u) e.y |= bit_of(BM2_APO).y;
+  if (PAT == TT_PATTERN_O200K && cp == 47u) e.y |= bit_of(BM2_SLASH).y;
+  return e;
 }
 
 // Bitmap bits (tt_runs.h) of an ASCII character, and of a character of a class
@@ -239,29 +266,27 @@ constexpr uint16_t U_INCOMING = 0xFFFFu;               // list entry for the inc
 // LDS of the classification phase and of the BPE phase share one region:
 // nothing of the first is read after the unit scan, nothing of the second is
 // written before it.
-template <bool WALK>
+template <bool WIDE>
 struct RulesMem;
 template <>
 struct RulesMem<false> {    // GPT-2, cl100k
   ClassLds cls;             // character classes
   uint32_t join[2048];      // junction byte pairs of the merges
-  uint32_t bm[BM_COUNT * BM_STRIDE];  // bitmaps of the window
-  uint32_t bm_doc[BM_WORDS];          // batch: document starts
-  uint32_t nocut[PT_WIN / 32];        // ignore_merges: window positions no junction cut may split
+  uint32_t bm[8 * BM_STRIDE];   // bitmaps of the window
+  uint32_t bm_doc[BM_WORDS];    // batch: document starts
+  uint32_t nocut[PT_WIN / 32];  // ignore_merges: window positions no junction cut may split
 };
 template <>
 struct RulesMem<true> {     // o200k, DeepSeek
-  O2Lds o2;                 // character classes
-  uint32_t join[2048];      // junction byte pairs of the merges
-  uint8_t code[PT_PAD + PT_WIN + 16] __attribute__((aligned(16)));  // class/doc-start codes
-  uint8_t o2piece[PT_WIN];  // 1 at the piece starts the walks find
-  uint32_t o2bits[WALK_BITMAPS * WIN_WORDS];  // class-set bitmaps of the window
-  uint32_t o2seg[PT_WIN / 32];    // segment starts (synchronizing positions, document starts)
-  uint32_t nocut[PT_WIN / 32];    // ignore_merges: window positions no junction cut may split
+  O2Lds cls;
+  uint32_t join[2048];
+  uint32_t bm[16 * BM_STRIDE];
+  uint32_t bm_doc[BM_WORDS];
+  uint32_t nocut[PT_WIN / 32];
 };
-template <bool WALK>
+template <bool WIDE>
 union PhaseMem {
-  RulesMem<WALK> a;
+  RulesMem<WIDE> a;
   struct {
     uint32_t tok[PT_WIN];     // tokens of unit k at tok[ustart[k] ..]
     uint16_t uoff[PT_WIN];    // first output of each unit within the tile
@@ -280,11 +305,11 @@ union PhaseMem {
   } c;
 };
 
-template <bool WALK>
+template <bool WIDE>
 struct PtShared {
   uint8_t buf[PT_PAD + PT_WIN + 16] __attribute__((aligned(16)));     // window bytes
   uint8_t dstart[PT_PAD + PT_WIN + 16] __attribute__((aligned(16)));  // 1 where a document starts
-  PhaseMem<WALK> ph;
+  PhaseMem<WIDE> ph;
   uint16_t ustart[PT_OWN + 2];  // window index of every unit start in the owned bytes
   uint16_t ucnt[PT_OWN + 2];    // tokens of each unit
   RowsShared<PT_THREADS / 64> rows;
@@ -303,17 +328,10 @@ struct PtShared {
   uint32_t uw[BM_WORDS], upre[BM_WORDS];  // unit starts, and those before each word
   uint32_t m;                 // their number
   uint32_t cwave[PT_THREADS / 64];  // span export: per-wave sums
-  int64_t o2_doc_after;          // walked patterns, batch: first document start after the window
-  int64_t o2_last_s, o2_last_e;  // walked patterns: the tile's last piece (window indices)
-  uint32_t o2_pub;               //   and whether it is published yet
   uint32_t whole[PT_WIN / 32];  // ignore_merges: starts of pieces that are vocabulary entries
   uint32_t ncw[BM_WORDS], ncpre[BM_WORDS];  // span export: non-continuation bytes, and those before each word
   uint32_t cbase;             // span export: non-continuation bytes before the tile
   uint32_t ctile;             // span export: non-continuation bytes the tile owns
-  // walked patterns: where the run of each run set through the window's end
-  // ends past it, its last tracked character there, and whether wave 0 has
-  // published them
-  FarRuns far;
 };
 
 }  // namespace
@@ -439,18 +457,16 @@ __device__ uint32_t place_tile(const Work& w, Sh& sh, uint32_t t, uint32_t count
 // TT_PHASE_STAMPS; the product build has none of this): thread 0 of every tile
 // writes the 100 MHz wall clock at each phase boundary into tt_phase_buf, slot
 // k of the tile's TT_PHASE_SLOTS, and tt_phase_stamps copies them to the host.
-// Slots: 0 entry, 1 ticket and tables, 2 window staged, 3 classified, 4 cl100k
-// scan done, 5 predicate done, 6 dispatch done, 7 thread and wave engines
-// done, 8 block engine done, 9 placement look-back done, 10 tokens written;
-// inside the dispatch 11 unit scan done, 12 unit starts listed, 13 incoming
-// unit found and dictionaries probed, 14 length lists built; inside the
-// walked patterns' predicate 16 bitmaps built, 17 extra starts and the first
-// wait done, 18 walks done, 19 flags done; 20 the incoming unit's start known
-// (by the thread that dispatches it); 21 the predicate's per-position rules
-// done (thread 0), 22 the cl100k read past the window and the vocabulary
-// probes of ignore_merges done; 23 the block index; 24 + w: wave w done with
-// the predicate (the same point as 5, per wave); 15 where the block runs (XCD
-// in the high word, the hardware ID register in the low word).
+// Slots: 0 entry, 1 ticket and tables, 2 window staged, 3 classified, 4 (span
+// export) character counts published, 5 piece and unit starts known, 6 dispatch
+// done, 7 wave engines done, 8 block engine done, 9 placement look-back done, 10
+// tokens written; inside the dispatch 11 units numbered, 12 unit starts listed,
+// 13 incoming unit found and dictionaries probed, 14 length lists built; 20 the
+// incoming unit's start known (by the thread that dispatches it); inside the
+// starts 21 the rules done, 22 the vocabulary probes of ignore_merges done; 23
+// the block index; 24 + w: wave w done with the starts (the same point as 5, per
+// wave); 15 where the block runs (XCD in the high word, the hardware ID register
+// in the low word).
 #ifdef TT_PHASE_STAMPS
 constexpr int TT_PHASE_SLOTS = 32, TT_PHASE_TILES = 8192;
 __device__ unsigned long long tt_phase_buf[TT_PHASE_TILES * TT_PHASE_SLOTS];
@@ -475,10 +491,9 @@ template <int PAT, bool BATCH, int MODE, bool IGN, int WAVES>
 __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))) void tile_kernel(Work w, DevTables tb) {
   constexpr bool SEG = MODE >= 1;
   constexpr bool SPANS = MODE == 2;
-  // the patterns whose pieces are walked between synchronizing positions
   constexpr bool DS = PAT == TT_PATTERN_DEEPSEEK;
-  constexpr bool WALK = PAT == TT_PATTERN_O200K || DS;
-  __shared__ PtShared<WALK> sh;
+  constexpr bool WIDE = PAT == TT_PATTERN_O200K || DS;  // 4-bit classes, up to 16 bitmaps
+  __shared__ PtShared<WIDE> sh;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
@@ -500,17 +515,18 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
   {
     // the class table (12.9 KB) is read once per block
     static_assert(CLS_L1_BYTES % 16 == 0 && CLS_L2_BYTES % 16 == 0, "class table staging uses 16-byte words");
-    if constexpr (WALK) {
+    if constexpr (WIDE) {
       constexpr int N1 = 4352 / 16, N2 = (DS ? TT_DS_NBLOCKS : TT_O2_NBLOCKS) * 128 / 16;
       const uint4* s1 = reinterpret_cast<const uint4*>(DS ? TT_DS_L1 : TT_O2_L1);
       const uint4* s2 = reinterpret_cast<const uint4*>(DS ? TT_DS_L2 : TT_O2_L2);
-      uint4* d1 = reinterpret_cast<uint4*>(sh.ph.a.o2.l1);
-      uint4* d2 = reinterpret_cast<uint4*>(sh.ph.a.o2.l2);
+      uint4* d1 = reinterpret_cast<uint4*>(sh.ph.a.cls.l1);
+      uint4* d2 = reinterpret_cast<uint4*>(sh.ph.a.cls.l2);
       for (int i = tid; i < N1 + N2; i += PT_THREADS) {
         if (i < N1) d1[i] = s1[i];
         else d2[i - N1] = s2[i - N1];
       }
-      if (tid < 128) sh.ph.a.o2.asc[tid] = (uint8_t)walk_code<PAT>(sh.ph.a.o2, (uint32_t)tid);
+      if (tid < 128) sh.ph.a.cls.asc[tid] = o2_ascii_bits<PAT>((uint32_t)tid);
+      if (tid >= 128 && tid < 144) sh.ph.a.cls.cls[tid - 128] = o2_class_bits<PAT>((uint32_t)(tid - 128));
     } else {
       constexpr int N1 = CLS_L1_BYTES / 16, N2 = CLS_L2_BYTES / 16;
       const uint4* s1 = reinterpret_cast<const uint4*>(TT_CLS_L1);
@@ -537,7 +553,6 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
     sh.n_big = 0;
     sh.inc_cnt = 0;
   }
-  if (tid < WALK_BITMAPS) sh.far.state[tid] = FAR_NONE;
   __syncthreads();
   const uint32_t t = wave_uniform(sh.tile);
   const uint32_t n_tiles = w.n_tiles;
@@ -583,7 +598,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
       v = make_uint2(lo, hi);
     }
     *reinterpret_cast<uint2*>(&sh.buf[PT_PAD + q0]) = v;
-    if (!WALK && !BATCH) return;  // (the text start is the only document start)
+    if (!BATCH) return;  // (the text start is the only document start)
     uint2 d = make_uint2(0u, 0u);
     if (p0 <= 0 && p0 + 8 > 0) d.x = (p0 == 0) ? 1u : 0u;  // the text start is a document start
     if (p0 < 0 && p0 + 8 > 0) {
@@ -601,7 +616,6 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
   uint2 docs = make_uint2(0u, 0u);  // batch: the first documents at or after the window's start and end
   if (BATCH) {
     docs = w.tile_docs[t];
-    if (WALK && tid == 0) sh.o2_doc_after = docs.y < (uint32_t)w.n_docs ? w.doc_off[docs.y] : n;
   }
   __syncthreads();
   if (BATCH) {
@@ -621,7 +635,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
   // decides everything from registers: a sequence starts at most three bytes
   // before a position it covers and ends at most three bytes after.  Four
   // ASCII bytes inside the text take their codes from the ASCII table.
-  // GPT-2- and cl100k-style: the codes are bits of the window's bitmaps, only
+  // The codes are bits of the window's bitmaps, only
   // the lead bytes of longer sequences are decoded, one after the other (a
   // word of valid text holds two at most), and continuation bytes are checked
   // as byte masks of the whole word: 2.0 us of a tile in multilingual text, 4.1
@@ -639,71 +653,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
         if (p0 + j < 0 || p0 + j >= n) nib &= ~(1u << j);
     store_nibbles(sh.ncw, q0, lane, nib);
   }
-  if constexpr (WALK) {
-    const int q0 = tid * PT_BPT;
-    const uint32_t* bw = reinterpret_cast<const uint32_t*>(&sh.buf[PT_PAD + q0 - 4]);
-    const uint32_t* dw = reinterpret_cast<const uint32_t*>(&sh.dstart[PT_PAD + q0 - 4]);
-    const uint32_t bw0 = bw[0], bw1 = bw[1], bw2 = bw[2];
-    const uint32_t dw0 = dw[0], dw1 = dw[1], dw2 = dw[2];
-    const int64_t p0 = w0 + q0;  // text position of the first of the four
-    uint32_t codes;
-    if ((bw1 & 0x80808080u) == 0u && p0 >= 0 && p0 + PT_BPT <= n) {
-      const uint8_t* asc = sh.ph.a.o2.asc;
-      codes = (uint32_t)asc[bw1 & 255u] | ((uint32_t)asc[(bw1 >> 8) & 255u] << 8) |
-              ((uint32_t)asc[(bw1 >> 16) & 255u] << 16) | ((uint32_t)asc[bw1 >> 24] << 24);
-      codes |= (dw1 & 0x01010101u) << 7;  // document starts (flags are 0 or 1)
-    } else {
-      const uint64_t blo = bw0 | ((uint64_t)bw1 << 32), bhi = bw1 | ((uint64_t)bw2 << 32);
-      const uint64_t dlo = dw0 | ((uint64_t)dw1 << 32), dhi = dw1 | ((uint64_t)dw2 << 32);
-      // r is relative to q0, in [-4, 8)
-      auto byt = [&](int r) -> uint32_t {
-        return r < 0 ? (uint32_t)(blo >> (8 * (r + 4))) & 255u : (uint32_t)(bhi >> (8 * r)) & 255u;
-      };
-      auto dst = [&](int r) -> bool {
-        return ((r < 0 ? (uint32_t)(dlo >> (8 * (r + 4))) : (uint32_t)(dhi >> (8 * r))) & 255u) != 0u;
-      };
-      auto ins = [&](int r) -> bool { return p0 + r >= 0 && p0 + r < n; };
-      codes = 0;
-#pragma unroll
-      for (int j = 0; j < PT_BPT; ++j) {
-        const int q = q0 + j;
-        const uint32_t b = byt(j);
-        const bool in_j = ins(j);
-        const bool own = q >= PT_HALO && q < PT_HALO + PT_OWN && in_j;
-        const bool cont = (b & 0xC0u) == 0x80u;
-        // a lead byte: its sequence, which a document start or the text end cuts
-        uint32_t avail = 1;
-        bool stop = false;
-#pragma unroll
-        for (int k = 1; k <= 3; ++k) {
-          stop = stop || !ins(j + k) || dst(j + k);
-          avail += stop ? 0u : 1u;
-        }
-        uint32_t cp = 0;
-        const uint32_t len = decode_sel(b, byt(j + 1), byt(j + 2), byt(j + 3), avail, cp);
-        // a continuation byte must lie inside the sequence of a lead byte at
-        // most three bytes earlier, with no document start in between
-        bool claimed = false, blocked = dst(j);
-#pragma unroll
-        for (int k = 1; k <= 3; ++k) {
-          const uint32_t br = byt(j - k);
-          const bool ok = ins(j - k), c = (br & 0xC0u) == 0x80u;
-          const uint32_t ll = br < 0x80u ? 1u : br < 0xC2u ? 0u : br < 0xE0u ? 2u : br < 0xF0u ? 3u : br < 0xF5u ? 4u : 0u;
-          claimed = claimed || (!blocked && ok && !c && ll > (uint32_t)k);
-          blocked = blocked || !ok || !c || dst(j - k);
-        }
-        const uint32_t code = (!in_j || cont) ? O2_NONE : len == 0u ? O2_O : walk_code<PAT>(sh.ph.a.o2, cp);
-        bad = bad || (own && (cont ? !claimed : len == 0u));
-        codes |= (code | (dst(j) ? CODE_DOCSTART : 0u)) << (8 * j);
-      }
-    }
-    *reinterpret_cast<uint32_t*>(&sh.ph.a.code[PT_PAD + q0]) = codes;
-    if (tid < 3) {  // positions outside [0, PT_WIN) carry no character for the rules
-      const int qx = tid == 0 ? -8 : PT_WIN + 8 * (tid - 1);
-      const uint32_t none4 = 0x0F0F0F0Fu;
-      *reinterpret_cast<uint2*>(&sh.ph.a.code[PT_PAD + qx]) = make_uint2(none4, none4);
-    }
-  } else {
+  {
     const int q0 = tid * PT_BPT;
     const int64_t p0 = w0 + q0;  // text position of the first of the four
     const uint32_t* bw = reinterpret_cast<const uint32_t*>(&sh.buf[PT_PAD + q0 - 4]);
@@ -723,10 +673,19 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
         cuts |= ((~sh.ph.a.join[k2 >> 5] >> (k2 & 31u)) & 1u) << j;
       }
     }
-    const uint32_t* asc = sh.ph.a.cls.asc;
-    uint32_t e = asc[x1 & 127u] | (asc[(x1 >> 8) & 127u] << 1) | (asc[(x1 >> 16) & 127u] << 2) | (asc[(x1 >> 24) & 127u] << 3);
+    const auto* asc = sh.ph.a.cls.asc;
+    const auto a0 = asc[x1 & 127u], a1 = asc[(x1 >> 8) & 127u], a2 = asc[(x1 >> 16) & 127u], a3 = asc[(x1 >> 24) & 127u];
+    uint32_t e, e2 = 0;  // bitmaps 0..7, and 8..15
+    if constexpr (WIDE) {
+      e = a0.x | (a1.x << 1) | (a2.x << 2) | (a3.x << 3);
+      e2 = a0.y | (a1.y << 1) | (a2.y << 2) | (a3.y << 3);
+    } else {
+      e = a0 | (a1 << 1) | (a2 << 2) | (a3 << 3);
+    }
     if (((x0 | x1) & 0x80808080u) != 0u) {
-      e &= nibble(~x1 >> 7) * 0x11111111u;  // (not the bytes above 127)
+      const uint32_t ascii = nibble(~x1 >> 7) * 0x11111111u;  // (not the bytes above 127)
+      e &= ascii;
+      e2 &= ascii;
       const bool own = q0 >= PT_HALO && q0 < PT_HALO + PT_OWN;
       static_assert(PT_HALO % PT_BPT == 0 && PT_OWN % PT_BPT == 0, "a word is the tile's own or not");
       // bit 7 of every byte: leads of at least two, three and four bytes, in
@@ -750,19 +709,28 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
         // one and the ranges of the second byte)
         const uint32_t len = decode_sel(b0, (v >> 8) & 255u, (v >> 16) & 255u, v >> 24, 4u, cp);
         bad = bad || (own && len == 0u);
-        e |= class_bits(table_class(sh.ph.a.cls, len ? cp : 0xFFFDu)) << j;
+        cp = len ? cp : 0xFFFDu;
+        if constexpr (WIDE) {
+          const auto& ct = sh.ph.a.cls;
+          const uint2 c = ct.cls[DS ? ds_table_class(ct.l1, ct.l2, cp) : o2_table_class(ct.l1, ct.l2, cp)];
+          e |= c.x << j;
+          e2 |= c.y << j;
+        } else {
+          e |= class_bits(table_class(sh.ph.a.cls, cp)) << j;
+        }
       }
     }
     if (p0 < 0 || p0 + PT_BPT > n) {  // nothing is set outside the text
       uint32_t in = 0;
       for (int j = 0; j < PT_BPT; ++j) in |= (p0 + j >= 0 && p0 + j < n ? 1u : 0u) << j;
       e &= in * 0x11111111u;
+      e2 &= in * 0x11111111u;
     }
     e |= cuts << (4 * BM_CUT);
     sh.ph.a.bm[(lane & 7) * BM_STRIDE + (tid >> 3)] = to_bitmaps(e, lane);
+    if constexpr (WIDE) sh.ph.a.bm[(8 + (lane & 7)) * BM_STRIDE + (tid >> 3)] = to_bitmaps(e2, lane);
     if (BATCH) store_nibbles(sh.ph.a.bm_doc, q0, lane, nibble(dw1));
   }
-  if constexpr (WALK) *reinterpret_cast<uint32_t*>(&sh.ph.a.o2piece[tid * PT_BPT]) = 0u;
   const bool tile_bad = __syncthreads_or(bad) != 0;
   // span export: the characters that begin before each word of the window, and
   // the tile's own, published before this block waits on anything (the
@@ -784,345 +752,128 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
   uint32_t flags = 0;           // bit j: a piece (then: a unit) starts at qb + j
   TT_PHASE(4);
   // ---- piece starts ---------------------------------------------------------
-  if constexpr (WALK) {
-    // cr(r) is the code of window position qb + r for r in [-8, 8)
-    const uint32_t* cwp = reinterpret_cast<const uint32_t*>(&sh.ph.a.code[PT_PAD + qb - 8]);
-    const uint32_t cw0 = cwp[0], cw1 = cwp[1], cw2 = cwp[2], cw3 = cwp[3];
-    auto cr = [&](int r) -> uint32_t {
-      const int i = r + 8;
-      const uint32_t lo = (i & 4) ? cw1 : cw0, hi = (i & 4) ? cw3 : cw2;
-      return (((i & 8) ? hi : lo) >> ((i & 3) * 8)) & 255u;
-    };
-    // o200k- and DeepSeek-style: segment starts are document starts,
-    // synchronizing positions (their two neighbouring characters form a
-    // transition of o2_sync or ds_sync) and two whitespace cases that start a
-    // piece for every left context given the text to their right (below);
-    // the pieces of a segment come from running the pattern's alternatives
-    // from its start, one lane per segment
-    auto walk_ws = [&](uint32_t cl) -> bool { return DS ? (cl == DS_SP || cl == DS_WS) : cl == O2_WS; };
-    auto walk_solid = [&](uint32_t cl) -> bool {  // not whitespace (DeepSeek-style: and of the rest group)
-      return DS ? (cl != DS_SP && cl != DS_WS && cl != DS_NL && ds_group(cl) == 0u)
-                : (cl != O2_WS && cl != O2_NL && cl != O2_NONE);
-    };
-    // Everything here is selects over the register window and table bits
-    // (o2_sync_bits, ds_sync_bits, the bitmap class masks): a switch over
-    // classes would be a tree of divergent branches.
-    // the window bytes qb - 4 .. qb + 3: the character before a position
-    // starts at most four bytes back
-    const uint32_t bwlo = *reinterpret_cast<const uint32_t*>(&sh.buf[PT_PAD + qb - 4]);
-    const uint32_t bwhi = *reinterpret_cast<const uint32_t*>(&sh.buf[PT_PAD + qb]);
-    auto wbyte = [&](int r) -> uint32_t {  // r in [-4, 4)
-      return ((r < 0 ? bwlo : bwhi) >> (8 * (r & 3))) & 255u;
-    };
-    uint32_t seg = 0;
-    uint32_t nib[WALK_BITMAPS];  // the class-set bitmaps' bits of the thread's four positions
-#pragma unroll
-    for (int k = 0; k < WALK_BITMAPS; ++k) nib[k] = 0;
-#pragma unroll
-    for (int j = 0; j < PT_BPT; ++j) {
-      const int q = qb + j;
-      const uint32_t c = cr(j);
-      const uint32_t cl = c & 15u;
-      const bool in_q = inside(q);
-      const bool dstart = (c & CODE_DOCSTART) != 0u;
-      // the character before q: its distance, class and (one-byte) byte
-      int k = 0;
-      uint32_t xc = O2_NONE, xb = 0x80u;
-#pragma unroll
-      for (int d = 4; d >= 1; --d) {
-        const bool lead = (cr(j - d) & 15u) != O2_NONE;
-        k = lead ? d : k;
-        xc = lead ? (cr(j - d) & 15u) : xc;
-        xb = lead ? (d == 1 ? wbyte(j - 1) : 0x80u) : xb;
-      }
-      const bool pair = (k > 0) && (q - k >= 0) &&
-                        (DS ? ds_sync_bits(xc, cl) : o2_sync_bits(xc, cl, xb, wbyte(j)));
-      // one-byte whitespace before a character that is not whitespace, in
-      // the same document (and, DeepSeek-style, the same group stretch): no
-      // piece holds whitespace past its first character unless the piece
-      // ends with whitespace or CR/LF (the alternatives that take whitespace
-      // runs), and those cannot end before a character that is not
-      // whitespace inside the stretch, so a piece starts here whatever the
-      // left context
-      const uint32_t c2 = cr(j + 1);
-      const bool ws_solid = walk_ws(cl) & inside(q + 1) & ((c2 & CODE_DOCSTART) == 0u) & walk_solid(c2 & 15u);
-      seg |= (uint32_t)(in_q & (cl != O2_NONE) & (dstart | pair | ws_solid)) << j;
-      // the class-set bitmaps (tt_o200k.h): the sets of a character at its
-      // first byte, the run sets at its continuation bytes, nothing at
-      // document starts and outside the text; and the ASCII digits
-      const bool in_b = in_q & !dstart;
-#pragma unroll
-      for (int kb = 0; kb < WALK_BITMAPS; ++kb) {
-        const uint32_t cls_k = DS ? ds_bitmap_classes(kb) : o2_bitmap_classes(kb);
-        const bool bit = kb == WB_DIGITS ? wbyte(j) - (uint32_t)'0' < 10u : ((cls_k >> cl) & 1u) != 0u;
-        nib[kb] |= (uint32_t)(in_b & bit) << j;
-      }
-    }
-    static_assert(PT_BPT == 4 && PT_THREADS * PT_BPT == PT_WIN, "eight lanes per bitmap word");
-    store_nibbles(sh.ph.a.o2seg, qb, lane, seg);
-#pragma unroll
-    for (int kb = 0; kb < WALK_BITMAPS; ++kb) store_nibbles(&sh.ph.a.o2bits[kb * WIN_WORDS], qb, lane, nib[kb]);
-    if (tid == 0) {  // the tile's last piece, until a walk finds it (kept only for invalid text)
-      sh.o2_last_s = PT_HALO;
-      sh.o2_last_e = n - w0 < PT_HALO + PT_OWN ? n - w0 : PT_HALO + PT_OWN;
-      sh.o2_pub = 0;
-    }
-    __syncthreads();
-    TT_PHASE(16);
-    const O2View v{(lds_u8*)sh.buf, (lds_u8*)sh.ph.a.code, (lds_u8*)sh.ph.a.o2.l1, (lds_u8*)sh.ph.a.o2.l2,
-                   w.text, w0, n, BATCH ? sh.o2_doc_after : n, (lds_u32*)sh.ph.a.o2bits,
-                   (lds_u8*)sh.ph.a.o2.asc, (lds_far*)&sh.far};
-    const int64_t own_end = n - w0 < PT_HALO + PT_OWN ? n - w0 : PT_HALO + PT_OWN;
-    auto segbit = [&](int64_t q) -> bool { return q >= 0 && q < PT_WIN && ((sh.ph.a.o2seg[q >> 5] >> (q & 31)) & 1u); };
-    {
-      // Whitespace right after CR/LF whose whitespace run holds no further
-      // CR/LF starts a piece whatever the left context: the CR/LF ends a
-      // symbol piece's CR/LF tail or a piece of the CR/LF alternative, which
-      // runs to the last CR/LF of its whitespace run.  The run is read from
-      // the bitmaps, so these marks come after the barrier; a walk of another
-      // wave that does not see one yet walks on through it, to the same
-      // pieces.
-      uint32_t add = 0;
-#pragma unroll
-      for (int j = 0; j < PT_BPT; ++j) {
-        const int q = qb + j;
-        const uint32_t c = cr(j);
-        if (((seg >> j) & 1u) || q < 1 || !inside(q) || !inside(q - 1) || (c & CODE_DOCSTART) || !walk_ws(c & 15u) ||
-            (cr(j - 1) & 15u) != (DS ? (uint32_t)DS_NL : (uint32_t)O2_NL))
-          continue;
-        const int64_t r = win_next_zero(v.bits + (DS ? DSB_SP : O2B_SP) * WIN_WORDS, q);
-        if (r < PT_WIN && win_last_one(v.bits + (DS ? DSB_NL : O2B_NL) * WIN_WORDS, q, r) < 0) add |= 1u << j;
-      }
-      if (add) {
-        seg |= add;
-        atomicOr(&sh.ph.a.o2seg[qb >> 5], add << (qb & 31));
-      }
-    }
-    // one loop per lane, one piece per step: the lane's walk starts in order
-    // (thread 0's continued segment first, then its own segment starts), so
-    // a wave runs as long as its busiest lane, not its longest segment of
-    // every start
-    // thread 0 first walks the segment that the tile's first bytes continue,
-    // from its start in the left context, else from the end of the last piece
-    // of the previous tile (which holds the previous tile's last byte, so its
-    // end is at or after this tile's first byte).  When that piece also holds
-    // this tile's last byte, the tile has no piece start of its own and
-    // passes the piece on without walking: a long piece is walked once, by the
-    // tile it starts in, not again by every tile it covers.
-    // The last piece of the tile (the one that holds its last byte) is kept in
-    // last_s / last_e (their defaults were set before the barrier above, so
-    // that no walk's write can come before them), and the next tile continues
-    // from it: the lane that finds it publishes it at once (the next tile may
-    // be waiting for it), not after the tile's other walks.
-    auto publish_last = [&](int64_t ps, int64_t pe) {
-      const uint64_t ep = (uint64_t)w.epoch << 32;
-      st_word(&w.tile_end[t], ep | (uint32_t)(w0 + pe));
-      st_word(&w.tile_sum[t], ep | (uint32_t)(w0 + ps));
-      sh.o2_pub = 1u;
-    };
-    int64_t first = -1;
-    if (tid == 0 && !segbit(PT_HALO)) {
-      for (int q = PT_HALO - 1; q >= 0 && first < 0; --q)
-        if (segbit(q)) first = q;
-      if (first < 0 && t == 0) first = PT_HALO;  // (invalid text: no character at the text start)
-      if (first < 0) {
-        const uint64_t xs = wait_word(&w.tile_sum[t - 1], w.epoch);
-        const uint64_t xe = wait_word(&w.tile_end[t - 1], w.epoch);
-        const int64_t ps = (int64_t)(uint32_t)xs - w0, pe = (int64_t)(uint32_t)xe - w0;
-        if (pe >= own_end) {
-          sh.o2_last_s = ps;
-          sh.o2_last_e = pe;
-          publish_last(ps, pe);
-        } else {
-          first = pe < PT_HALO ? PT_HALO : pe;  // (pe < PT_HALO only for invalid text)
-        }
-      }
-    }
-    TT_PHASE(17);
-    uint32_t todo = 0;  // bit j: own position qb + j starts a segment to walk
-#pragma unroll
-    for (int j = 0; j < PT_BPT; ++j)
-      if (((seg >> j) & 1u) && qb + j >= PT_HALO && qb + j < own_end) todo |= 1u << j;
-    // The wave's segment starts are dealt to its lanes in turn (a lane whose
-    // four bytes hold several starts does not walk them all): rank r counts
-    // the starts at byte j = 0 of every lane first, then j = 1, and so on;
-    // lane l walks ranks l, l + 64, ...
-    const uint64_t sb0 = __ballot(todo & 1u), sb1 = __ballot(todo & 2u), sb2 = __ballot(todo & 4u),
-                   sb3 = __ballot(todo & 8u);
-    const uint32_t sn0 = (uint32_t)__builtin_popcountll(sb0), sn1 = (uint32_t)__builtin_popcountll(sb1),
-                   sn2 = (uint32_t)__builtin_popcountll(sb2);
-    const uint32_t n_seg = sn0 + sn1 + sn2 + (uint32_t)__builtin_popcountll(sb3);
-    auto seg_at = [&](uint32_t r) -> int64_t {  // window index of the start of rank r (< n_seg)
-      uint64_t m = sb0;
-      int j = 0;
-      if (r >= sn0) { r -= sn0; m = sb1; j = 1; }
-      if (j == 1 && r >= sn1) { r -= sn1; m = sb2; j = 2; }
-      if (j == 2 && r >= sn2) { r -= sn2; m = sb3; j = 3; }
-      return (int64_t)((wave * 64 + (int)select_bit64(m, r)) * PT_BPT + j);
-    };
-    uint32_t rank = lane;
-    int64_t s = first;
-    bool on_first = first != -1;
-    if (!on_first && rank < n_seg) {
-      s = seg_at(rank);
-      rank += 64;
-    }
-    bool active = on_first || s != -1;
-    // A walk whose piece needs a run through the window's end (rare) stops
-    // at that piece; when every lane of the wave has stopped or finished,
-    // the wave finds the runs asked for and those walks go on.
-    int need = -1;
-#pragma unroll 1
-    for (;;) {
-#pragma unroll 1
-      while (active) {
-        if (s >= PT_HALO) sh.ph.a.o2piece[s] = 1;  // (s < own_end <= PT_WIN)
-        // A run of numbers is cut in threes from its head whatever surrounds it
-        // (no other alternative takes a number), so from a piece start inside a
-        // run of ASCII digits every third byte starts a piece: the full chunks
-        // that end by own_end are marked in one step (a run of thousands of
-        // digits is one short loop, not a piece per step).
-        int64_t full = 0;  // full chunks of three ASCII digits from s
-        if ((uint32_t)sh.buf[PT_PAD + s] - (uint32_t)'0' < 10u) {
-          const int64_t dig = win_next_zero(v.bits + WB_DIGITS * WIN_WORDS, s) - s;
-          full = (dig < own_end - s ? dig : own_end - s) / 3;
-        }
-        int64_t ps = s, e;
-        if (full >= 1) {
-#pragma unroll 1
-          for (int64_t k = 1; k < full; ++k)
-            if (s + 3 * k >= PT_HALO) sh.ph.a.o2piece[s + 3 * k] = 1;
-          ps = s + 3 * (full - 1);
-          e = s + 3 * full;
-        } else {
-          e = DS ? ds_piece_end(v, s) : o2_piece_end(v, s);
-          if (e < 0) {  // the piece needs the run through the window's end of bitmap -1 - e
-            need = (int)(-1 - e);
-            break;
-          }
-        }
-        if (e >= own_end) {  // the tile's last piece (one lane finds it)
-          sh.o2_last_s = ps;
-          sh.o2_last_e = e;
-          publish_last(ps, e);
-        }
-        if (e < own_end && !segbit(e)) {
-          s = e;
-        } else if (rank < n_seg) {
-          on_first = false;
-          s = seg_at(rank);
-          rank += 64;
-        } else {
-          active = false;
-        }
-      }
-      uint32_t sets = need >= 0 ? 1u << need : 0u;  // the bitmaps the wave's walks ask for
-#pragma unroll
-      for (int d = 1; d < 64; d <<= 1) sets |= (uint32_t)__shfl_xor((int)sets, d, 64);
-      if (sets == 0u) break;
-      if (DS) ds_far_serve(v, sets);
-      else o2_far_serve(v, sets);
-      need = -1;
-    }
-    __syncthreads();
-    TT_PHASE(18);
-    const uint32_t pw = *reinterpret_cast<const uint32_t*>(&sh.ph.a.o2piece[qb]);
-    flags = (pw & 1u) | ((pw >> 7) & 2u) | ((pw >> 14) & 4u) | ((pw >> 21) & 8u);
-    // (no walk found the last piece only in invalid text)
-    if (tid == 0 && sh.o2_pub == 0u) publish_last(sh.o2_last_s, sh.o2_last_e);
-  }
-  if (WALK) TT_PHASE(19);
-  if constexpr (!WALK) {
+  {
     // one wave evaluates the rules on the bitmaps and, where no vocabulary
     // probe comes between, cuts the pieces into units and numbers them
     if (wave == 0) {
       const uint32_t* bm = &sh.ph.a.bm[lane];
-      RunBits b;
-      b.L = bm[BM_L * BM_STRIDE];
-      b.N = bm[BM_N * BM_STRIDE];
-      b.O = bm[BM_O * BM_STRIDE];
-      b.WS = bm[BM_WS * BM_STRIDE];
-      b.NL = bm[BM_NL * BM_STRIDE];
-      b.SP = bm[BM_SP * BM_STRIDE];
-      b.APO = bm[BM_APO * BM_STRIDE];
+      auto map = [&](int k) -> uint32_t { return bm[k * BM_STRIDE]; };
+      RunBits b{};
+      b.N = map(BM_N);
+      b.WS = map(BM_WS);
+      b.NL = map(BM_NL);
+      b.SP = map(BM_SP);
       b.D = BATCH ? sh.ph.a.bm_doc[lane] : (t == 0 && lane == PT_HALO / 32 ? 1u : 0u);
-      b.C = b.L | b.N | b.O | b.WS | b.NL;
+      b.C = b.N | b.WS | b.NL;
+      O2Maps m2{};
+      DsMaps md{};
+      if constexpr (PAT == TT_PATTERN_O200K) {
+        m2 = O2Maps{map(BM2_U), map(BM2_LO), map(BM2_X), map(BM2_M), map(BM2_APO), map(BM2_SLASH)};
+        b.O = map(BM_O);
+        b.C |= b.O | m2.U | m2.Lo | m2.X | m2.M;
+      } else if constexpr (DS) {
+        md = DsMaps{map(BMD_AL), map(BMD_L), map(BMD_AP), map(BMD_PS), map(BMD_O), map(BMD_KL), map(BMD_KP), map(BMD_KO)};
+        b.C |= md.AL | md.L | md.AP | md.PS | md.O | md.KL | md.KP | md.KO;
+      } else {
+        b.L = map(BM_L);
+        b.O = map(BM_O);
+        b.APO = map(BM_APO);
+        b.C |= b.L | b.O;
+      }
       const int in_end = n - w0 < PT_WIN ? (int)(n - w0) : PT_WIN;
       b.K = bm_range(t == 0 ? PT_HALO : 0, in_end, lane) & ~b.C;
       b.multi = __ballot(b.K != 0u) != 0ull;
       const uint32_t own = bm_range(PT_HALO, min(in_end, PT_HALO + PT_OWN), lane);
       const uint8_t* ds = BATCH ? sh.dstart : nullptr;
-      uint32_t st;
-      if (PAT == TT_PATTERN_GPT2) {
-        st = gpt2_starts(b, sh.buf, ds, lane);
-      } else {
-        st = cl100k_starts(
-            b, own, sh.buf, ds, lane, t == 0,
-            [&](uint32_t sum) {
-              if (lane == 0) st_word(&w.tile_sum[t], ((uint64_t)w.epoch << 32) | sum);
-            },
-            [&]() -> RunCarry {
-              // back tile by tile (usually one step) to a tile whose trailing
-              // run does not span it
-              uint32_t acc = 0, sym = 0;
-              if (lane == 0) {
-                for (int64_t j = (int64_t)t - 1; j >= 0; --j) {
-                  const uint32_t v = (uint32_t)wait_word(&w.tile_sum[j], w.epoch);
-                  acc += (v >> 1) & 3u;
-                  if (!(v & SUM_RUNALL)) {
-                    sym = (v >> 3) & 1u;
-                    break;
-                  }
-                }
-              }
-              return RunCarry{wave_uniform(acc) % 3u, wave_uniform(sym) != 0u};
-            },
-            [&]() -> bool {
-              // The wave reads on, 16 bytes per lane per step, to the first byte
-              // that is not plain ASCII whitespace (space, tab, VT, FF) and
-              // decodes the character there (CR/LF: not the run's last stretch;
-              // other whitespace: read on after it; anything else, or the end
-              // of the text or document: the last).  Every lane holds the same
-              // position and answer; offsets are from the window's end.
-              if (w0 + PT_WIN >= n) return true;
-              const uint8_t* base = w.text + (w0 + PT_WIN);
-              int64_t lim = n;
-              if (BATCH) {
-                if (docs.y < (uint32_t)w.n_docs) lim = w.doc_off[docs.y];
-              }
-              const uint32_t end = (uint32_t)(lim - (w0 + PT_WIN));
-              uint32_t pos = 0;
-              while (pos < end && (base[pos] & 0xC0u) == 0x80u) ++pos;
+      auto publish = [&](uint32_t sum) {
+        if (lane == 0) st_word(&w.tile_sum[t], ((uint64_t)w.epoch << 32) | sum);
+      };
+      // back tile by tile (usually one step) until what is asked for (the
+      // SUM_*_ALL bits) is known
+      auto carry = [&](uint32_t ask) -> RunCarry {
+        uint32_t acc = 0, val = 0;
+        if (lane == 0) {
+          uint32_t open = ask;
+          for (int64_t j = (int64_t)t - 1; j >= 0 && open != 0u; --j) {
+            const uint32_t v = (uint32_t)wait_word(&w.tile_sum[j], w.epoch);
+            if (open & SUM_N_ALL) acc += (v >> 1) & 3u;
+            const uint32_t now = open & ~v;  // told by this tile
+            if (now & SUM_TAIL_ALL) val |= v & SUM_TAIL;
+            if (now & SUM_STATE_ALL) val |= v & (15u << SUM_STATE_SHIFT);
+            open &= ~now;
+          }
+        }
+        acc = wave_uniform(acc);
+        val = wave_uniform(val);
+        return RunCarry{acc % 3u, (val & SUM_TAIL) != 0u, (val >> SUM_STATE_SHIFT) & 15u};
+      };
+      auto class_of = [&](uint32_t cp) -> uint32_t {
+        const auto& ct = sh.ph.a.cls;
+        if constexpr (DS) return cp < 128u ? ds_ascii_class(cp) : ds_table_class(ct.l1, ct.l2, cp);
+        else if constexpr (WIDE) return cp < 128u ? o2_ascii_class(cp) : o2_table_class(ct.l1, ct.l2, cp);
+        else return cp == 10u || cp == 13u ? 4u : cp < 128u ? (cp == 32u || (cp - 9u) < 5u ? 3u : 0u) : table_class(ct, cp);
+      };
+      // The text after the window, 16 bytes per lane per step, from its first
+      // character to the first one that `in` does not hold, by the pattern's
+      // class (ASCII bytes by `plain`, which holds part of `in`): its class, or
+      // ~0 at the end of the text or document and for invalid input (reported
+      // elsewhere).  Every lane holds the same position and answer.
+      auto beyond = [&](auto plain, auto in) -> uint32_t {
+        if (w0 + PT_WIN >= n) return ~0u;
+        const uint8_t* base = w.text + (w0 + PT_WIN);
+        int64_t lim = n;
+        if (BATCH && docs.y < (uint32_t)w.n_docs) lim = w.doc_off[docs.y];
+        const uint32_t end = (uint32_t)(lim - (w0 + PT_WIN));
+        uint32_t pos = 0;
+        while (pos < end && (base[pos] & 0xC0u) == 0x80u) ++pos;
 #pragma unroll 1
-              for (;;) {
-                uint32_t first = 16u;
+        for (;;) {
+          uint32_t first = 16u;
 #pragma unroll 4
-                for (int k = 15; k >= 0; --k) {
-                  const uint32_t p = pos + 16u * (uint32_t)lane + (uint32_t)k;
-                  const uint32_t c = p < end ? (uint32_t)base[p] : 0u;  // (the end counts as a stop)
-                  if (c != 0x20u && c != 0x09u && c != 0x0Bu && c != 0x0Cu) first = (uint32_t)k;
-                }
-                const uint64_t m = __ballot(first < 16u);
-                if (m == 0ull) {
-                  pos += 16u * 64u;
-                  continue;
-                }
-                const int src = __builtin_ctzll(m);
-                const uint32_t p = pos + 16u * (uint32_t)src + (uint32_t)__builtin_amdgcn_readlane((int)first, src);
-                if (p >= end) return true;
-                const uint32_t avail = end - p < 4u ? end - p : 4u;
-                auto at = [&](uint32_t k) -> uint32_t { return k < avail ? (uint32_t)base[p + k] : 0u; };
-                uint32_t cp = 0;
-                const uint32_t len = decode_sel(at(0), at(1), at(2), at(3), avail, cp);
-                if (len == 0u) return true;  // invalid input; reported elsewhere
-                if (cp == 10u || cp == 13u) return false;
-                if (cp < 128u || table_class(sh.ph.a.cls, cp) != 3u) return true;
-                pos = p + len;
-              }
-            });
+          for (int k = 15; k >= 0; --k) {
+            const uint32_t p = pos + 16u * (uint32_t)lane + (uint32_t)k;
+            if (!(p < end && plain((uint32_t)base[p]))) first = (uint32_t)k;  // (the end counts as a stop)
+          }
+          const uint64_t m = __ballot(first < 16u);
+          if (m == 0ull) {
+            pos += 16u * 64u;
+            continue;
+          }
+          const int src = __builtin_ctzll(m);
+          const uint32_t p = pos + 16u * (uint32_t)src + (uint32_t)__builtin_amdgcn_readlane((int)first, src);
+          if (p >= end) return ~0u;
+          const uint32_t avail = end - p < 4u ? end - p : 4u;
+          auto at = [&](uint32_t k) -> uint32_t { return k < avail ? (uint32_t)base[p + k] : 0u; };
+          uint32_t cp = 0;
+          const uint32_t len = decode_sel(at(0), at(1), at(2), at(3), avail, cp);
+          if (len == 0u) return ~0u;
+          const uint32_t c = class_of(cp);
+          if (!in(c)) return c;
+          pos = p + len;
+        }
+      };
+      constexpr uint32_t C_WS = DS ? (uint32_t)DS_WS : WIDE ? (uint32_t)O2_WS : 3u;
+      constexpr uint32_t C_NL = DS ? (uint32_t)DS_NL : WIDE ? (uint32_t)O2_NL : 4u;
+      // whether no CR/LF follows the whitespace stretch that reaches the window's end
+      auto last_ws = [&]() -> bool {
+        return beyond([](uint32_t c) { return c == 0x20u || c == 0x09u || c == 0x0Bu || c == 0x0Cu; },
+                      [](uint32_t c) { return c == C_WS || (DS && c == (uint32_t)DS_SP); }) != C_NL;
+      };
+      uint32_t st;
+      if constexpr (PAT == TT_PATTERN_GPT2) {
+        st = gpt2_starts(b, sh.buf, ds, lane);
+      } else if constexpr (PAT == TT_PATTERN_CL100K) {
+        st = cl100k_starts(b, own, sh.buf, ds, lane, t == 0, publish, carry, last_ws);
+      } else if constexpr (DS) {
+        st = deepseek_starts(b, md, own, lane, t == 0, publish, carry, last_ws);
+      } else {
+        st = o200k_starts(b, m2, own, sh.buf, ds, lane, t == 0, publish, carry, last_ws, [&]() -> bool {
+          const uint32_t c = beyond([](uint32_t x) { return x - 'A' < 26u; }, [](uint32_t x) { return x == O2_UP; });
+          return c == O2_LO || c == O2_BO || c == O2_MK;
+        });
       }
       uint32_t u = st & own;
-      if (SEG && !IGN) u |= bm[BM_CUT * BM_STRIDE] & own & ~b.D;
+      if (SEG && !IGN) u |= map(BM_CUT) & own & ~b.D;
       const uint32_t c = (uint32_t)__popc(u);
       const uint32_t incl = wave_incl_sum(c);
       sh.uw[lane] = u;
@@ -1192,7 +943,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
     __syncthreads();
   }
   TT_PHASE(22);
-  if (SEG && (WALK || IGN)) {
+  if (SEG && IGN) {
     // BPE segments: add the byte positions inside pieces that no merge spans
     // (q is not a piece start, so q - 1 lies in the same piece)
     const uint32_t* bwp = reinterpret_cast<const uint32_t*>(&sh.buf[PT_PAD + qb - 4]);
@@ -1204,8 +955,8 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
       const uint32_t k2 = ((key & 255u) << 8) | (key >> 8);
       const bool joined = (sh.ph.a.join[k2 >> 5] >> (k2 & 31u)) & 1u;
       const bool eligible = q >= PT_HALO && q < PT_HALO + PT_OWN && inside(q) && inside(q - 1) &&
-                            !(flags & (1u << j)) && !((WALK || BATCH) && sh.dstart[PT_PAD + q]) &&
-                            !(IGN && ((sh.ph.a.nocut[q >> 5] >> (q & 31)) & 1u));
+                            !(flags & (1u << j)) && !(BATCH && sh.dstart[PT_PAD + q]) &&
+                            !((sh.ph.a.nocut[q >> 5] >> (q & 31)) & 1u);
       if (eligible && !joined) flags |= 1u << j;
     }
   }
@@ -1216,7 +967,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
   // start flags
   const uint32_t cnt = __popc(flags);
   uint32_t m, texcl;  // unit starts of the tile, and those before this thread's positions
-  if constexpr (WALK || IGN) {
+  if constexpr (IGN) {
     const uint32_t inc = wave_incl_sum(cnt);
     __syncthreads();
     if (lane == 63) sh.wave_tot[wave] = inc;
@@ -1247,7 +998,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
 
   TT_PHASE(11);
   // the tile's last unit start, published before this block waits on anything
-  if constexpr (!(WALK || IGN)) {
+  if constexpr (!IGN) {
     // (published with the starts)
   } else if (m == 0) {
     if (tid == 0) st_word(&w.tile_last[t], ((uint64_t)w.epoch << 32) | NO_START);
@@ -1679,9 +1430,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
     // The output offset of every document whose first unit this tile encodes
     // (a document starts a unit; empty documents share the start of the next
     // one), and in the last tile the total, or the error, for those at the end.
-    if constexpr (!(WALK || IGN)) {
-      // (the unit starts are still there)
-    } else {
+    if constexpr (IGN) {  // (else the unit starts are still there)
       store_nibbles(sh.uw, qb, lane, flags);
       if ((tid & 7) == 0) sh.upre[tid >> 3] = texcl;
       __syncthreads();

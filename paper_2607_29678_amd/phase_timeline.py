@@ -10,9 +10,8 @@ workload, one JSON line: the mean and maximum time of every phase
 over the tiles, the phases of the critical tiles (the last to finish their
 placement look-back) and of the tiles that publish their token count last
 (which every later tile's placement waits for), when tiles start and publish
-their counts (also by the number of tiles on the tile's compute unit), the
-split of the dispatch phase and, for the walked patterns, of the predicate
-phase.  Times are in microseconds; the kernel time
+their counts (also by the number of tiles on the tile's compute unit), and the
+split of the dispatch phase.  Times are in microseconds; the kernel time
 from HIP events is printed beside the stamps' span.
 
     python -m paper_2607_29678_amd.phase_timeline --build
@@ -30,13 +29,11 @@ import numpy as np
 from . import _build, _lib
 
 SLOTS, MAX_TILES, PT_OWN = 32, 8192, 1984
-PHASES = ["ticket and tables", "window staging", "decode and classify", "cl100k scan and carries", "predicate",
+PHASES = ["ticket and tables", "window staging", "decode and classify", "span export: character counts", "piece starts",
           "units and dispatch", "thread and wave engines", "block engine", "placement look-back", "writing tokens"]
 DISPATCH = ["unit scan", "unit starts listed", "incoming unit and dictionaries", "length lists", "to the engines",
             "incoming unit's start known (after the listing)"]
-WALK = ["bitmaps", "extra starts and first wait", "walks", "flags"]
-PRED = ["per-position rules (wave 0)", "read past the window, vocabulary probes", "junction cuts (wave 0)",
-        "predicate, slowest wave"]
+PRED = ["rules on the bitmaps, units", "vocabulary probes", "junction cuts (ignore_merges)", "piece starts, slowest wave"]
 
 
 def _summary(rows, names):
@@ -87,7 +84,7 @@ def timeline(workload, pattern, table, samples=8, reps=2, host=False):
         call(i)
     torch.cuda.synchronize()
     buf = np.zeros(MAX_TILES * SLOTS, dtype=np.uint64)
-    phases, disp, walk, pred, crit, spans, late, starts, counts = [], [], [], [], [], [], [], [], []
+    phases, disp, pred, crit, spans, late, starts, counts = [], [], [], [], [], [], [], []
     by_cu = {}  # tiles on a compute unit -> times at which such tiles publish their counts
     tok.set_profiling(samples * reps)
     for _ in range(reps):
@@ -105,9 +102,6 @@ def timeline(workload, pattern, table, samples=8, reps=2, host=False):
                                   rel[:, 14] - rel[:, 13], rel[:, 6] - rel[:, 14], inc], axis=1))
             pred.append(np.stack([rel[:, 21] - rel[:, 4], rel[:, 22] - rel[:, 21], rel[:, 5] - rel[:, 22],
                                   rel[:, 24:32].max(axis=1) - rel[:, 4]], axis=1))
-            if pattern in ("o200k", "deepseek"):
-                walk.append(np.stack([rel[:, 16] - rel[:, 4], rel[:, 17] - rel[:, 16], rel[:, 18] - rel[:, 17],
-                                      rel[:, 19] - rel[:, 18]], axis=1))
             c = int(np.argmax(rel[:, 9]))
             crit.append({"tile": c, "of": nt, "phases": [round(float(x), 2) for x in phases[-1][c]]})
             # the tile whose count is published last (the end of its engines):
@@ -141,8 +135,6 @@ def timeline(workload, pattern, table, samples=8, reps=2, host=False):
            "last_count_tiles": late[:4],
            "count_published_us_by_tiles_on_unit": {str(k): dict(_spread(v), tiles=int(sum(len(x) for x in v)))
                                                    for k, v in sorted(by_cu.items())}}
-    if walk:
-        out["walked_predicate"] = _summary(walk, WALK)
     return out
 
 
