@@ -217,7 +217,7 @@ __device__ __forceinline__ uint64_t bpe_lanes(uint32_t W, uint32_t L, uint32_t b
 
 // ---------------------------------------------------------------------------
 // One wave64, at most 128 bytes: lane i holds tokens i and 64 + i and the
-// ranks of the pairs starting there.  A round is the same as in bpe_wave over
+// ranks of the pairs starting there.  A round merges the lowest rank over
 // a 128-bit occurrence mask (the choice in the second row continues the
 // alternation of a run that crosses from the first, through the carry of the
 // first row's last bit); the survivors are compacted through the wave's own
@@ -282,140 +282,252 @@ __device__ __forceinline__ uint32_t bpe_wave2(uint32_t L, ByteF byte, const DevT
 }
 
 // ---------------------------------------------------------------------------
-// NW waves over rows of 64 tokens.  I0/I1 (IDs) and R0/R1 (pair ranks) are
-// double buffers of at least L words, `sel` holds rows(L) + 1 selection masks;
-// they may live in LDS or in global memory (visible to the whole block).
-// Every thread of the block calls it with the same arguments.
+// Longer units: NW waves over rows of 64 tokens.  T holds two buffers of
+// `stride` >= L tokens and `sel` one selection mask per row; they may live in LDS
+// or in global memory (visible to the whole block).  Every thread of the block
+// calls it with the same arguments.
+//
+// A token is one word: ID, rank of the pair it starts and J at the byte
+// boundary before it (21 bits each, see bpe_lanes for J and for the pairs a
+// round merges).  Each wave owns a range of rows and a round reads them twice:
+// first the choice among the pairs and the number of tokens left, then, with the
+// counts of the waves before it known, the merged tokens with the ranks of their
+// new pairs and the next round's lowest rank.  How the choice in a wave's rows
+// depends on the wave before (an occurrence at its end) only matters to the run
+// of occurrences the rows begin with: its choice shifts by one.
+// One block works while later tiles wait for its count, so a round is bound by
+// the latency of a row's loads and by the instructions of eight waves: rows are
+// taken a few at a time with their loads and rank lookups in flight together
+// (two where the ranks are looked up: more would spill registers in the kernel of
+// four blocks per compute unit), and rows with no merge are only moved.
+// Merging lowest ranks only, with IDs and ranks apart and one load in flight,
+// 25,013 bytes of one repeated letter took 12 rounds and 576 us among the tiles of
+// a 3.8 MB request (kernel 662 us; another such request 292); now 8 rounds and 168
+// us (265; 200).
 // ---------------------------------------------------------------------------
 template <int NW>
 struct RowsShared {
   uint32_t wmin[NW];
-  uint32_t f0[NW], f1[NW], cin[NW];
-  uint32_t wsum[NW], wbase[NW];
-  uint32_t n_next;
+  // per wave: tokens its rows keep, and whether their last pair is chosen, if the
+  // last pair before them is not chosen (k0) or is (k1); occurrences they begin with
+  uint32_t k0[NW], k1[NW], pre[NW];
 };
 
-template <int NW, class ByteF, class OutF>
-__device__ uint32_t bpe_rows(uint32_t L, ByteF byte, const DevTables& tb, uint32_t* I0, uint32_t* I1, uint32_t* R0,
-                             uint32_t* R1, uint64_t* sel, RowsShared<NW>& sm, OutF out) {
-  const int tid = (int)threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  constexpr int NT = NW * 64;
-  uint32_t* ids[2] = {I0, I1};
-  uint32_t* rk[2] = {R0, R1};
-  int cur = 0;
-  uint32_t n = L;
+constexpr uint32_t ROW_INF = (1u << ID_BITS) - 1u;  // no rank, in a row token
+static_assert(MAX_MERGES <= ROW_INF, "ranks of row tokens are below ROW_INF");
 
-  for (uint32_t i = tid; i < n; i += NT) I0[i] = byte(i);
-  __syncthreads();
-  for (uint32_t i = tid; i < n; i += NT) R0[i] = i + 1 < n ? tb.pairj[(I0[i] << 8) | I0[i + 1]].rank : RANK_INF;
-  __syncthreads();
+struct RowTok {
+  uint64_t v;
+  __device__ __forceinline__ static RowTok make(uint32_t id, uint32_t rk, uint32_t bl) {
+    return {(uint64_t)(id | (rk << ID_BITS)) | (uint64_t)((rk >> (32 - ID_BITS)) | (bl << (2 * ID_BITS - 32))) << 32};
+  }
+  __device__ __forceinline__ uint32_t id() const { return (uint32_t)v & ROW_INF; }
+  __device__ __forceinline__ uint32_t rk() const { return (uint32_t)(v >> ID_BITS) & ROW_INF; }
+  __device__ __forceinline__ uint32_t bl() const { return (uint32_t)(v >> 32) >> (2 * ID_BITS - 32); }
+};
+
+template <int NW, class OutF>
+__device__ __forceinline__ uint32_t bpe_rows(uint32_t L, const uint8_t* src, const DevTables& tb, uint64_t* T,
+                                             uint64_t stride, uint64_t* sel, RowsShared<NW>& sm, OutF out) {
+  const uint32_t tid = threadIdx.x;
+  const uint32_t lane = tid & 63u;
+  const uint32_t wave = wave_uniform(tid >> 6);
+  constexpr uint32_t NT = NW * 64, B = 2, C = 4;  // rows in flight with rank lookups, and without
+  const uint32_t cap = ROW_INF;
+  uint32_t n = L;
+  uint32_t cur = 0;
+
+  uint32_t m = ROW_INF;
+  for (uint32_t i0 = tid; i0 < n; i0 += NT * C) {
+    uint32_t b[C], bp[C], bn[C];
+#pragma unroll
+    for (uint32_t k = 0; k < C; ++k) {
+      const uint32_t i = min(i0 + k * NT, n - 1u);
+      b[k] = src[i];
+      bp[k] = src[i ? i - 1u : 0u];
+      bn[k] = src[min(i + 1u, n - 1u)];
+    }
+    uint32_t rk[C], bl[C];
+#pragma unroll
+    for (uint32_t k = 0; k < C; ++k) {
+      rk[k] = tb.pairj[(b[k] << 8) | bn[k]].rank;
+      bl[k] = tb.pairj[(bp[k] << 8) | b[k]].low;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < C; ++k) {
+      const uint32_t i = i0 + k * NT;
+      const uint32_t r = i + 1u < n ? min(rk[k], cap) : cap;
+      if (i < n) T[i] = RowTok::make(b[k], r, i ? min(bl[k], cap) : cap).v;
+      m = min(m, r);
+    }
+  }
 
   for (;;) {
-    const uint32_t* I = ids[cur];
-    const uint32_t* R = rk[cur];
-    uint32_t* I2 = ids[cur ^ 1];
-    uint32_t* R2 = rk[cur ^ 1];
-
-    // 1. lowest rank in the unit
-    uint32_t m = RANK_INF;
-    for (uint32_t i = tid; i < n; i += NT) m = min(m, R[i]);
     m = wave_min_u32(m);
-    if (NW > 1) {
-      if (lane == 0) sm.wmin[wave] = m;
-      __syncthreads();
-      m = RANK_INF;
-      for (int v = 0; v < NW; ++v) m = min(m, sm.wmin[v]);
-    }
-    if (m == RANK_INF) break;
+    if (lane == 0) sm.wmin[wave] = m;
+    __syncthreads();  // (and the tokens are written)
+    for (int v = 0; v < NW; ++v) m = min(m, sm.wmin[v]);
+    m = wave_uniform(m);
+    if (m == cap) break;
+    const uint64_t* A = T + (cur ? stride : 0u);
+    uint64_t* A2 = T + (cur ? 0u : stride);
 
-    // 2. leftmost non-overlapping occurrences, row by row.  A row's choice
-    // depends on whether the last pair of the previous row was chosen; with
-    // several waves each wave first evaluates its rows for both carries.
-    const uint32_t rows = (n + 63) / 64;
-    const uint32_t rpw = (rows + NW - 1) / NW;
-    const uint32_t r_lo = min(rows, (uint32_t)wave * rpw);
-    const uint32_t r_hi = min(rows, r_lo + rpw);
-    uint32_t carry = 0;
-    if (NW > 1) {
-      uint32_t c0 = 0, c1 = 1;
-      for (uint32_t r = r_lo; r < r_hi; ++r) {
-        const uint32_t i = r * 64 + lane;
-        const uint64_t occ = __ballot(i < n && R[i] == m);
-        c0 = (uint32_t)(leftmost_nonoverlapping(occ & ~(uint64_t)c0) >> 63);
-        c1 = (uint32_t)(leftmost_nonoverlapping(occ & ~(uint64_t)c1) >> 63);
+    // 1. the choice, as if the last pair before the wave's rows were not chosen
+    const uint32_t rows = (n + 63u) / 64u;
+    const uint32_t rpw = (rows + NW - 1u) / NW;
+    const uint32_t r_lo = min(rows, wave * rpw), r_hi = min(rows, r_lo + rpw);
+    const uint32_t toks = min(n, r_hi * 64u) - min(n, r_lo * 64u);
+    uint32_t carry = 0, chosen = 0, pre = 0;
+    bool in_pre = true;
+    for (uint32_t r0 = r_lo; r0 < r_hi; r0 += C) {
+      RowTok t[C], t2[C];
+#pragma unroll
+      for (uint32_t k = 0; k < C; ++k) {
+        const uint32_t i = (r0 + k) * 64u + lane;
+        t[k].v = A[min(i, n - 1u)];
+        t2[k].v = A[min(i + 2u, n - 1u)];
       }
-      if (lane == 0) {
-        sm.f0[wave] = c0;
-        sm.f1[wave] = c1;
-      }
-      __syncthreads();
-      if (tid == 0) {
-        uint32_t c = 0;
-        for (int v = 0; v < NW; ++v) {
-          sm.cin[v] = c;
-          c = c ? sm.f1[v] : sm.f0[v];
+#pragma unroll
+      for (uint32_t k = 0; k < C; ++k) {
+        if (r0 + k < r_hi) {
+          const uint32_t i = (r0 + k) * 64u + lane;
+          const uint32_t rk = i + 1u < n ? t[k].rk() : cap;
+          const uint32_t bd = i + 2u < n ? min(t[k].bl(), t2[k].bl()) : t[k].bl();
+          const uint64_t occ = __ballot(rk == m);
+          const uint64_t s = leftmost_nonoverlapping(occ & ~(uint64_t)carry) | (__ballot(rk < bd) & ~occ);
+          if (lane == 0) sel[r0 + k] = s;
+          chosen += (uint32_t)__popcll(s);
+          carry = (uint32_t)(s >> 63);
+          if (in_pre) {
+            pre += ~occ ? (uint32_t)__builtin_ctzll(~occ) : 64u;
+            in_pre = ~occ == 0ull;
+          }
         }
       }
-      __syncthreads();
-      carry = sm.cin[wave];
     }
-    uint32_t keep_total = 0;
-    for (uint32_t r = r_lo; r < r_hi; ++r) {
-      const uint32_t i = r * 64 + lane;
-      const uint64_t occ = __ballot(i < n && R[i] == m);
-      const uint64_t s = leftmost_nonoverlapping(occ & ~(uint64_t)carry);
-      if (lane == 0) sel[r] = s;
-      const uint64_t valid = (n - r * 64 >= 64) ? ~0ull : ((1ull << (n - r * 64)) - 1ull);
-      const uint64_t keep = valid & ~((s << 1) | (uint64_t)carry);
-      keep_total += (uint32_t)__popcll(keep);
-      carry = (uint32_t)(s >> 63);
+    if (lane == 0) {
+      // a run that fills the rows carries the shift to their last pair
+      const uint32_t chosen1 = chosen - (pre & 1u), carry1 = in_pre ? carry ^ 1u : carry;
+      sm.k0[wave] = ((toks - (chosen - carry)) << 1) | carry;
+      sm.k1[wave] = ((toks - 1u - (chosen1 - carry1)) << 1) | carry1;
+      sm.pre[wave] = pre;
     }
-    if (tid == 0) sel[rows] = 0;  // sentinel row (only bit 0 is ever read)
-    // 3. compaction
-    if (NW > 1) {
-      if (lane == 0) sm.wsum[wave] = keep_total;
-      __syncthreads();
-      if (tid == 0) {
-        uint32_t b = 0;
-        for (int v = 0; v < NW; ++v) {
-          sm.wbase[v] = b;
-          b += sm.wsum[v];
+    __syncthreads();
+    uint32_t base = 0, n2 = 0, c_in = 0, c_next = 0, pre_next = 0;
+    {
+      uint32_t c = 0;
+      for (uint32_t v = 0; v < NW; ++v) {
+        if (v == wave) {
+          c_in = c;
+          base = n2;
         }
-        sm.n_next = b;
+        if (v == wave + 1u) {
+          c_next = c;
+          pre_next = sm.pre[v];
+        }
+        if (v * rpw >= rows) continue;  // no rows
+        const uint32_t x = c ? sm.k1[v] : sm.k0[v];
+        n2 += x >> 1;
+        c = x & 1u;
       }
     }
-    __syncthreads();
-    uint32_t base = NW > 1 ? sm.wbase[wave] : 0u;
-    const uint32_t n2 = NW > 1 ? sm.n_next : keep_total;
-    uint32_t prevbit = (NW > 1 && r_lo > 0) ? (uint32_t)(sel[r_lo - 1] >> 63) : 0u;
-    for (uint32_t r = r_lo; r < r_hi; ++r) {
-      const uint32_t i = r * 64 + lane;
-      const uint64_t s = sel[r];
-      const uint64_t valid = (n - r * 64 >= 64) ? ~0ull : ((1ull << (n - r * 64)) - 1ull);
-      const uint64_t keep = valid & ~((s << 1) | (uint64_t)prevbit);
-      if ((keep >> lane) & 1ull) {
-        const uint32_t k = base + bits_below(keep);
-        const uint32_t my = (uint32_t)(s >> lane) & 1u;
-        const uint32_t nx = lane < 63 ? (uint32_t)(s >> (lane + 1)) & 1u : (uint32_t)(sel[r + 1] & 1ull);
-        I2[k] = my ? 256u + m : I[i];
-        R2[k] = (my | nx) ? RANK_DIRTY : R[i];
+    c_in = wave_uniform(c_in);
+    c_next = wave_uniform(c_next);
+    base = wave_uniform(base);
+    pre_next = wave_uniform(pre_next);
+    pre = c_in ? pre : 0u;
+    pre_next = c_next ? pre_next : 0u;
+
+    // 2. the tokens after the round
+    m = cap;
+    carry = c_in;
+    for (uint32_t r0 = r_lo; r0 < r_hi; r0 += B) {
+      // the masks of the rows and of the one after them, with the shift of the
+      // run the wave's rows (or the next wave's) begin with
+      uint64_t ms = 0;
+      if (lane <= B && r0 + lane < rows) {
+        const uint32_t r = r0 + lane;
+        ms = sel[r];
+        const uint32_t off = r < r_hi ? (r - r_lo) * 64u : 0u, p = r < r_hi ? pre : pre_next;
+        const uint32_t k = p > off ? p - off : 0u;
+        ms ^= k >= 64u ? ~0ull : ((1ull << k) - 1ull);
       }
-      base += (uint32_t)__popcll(keep);
-      prevbit = (uint32_t)(s >> 63);
+      uint64_t s[B + 1];
+#pragma unroll
+      for (uint32_t k = 0; k <= B; ++k)
+        s[k] = (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)ms, (int)k) |
+               (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(ms >> 32), (int)k) << 32;
+      if ((s[0] | s[1] | (s[2] & 3ull) | (uint64_t)carry) == 0ull && (r0 + 2u) * 64u < n && r0 + 1u < r_hi) {
+        // nothing merges in or next to two full rows: they move as they are
+        RowTok x[2];
+#pragma unroll
+        for (uint32_t k = 0; k < 2u; ++k) x[k].v = A[(r0 + k) * 64u + lane];
+#pragma unroll
+        for (uint32_t k = 0; k < 2u; ++k) {
+          A2[base + k * 64u + lane] = x[k].v;
+          m = min(m, x[k].rk());
+        }
+        base += 128u;
+        continue;
+      }
+      RowTok t[B], t1[B];
+#pragma unroll
+      for (uint32_t k = 0; k < B; ++k) {
+        const uint32_t i = (r0 + k) * 64u + lane;
+        t[k].v = A[min(i, n - 1u)];
+        t1[k].v = A[min(i + 1u + (uint32_t)((s[k] >> lane) & 1u), n - 1u)];
+      }
+      uint32_t id[B], rk[B];
+      bool kept[B], dirty[B];
+      bool any = false;
+#pragma unroll
+      for (uint32_t k = 0; k < B; ++k) {
+        const uint32_t i = (r0 + k) * 64u + lane;
+        const bool in = r0 + k < r_hi && i < n;
+        const bool me = (s[k] >> lane) & 1ull;
+        const uint64_t keep = ~((s[k] << 1) | (uint64_t)carry);
+        if (r0 + k < r_hi) carry = (uint32_t)(s[k] >> 63);
+        kept[k] = in && ((keep >> lane) & 1ull);
+        // the next token after the round starts at i1; is it a merged one too?
+        const uint32_t i1 = i + 1u + (me ? 1u : 0u);
+        const uint32_t d = lane + 1u + (me ? 1u : 0u);
+        const bool nx = d < 64u ? (s[k] >> d) & 1ull : (s[k + 1] >> (d - 64u)) & 1ull;
+        const bool pair = i1 < n;
+        id[k] = me ? 256u + t[k].rk() : t[k].id();
+        dirty[k] = kept[k] && pair && (me || nx);
+        rk[k] = pair ? t[k].rk() : cap;
+        any = any || dirty[k];
+        t1[k].v = nx ? 256u + t1[k].rk() : t1[k].id();
+      }
+      if (__ballot(any)) {
+        uint32_t q[B];
+#pragma unroll
+        for (uint32_t k = 0; k < B; ++k) q[k] = probe_rank(tb, dirty[k] ? id[k] : 0u, dirty[k] ? (uint32_t)t1[k].v : 0u);
+#pragma unroll
+        for (uint32_t k = 0; k < B; ++k) rk[k] = dirty[k] ? min(q[k], cap) : rk[k];
+      }
+#pragma unroll
+      for (uint32_t k = 0; k < B; ++k) {
+        const uint64_t kp = __ballot(kept[k]);
+        if (kept[k]) {
+          A2[base + bits_below(kp)] = RowTok::make(id[k], rk[k], t[k].bl()).v;
+          m = min(m, rk[k]);
+        }
+        base += (uint32_t)__popcll(kp);
+      }
     }
-    __syncthreads();
-    n = n2;
-    // 4. ranks of the pairs next to the merges
-    for (uint32_t i = tid; i < n; i += NT) {
-      if (R2[i] == RANK_DIRTY) R2[i] = i + 1 < n ? probe_rank(tb, I2[i], I2[i + 1]) : RANK_INF;
-    }
-    __syncthreads();
-    cur ^= 1;
+    n = wave_uniform(n2);
+    cur ^= 1u;
   }
-  const uint32_t* I = ids[cur];
-  for (uint32_t i = tid; i < n; i += NT) out(i, I[i]);
+  const uint64_t* A = T + (cur ? stride : 0u);
+  for (uint32_t i0 = tid; i0 < n; i0 += NT * C) {
+    uint32_t id[C];
+#pragma unroll
+    for (uint32_t k = 0; k < C; ++k) id[k] = RowTok{A[min(i0 + k * NT, n - 1u)]}.id();
+#pragma unroll
+    for (uint32_t k = 0; k < C; ++k)
+      if (i0 + k * NT < n) out(i0 + k * NT, id[k]);
+  }
   return n;
 }
 

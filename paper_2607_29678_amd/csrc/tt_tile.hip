@@ -294,7 +294,7 @@ union PhaseMem {
     union {
       uint32_t wscr[PT_THREADS / 64][256];  // wave engine for 65..128 bytes: one area per wave
       struct {                              // block engine for 129..ROWS_LDS bytes
-        uint32_t I0[ROWS_LDS], I1[ROWS_LDS], R0[ROWS_LDS], R1[ROWS_LDS];
+        uint64_t tok[2 * ROWS_LDS];
         uint64_t sel[ROWS_LDS / 64 + 2];
       } rows;
     } x;
@@ -480,6 +480,18 @@ __device__ unsigned long long tt_phase_buf[TT_PHASE_TILES * TT_PHASE_SLOTS];
   } while (0)
 #endif
 #define TT_PHASE(k) TT_PHASE_BY(k, tid == 0)
+
+// The kernel's arguments, read again from where the launch put them, for a rare
+// phase: it then adds nothing to what the phases around it hold in scalar registers.
+struct TileArgs {
+  Work w;
+  DevTables tb;
+};
+__device__ __forceinline__ const TileArgs& tile_args() {
+  auto p = (const __attribute__((address_space(4))) TileArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm("" : "+s"(p));  // (not merged with earlier reads)
+  return *(const TileArgs*)p;
+}
 
 // MODE 0: split-level export; the outputs are the byte offsets of the pieces.
 // MODE 1: encoding; the outputs are the (internal) IDs of the units' tokens.
@@ -1259,6 +1271,11 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
   // bytes at byte s take words [s/16, s/16 + L/64 + 2), which never reach the
   // next unit's)
   const uint32_t n_big = sh.n_big;
+  // With six waves per SIMD (requests that do not fill the chip) the engine's code
+  // is placed behind the kernel's and reads its arguments again: 100K of prose and
+  // code 17.65 -> 17.05 us; with eight it stays in line (8M characters 133 us, 135 the
+  // other way).
+  if (__builtin_expect(n_big != 0u, WAVES == 8))
 #pragma unroll 1
   for (uint32_t i = 0; i < n_big; ++i) {
     const uint32_t u = sh.big[i];
@@ -1266,31 +1283,22 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
     const uint32_t a = inc_u ? 0u : sh.ustart[u];
     const uint32_t L = inc_u ? L_inc : sh.ustart[u + 1] - a;
     const uint64_t s0 = inc_u ? (uint64_t)s_prev : (uint64_t)(w0 + a);
-    uint32_t *I0, *I1, *R0, *R1;
-    uint64_t* sel;
-    if (L <= (uint32_t)ROWS_LDS) {
-      auto& rw = sh.ph.b.x.rows;
-      I0 = rw.I0;
-      I1 = rw.I1;
-      R0 = rw.R0;
-      R1 = rw.R1;
-      sel = rw.sel;
-    } else {
-      uint32_t* sc = w.scratch;
-      const uint64_t nn = (uint64_t)n;
-      I0 = sc + s0;
-      I1 = sc + nn + s0;
-      R0 = sc + 2 * nn + s0;
-      R1 = sc + 3 * nn + s0;
-      sel = reinterpret_cast<uint64_t*>(sc + 4 * nn) + s0 / 16;
-    }
+    const Work& rw = WAVES == 8 ? w : tile_args().w;
+    const DevTables& rt = WAVES == 8 ? tb : tile_args().tb;
+    const uint8_t* __restrict__ src = rw.text + s0;
+    uint32_t* stage = rw.stage + s0;
+    auto out = [&](uint32_t j, uint32_t id) {
+      if (inc_u) stage[j] = id;
+      else sh.ph.b.tok[a + j] = id;
+    };
     uint32_t c;
-    if (inc_u) {
-      c = bpe_rows<PT_THREADS / 64>(L, inc_byte, tb, I0, I1, R0, R1, sel, sh.rows, inc_out);
+    if (L <= (uint32_t)ROWS_LDS) {
+      auto& rows = sh.ph.b.x.rows;
+      c = bpe_rows<PT_THREADS / 64>(L, src, rt, rows.tok, ROWS_LDS, rows.sel, sh.rows, out);
     } else {
-      c = bpe_rows<PT_THREADS / 64>(
-          L, [&](uint32_t j) -> uint32_t { return sh.buf[PT_PAD + a + j]; }, tb, I0, I1, R0, R1, sel, sh.rows,
-          [&](uint32_t j, uint32_t id) { sh.ph.b.tok[a + j] = id; });
+      const uint64_t nn = (uint64_t)n;
+      uint64_t* sc = reinterpret_cast<uint64_t*>(rw.scratch);
+      c = bpe_rows<PT_THREADS / 64>(L, src, rt, sc + s0, nn, sc + 2 * nn + s0 / 16, sh.rows, out);
     }
     if (tid == 0) {
       if (inc_u) sh.inc_cnt = c;
@@ -1422,8 +1430,20 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
       out[at] = (int32_t)v;
     }
   };
-  for (uint32_t i = (uint32_t)tid; i < inc_cnt; i += PT_THREADS)
-    put(prefix + i, i == (uint32_t)tid ? inc_val : (uint32_t)ext_of(w.stage[s_prev + i]));
+  if ((uint32_t)tid < inc_cnt) put(prefix + (uint32_t)tid, inc_val);
+  for (uint32_t i = (uint32_t)tid + PT_THREADS; i < inc_cnt; i += 4u * PT_THREADS) {  // (a long incoming unit)
+    uint32_t v[4];
+#pragma unroll
+    for (uint32_t k = 0; k < 4u; ++k) v[k] = w.stage[s_prev + min(i + k * PT_THREADS, inc_cnt - 1u)];
+#pragma unroll
+    for (uint32_t k = 0; k < 4u; ++k) {
+      const int32_t e = ext[min(v[k], tb.n_ids - 1u)];
+      v[k] = v[k] < tb.n_ids ? (uint32_t)e : 0xFFFFFFFFu;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < 4u; ++k)
+      if (i + k * PT_THREADS < inc_cnt) put(prefix + i + k * PT_THREADS, v[k]);
+  }
   const uint32_t obase = prefix + inc_cnt;
   for (uint32_t i = (uint32_t)tid; i < ctot; i += PT_THREADS) put(obase + i, sh.ph.c.id[i]);
   if (BATCH) {
