@@ -559,10 +559,14 @@ __device__ __forceinline__ uint32_t deepseek_starts(const RunBits& b, const DsMa
   const uint32_t nl_heads = b.NL & ~b.after(b.NL), nl = b.NL & ~b.D;
   uint32_t sym = nl & pP;
   const NumberRuns nr = number_runs(b, first_tile, lane);
-  const uint32_t join = m.AL & b.after(m.AP & ~pP & ~pSP), al = m.AL & ~b.D;
+  // (whether a symbol that is the window's first character is a lone one is not
+  // known: the context of such a symbol and ASCII letters tells no more than one
+  // of letters alone)
+  const uint32_t first = !first_tile && lane == 0 ? b.C & (0u - b.C) : 0u, edge = m.AP & first & ~b.D;
+  const uint32_t join = m.AL & b.after(m.AP & ~pP & ~pSP & ~edge), al = m.AL & ~b.D;
   uint32_t d1 = bm_flood(al, join);  // ASCII letters behind a lone symbol
-  const bool al_in = !first_tile && covers_context(al);
-  const uint32_t run0 = al_in ? bm_flood(al, lane == 0 ? al & 1u : 0u) : 0u;
+  const bool al_in = !first_tile && covers_context(al | (edge ? edge | (edge - 1u) : 0u));
+  const uint32_t run0 = al_in ? bm_flood(al, lane == 0 ? al & (0u - al) : 0u) : 0u;
   {
     const int last = bm_last(b.C & own);
     uint32_t sum = number_summary(b, nr, own, lane) | nl_summary(b, own, nl_heads, sym);

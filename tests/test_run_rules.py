@@ -1,0 +1,44 @@
+"""Piece starts by the library's rules (``tt_runs.h``), run on the CPU, against the oracle: what the rules take
+from the 32 bytes before a tile, at the library's tile size and at small ones."""
+
+import pytest
+
+from oracle.pretok import piece_byte_starts
+from run_rules import HALO, starts
+
+OWN = 1984
+
+
+def _same(text, pattern, own=OWN, docs=None):
+    if docs is None:
+        want = piece_byte_starts(text, pattern)
+    else:
+        want, at = [], 0
+        for d in docs:
+            want += [at + x for x in piece_byte_starts(d, pattern)]
+            at += len(d.encode())
+    assert starts(text, pattern, own, docs) == want, (pattern, own, docs or text[-120:])
+
+
+def _at(lead, edge):
+    """Text that ends in ``lead``, whose last byte is the byte before ``edge``."""
+    return ("w " * edge)[:edge - len(lead.encode())] + lead
+
+
+# a window begins 32 bytes before its tile; a lead character on that byte, or cut by it
+LEADS = ["!!", " !", "…!", "a!", "!", "。'", "😀#", "\x01'", "中!", "\n!", "é'", "1$"]
+
+
+@pytest.mark.parametrize("own", [OWN, 64])
+@pytest.mark.parametrize("lead", LEADS)
+def test_lone_symbol_at_the_window_edge(own, lead):
+    """DeepSeek: ASCII letters belong to an ASCII symbol before them unless a symbol or U+0020 precedes it, which a
+    tile cannot see when the symbol is its window's first character."""
+    edge = 2 * own - HALO
+    for end in range(edge - 1, edge + 5):
+        for run in (HALO - 2, HALO - 1, HALO, 40, HALO + own, HALO + 2 * own):
+            for tail in ("é tail", "é", " x", "!é"):
+                _same(_at(lead, end) + "a" * run + tail, "deepseek", own)
+    for cut in (0, 1):  # a document starts at the symbol, or after it
+        text = _at(lead, edge + 1)
+        _same(None, "deepseek", own, [text[:len(text) - 1 + cut], text[len(text) - 1 + cut:] + "a" * (HALO - 1) + "é"])
