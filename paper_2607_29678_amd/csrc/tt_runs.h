@@ -233,6 +233,11 @@ __device__ __forceinline__ bool covers_context(uint32_t x) { return (__ballot(x 
 __device__ __forceinline__ bool covers_tile(const RunBits& b, uint32_t own, uint32_t x) {
   return __ballot((b.C & own & ~x) != 0u) == 0ull;
 }
+// In lane 0, the bytes before the window's first character: the end of a character
+// that begins outside, whose class is not in the bitmaps.
+__device__ __forceinline__ uint32_t cut_bytes(const RunBits& b, int lane) {
+  return lane == 0 ? (b.C & (0u - b.C)) - 1u : 0u;
+}
 // Bits of m reached from the bits of s by runs of m, towards later positions
 // (s within m; several bits of s may lie in one run).
 __device__ __forceinline__ uint32_t bm_flood(uint32_t m, uint32_t s) { return ((bm_add(m, s) ^ m) | s) & m; }
@@ -353,9 +358,10 @@ __device__ __forceinline__ uint32_t cl100k_starts(const RunBits& b, uint32_t own
   const NumberRuns nr = number_runs(b, first_tile, lane);
   publish(number_summary(b, nr, own, lane) | nl_summary(b, own, nl_heads, sym));
   RunCarry in{};
-  const bool nl_in = covers_context(b.NL);
+  const uint32_t cut0 = cut_bytes(b, lane);
+  const bool nl_in = !first_tile && covers_context(b.NL | cut0);
   if (!first_tile && (nl_in || number_enters(b, nr))) in = carry(nl_in ? SUM_TAIL_ALL : SUM_N_ALL);
-  if (nl_in && in.tail && lane == 0) sym |= nl & 1u;
+  if (nl_in && in.tail && lane == 0) sym |= nl & (cut0 + 1u);
   uint32_t st = whitespace_starts(b, b.L | b.N | b.O, pO, b.after(bm_flood(nl, sym)), lane, last_ws);
   st |= number_part(b, nr, in.n, lane);
   // symbols; letters, which take one preceding whitespace character but CR/LF,
@@ -408,8 +414,7 @@ __device__ __forceinline__ uint32_t o200k_starts(RunBits b, O2Maps m, uint32_t o
   const uint32_t tile_chars = b.C & own;
   RunCarry in{};
   bool in_tail = false;  // the context is the tail of a symbol piece
-  // (the context may begin inside a character, which then is not in the bitmaps)
-  const uint32_t cut0 = lane == 0 ? (b.C & (0u - b.C)) - 1u : 0u;
+  const uint32_t cut0 = cut_bytes(b, lane);
   const bool x_in = !first_tile && covers_context((b.fill(m.X) & ~b.D) | cut0);
   if (!first_tile && !x_in) {
     const uint32_t let = m.U | m.Lo | m.X, apo2 = bm_shl1(bm_shl1(m.APO)), o = b.O & ~m.SLASH;
@@ -575,11 +580,12 @@ __device__ __forceinline__ uint32_t deepseek_starts(const RunBits& b, const DsMa
     publish(sum);
   }
   RunCarry in{};
-  const bool nl_in = covers_context(b.NL);
+  const uint32_t cut0 = cut_bytes(b, lane);
+  const bool nl_in = !first_tile && covers_context(b.NL | cut0);
   const bool al_asks = al_in && __ballot((m.L & b.after(run0) & own) != 0u) != 0ull;
   if (!first_tile && (nl_in || al_asks || number_enters(b, nr)))
     in = carry((nl_in ? SUM_TAIL_ALL : 0u) | (al_asks ? SUM_STATE_ALL : 0u) | SUM_N_ALL);
-  if (nl_in && in.tail && lane == 0) sym |= nl & 1u;
+  if (nl_in && in.tail && lane == 0) sym |= nl & (cut0 + 1u);
   if (al_asks && in.state == ST_LOW) d1 |= run0;
   const uint32_t pO = b.after(b.fill(m.O)), pWS = b.after(b.fill(b.WS));
   uint32_t st = (let & ~b.after(b.fill(let)) & ~pWS & ~pO & ~join) | (m.L & b.after(d1));

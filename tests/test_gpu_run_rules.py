@@ -66,6 +66,20 @@ def test_runs_across_tiles(gpu, pattern, run, n):
 
 
 @pytest.mark.parametrize("pattern", PATTERNS)
+@pytest.mark.parametrize("lead", ["!!", " !", "…!", "a!", "中'", "…", "!…", "😀", "é", "\u0301", "・", "x'", "1", "A", "　"])
+def test_leads_at_the_window_edge(gpu, pattern, lead):
+    """A character on, or cut by, the window's first byte (32 bytes before the tile), then a run up to the tile and a
+    character that what precedes the run decides on."""
+    with _tok(pattern) as tok:
+        for end in range(OWN - 36, OWN - 27):
+            before = ("w " * OWN)[:end - len(lead.encode())] + lead
+            for run, tail in (("a", "é tail"), ("a", "中"), ("\n", "  \nx"), ("\n", "\t\r"), ("A", "b"), ("中", "A"),
+                              ("\u0301", "A"), ("7", "7"), ("/", "\n x"), ("!", "a")):
+                for n in (27, 30, 31, 32, 40):
+                    _same(tok, before + run * (n // len(run.encode())) + tail, pattern)
+
+
+@pytest.mark.parametrize("pattern", PATTERNS)
 def test_documents_cut_every_rule(gpu, pattern):
     """Short documents side by side: no rule looks across a document's start."""
     from oracle.bpe import bpe

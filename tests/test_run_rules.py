@@ -42,3 +42,19 @@ def test_lone_symbol_at_the_window_edge(own, lead):
     for cut in (0, 1):  # a document starts at the symbol, or after it
         text = _at(lead, edge + 1)
         _same(None, "deepseek", own, [text[:len(text) - 1 + cut], text[len(text) - 1 + cut:] + "a" * (HALO - 1) + "é"])
+
+
+@pytest.mark.parametrize("own", [OWN, 64])
+@pytest.mark.parametrize("pattern", ["cl100k", "deepseek", "o200k"])
+@pytest.mark.parametrize("lead", ["…", "😀", "！", "!", "!…", "é", "中", "٣", "　", "\u0301", "・", "\n", " "])
+def test_line_breaks_behind_a_cut_character(own, pattern, lead):
+    """A CR/LF run is the tail of a symbol piece when a symbol precedes it; the window may begin inside that symbol."""
+    edge = 2 * own - HALO
+    for end in range(edge - 1, edge + 5):
+        for run in (HALO - 4, HALO - 2, HALO - 1, HALO, HALO + own):
+            for tail in ("  \nx", "\t\r", "　\n", " x", "\nx"):
+                _same(_at(lead, end) + "\n" * run + tail, pattern, own)
+    text = _at(lead, edge + 1)
+    n = len(text) - len(lead)
+    for k in range(n, len(text) + 1):  # a document starts around the lead
+        _same(None, pattern, own, [text[:k], text[k:] + "\r" * (HALO - 1) + "  \n"])
