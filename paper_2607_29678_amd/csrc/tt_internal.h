@@ -259,6 +259,16 @@ constexpr int ROWS_LDS = 480;                      // longer units: rows in LDS 
 inline uint32_t n_tiles_for(uint32_t n) { return (n + PT_OWN - 1) / PT_OWN; }
 
 // Launchers (defined in the .hip files) -------------------------------------
+// A launch's own status.  (The runtime's last error may be an older one that
+// nobody has read: taken for the launch's, it would leave the ticket base behind
+// the tickets that the tiles took, and the next call's tiles waiting for ever.)
+template <class... P, class... A>
+inline hipError_t launch(void (*kernel)(P...), dim3 grid, dim3 block, hipStream_t st, A... a) {
+  return [&](P... p) -> hipError_t {
+    void* args[] = {&p...};
+    return hipLaunchKernel(reinterpret_cast<const void*>(kernel), grid, block, args, 0, st);
+  }(a...);
+}
 // mode 0: split export (outputs are piece byte offsets); mode 1: encode;
 // mode 2: encode with span export (single requests)
 // ignore: probe whole pieces in the vocabulary first (modes 1 and 2)

@@ -72,8 +72,7 @@ extern "C" int tt_encode_device_noalloc(tt_tokenizer* h, const uint8_t* d_utf8, 
   hipStream_t st = static_cast<hipStream_t>(stream);
   if (hipSetDevice(dev) != hipSuccess) return TT_ERR_HIP;
   if (len == 0) {
-    hipLaunchKernelGGL(set_len, dim3(1), dim3(64), 0, st, d_out_len, (int64_t)0);
-    return hipGetLastError() == hipSuccess ? TT_OK : TT_ERR_HIP;
+    return launch(set_len, dim3(1), dim3(64), st, d_out_len, 0) == hipSuccess ? TT_OK : TT_ERR_HIP;
   }
   DevState& ds = g_dev[dev];
   std::lock_guard<std::mutex> g(ds.mu);
@@ -86,8 +85,8 @@ extern "C" int tt_encode_device_noalloc(tt_tokenizer* h, const uint8_t* d_utf8, 
   if (ds.epoch == 0 || ds.epoch + 1 >= EPOCH_LIMIT) {
     // first call on this device, or the epochs wrapped: clear the words that
     // carry them (a kernel, not a memset, so that the call may be captured)
-    hipLaunchKernelGGL(clear_words, dim3(64), dim3(256), 0, st, reinterpret_cast<uint64_t*>(ds.base), NA_CLEAR / 8);
-    if (hipGetLastError() != hipSuccess) return TT_ERR_HIP;
+    if (launch(clear_words, dim3(64), dim3(256), st, reinterpret_cast<uint64_t*>(ds.base), NA_CLEAR / 8) != hipSuccess)
+      return TT_ERR_HIP;
     ds.epoch = 0;
     ds.ticket_base = 0;
   }

@@ -1563,7 +1563,7 @@ namespace {
 template <int PAT>
 hipError_t launch_pat(const Work& w, const DevTables& tb, int mode, bool batch, bool ignore, hipStream_t s) {
   dim3 grid(w.n_tiles), block(PT_THREADS);
-#define TT_TILE_W(B, M, I, V) hipLaunchKernelGGL((tile_kernel<PAT, B, M, I, V>), grid, block, 0, s, w, tb)
+#define TT_TILE_W(B, M, I, V) return launch(tile_kernel<PAT, B, M, I, V>, grid, block, s, w, tb)
 #define TT_TILE(B, M, I) TT_TILE_W(B, M, I, 6)
   // GPT-2- and cl100k-style encoding fits 64 registers and 40 KB of LDS, so a
   // fourth block fits on a compute unit: a 16M-character corpus takes 268 us
@@ -1576,7 +1576,6 @@ hipError_t launch_pat(const Work& w, const DevTables& tb, int mode, bool batch, 
     if (mode == 1 && !ignore && w.n_tiles > RESIDENT_TILES) {
       if (batch) TT_TILE_W(true, 1, false, 8);
       else TT_TILE_W(false, 1, false, 8);
-      return hipGetLastError();
     }
   }
   if (mode == 0) {
@@ -1595,7 +1594,6 @@ hipError_t launch_pat(const Work& w, const DevTables& tb, int mode, bool batch, 
   }
 #undef TT_TILE
 #undef TT_TILE_W
-  return hipGetLastError();
 }
 }  // namespace
 

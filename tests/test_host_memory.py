@@ -1,0 +1,83 @@
+"""What the host code (``tt_api.hip``, ``tt_session.hip``) does when memory runs out, on the CPU: the sources
+themselves, compiled for the host against a runtime with budgets for device and pinned memory, whose kernel gives
+one token per byte (``tests/native/fake_hip.cpp``)."""
+
+import ctypes
+import functools
+import os
+import shutil
+import subprocess
+import tempfile
+
+import numpy as np
+import pytest
+
+from paper_2607_29678_amd import Session, Tokenizer, TokTierError, _lib
+from run_rules import CSRC, NATIVE, clang
+
+ALL = (1 << 64) - 1
+
+
+@functools.lru_cache(maxsize=None)
+def _fake():
+    tmp = tempfile.mkdtemp(prefix="fake_hip_")
+    try:
+        so = os.path.join(tmp, "fake.so")
+        r = subprocess.run([clang(), "-O1", "-std=c++17", "-shared", "-fPIC", "-pthread", "-w", "-I" + NATIVE, "-I" + CSRC,
+                            "-x", "c++"] + [os.path.join(CSRC, f) for f in ("tt_api.hip", "tt_session.hip", "tt_copy.cpp")]
+                           + [os.path.join(NATIVE, "fake_hip.cpp"), "-o", so], capture_output=True, text=True)
+        assert r.returncode == 0, r.stderr[-4000:]
+        lib = ctypes.CDLL(so)
+    finally:
+        shutil.rmtree(tmp)
+    for name, (res, args) in _lib.SIGNATURES.items():
+        if hasattr(lib, name):
+            fn = getattr(lib, name)
+            fn.restype, fn.argtypes = res, args
+    lib.fake_budgets.argtypes = [ctypes.c_uint64, ctypes.c_uint64]
+    lib.fake_used.restype = ctypes.c_uint64
+    lib.fake_device.restype = ctypes.c_void_p
+    lib.fake_device.argtypes = [ctypes.c_uint64]
+    lib.fake_free.argtypes = [ctypes.c_void_p]
+    return lib
+
+
+@pytest.fixture
+def fake(monkeypatch):
+    lib = _fake()
+    monkeypatch.setattr(_lib, "_lib", lib)
+    yield lib
+    lib.fake_budgets(ALL, ALL)
+
+
+# IDs of 16, 24 and 32 bits (staged in as many bytes)
+FIRST = {16: 0, 24: 70_000, 32: 1 << 24}
+
+
+def _tok(bits=16, **opt):
+    first = FIRST[bits]
+    vocab = [b"??"] * first + [bytes([b]) for b in range(256)]
+    offsets = np.concatenate([[0], np.cumsum([len(v) for v in vocab])]).astype(np.int64)
+    return Tokenizer(np.zeros((0, 3), dtype=np.int32), np.frombuffer(b"".join(vocab), dtype=np.uint8), offsets, "gpt2", **opt)
+
+
+def _ids(data, bits=16):
+    return [FIRST[bits] + b for b in data]
+
+
+def test_a_failed_allocation_does_not_fail_the_next_call(fake):
+    """The runtime keeps its last error until it is read; a later call's launch does not take it for its own (and the
+    tile tickets stay in step with the calls)."""
+    with _tok() as tok:
+        text, ids, n = (fake.fake_device(k) for k in (1 << 20, 4 << 20, 8))
+        ctypes.memmove(text, b"x" * (1 << 20), 1 << 20)
+        fake.fake_budgets(16 << 20, ALL)
+        with pytest.raises(TokTierError) as e:
+            tok.encode_device(text, 1 << 20, ids, n)
+        assert e.value.status == -8
+        for _ in range(2):
+            tok.encode_device(text, 3, ids, n)
+        assert ctypes.cast(n, ctypes.POINTER(ctypes.c_int64))[0] == 3
+        assert ctypes.cast(ids, ctypes.POINTER(ctypes.c_int32))[:3] == _ids(b"xxx")
+        for p in (text, ids, n):
+            fake.fake_free(p)
