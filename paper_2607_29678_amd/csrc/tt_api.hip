@@ -187,6 +187,13 @@ namespace {
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// An allocation failed: the call's status says so, and the runtime's last error
+// is not left for the program's next check.
+int out_of_memory() {
+  (void)hipGetLastError();
+  return TT_ERR_OOM;
+}
+
 void free_ws(Workspace* s) {
   if (!s) return;
   if (s->dmem) (void)hipFree(s->dmem);
@@ -237,7 +244,7 @@ int ws_reserve(Workspace* s, uint64_t need, hipStream_t st) {
   size_t o_out = take(4 * N);
   size_t o_len = take(8);
   void* mem = nullptr;
-  if (hipMalloc(&mem, off) != hipSuccess) return TT_ERR_OOM;
+  if (hipMalloc(&mem, off) != hipSuccess) return out_of_memory();
   if (hipMemsetAsync(mem, 0, ctl_bytes, st) != hipSuccess) {
     (void)hipFree(mem);
     return TT_ERR_HIP;
@@ -270,7 +277,8 @@ int reserve_docs(Workspace* s, uint64_t words) {
   s->h_docs = nullptr;
   s->doc_cap = 0;
   const uint64_t cap = std::max<uint64_t>(words + words / 4, 512);
-  if (hipHostMalloc(reinterpret_cast<void**>(&s->h_docs), 8 * cap, hipHostMallocDefault) != hipSuccess) return TT_ERR_OOM;
+  if (hipHostMalloc(reinterpret_cast<void**>(&s->h_docs), 8 * cap, hipHostMallocDefault) != hipSuccess)
+    return out_of_memory();
   s->doc_cap = cap;
   return TT_OK;
 }
@@ -284,7 +292,7 @@ int get_ws(tt_tokenizer* h, hipStream_t stream, uint64_t need, Workspace** out) 
       s = new Workspace();
       if (hipHostMalloc(reinterpret_cast<void**>(&s->h_len), 8, hipHostMallocDefault) != hipSuccess) {
         free_ws(s);
-        return TT_ERR_OOM;
+        return out_of_memory();
       }
       h->ws[stream] = s;
     } else {
@@ -307,7 +315,7 @@ int reserve_spans(Workspace* s, uint64_t len, hipStream_t st) {
     s->d_spans = nullptr;
     s->span_cap = 0;
   }
-  if (hipMalloc(reinterpret_cast<void**>(&s->d_spans), 16 * (size_t)s->cap) != hipSuccess) return TT_ERR_OOM;
+  if (hipMalloc(reinterpret_cast<void**>(&s->d_spans), 16 * (size_t)s->cap) != hipSuccess) return out_of_memory();
   s->span_cap = s->cap;
   return TT_OK;
 }
@@ -329,7 +337,7 @@ int reserve_pinned(Workspace* s, uint64_t len) {
   if (hipHostMalloc(reinterpret_cast<void**>(&s->h_in), cap + 64, hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void**>(&s->h_ids), 4 * cap, hipHostMallocDefault) != hipSuccess) {
     drop();
-    return TT_ERR_OOM;
+    return out_of_memory();
   }
   s->pin_cap = cap;
   return TT_OK;
@@ -344,7 +352,7 @@ int reserve_pinned_spans(Workspace* s, uint64_t len) {
   s->span_pin_cap = 0;
   const uint64_t cap = std::min<uint64_t>(s->cap, (uint64_t)SPANS_PINNED_MAX);
   if (hipHostMalloc(reinterpret_cast<void**>(&s->h_spans), 16 * cap, hipHostMallocDefault) != hipSuccess)
-    return TT_ERR_OOM;
+    return out_of_memory();
   s->span_pin_cap = cap;
   return TT_OK;
 }
@@ -1056,14 +1064,14 @@ int tt_create_ex(const tt_merge* merges, int32_t n_merges, const uint8_t* vocab_
       hipMalloc(reinterpret_cast<void**>(&h->d_toklen), sizeof(uint32_t) * n_ids) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&h->d_join), sizeof(uint32_t) * 2048) != hipSuccess) {
     tt_destroy(h);
-    return TT_ERR_OOM;
+    return out_of_memory();
   }
   if (ignore && (hipMalloc(reinterpret_cast<void**>(&h->d_vdict), sizeof(u32x4) * vdict.size()) != hipSuccess ||
                  hipMalloc(reinterpret_cast<void**>(&h->d_vdict2), sizeof(u32x4) * vdict2.size()) != hipSuccess ||
                  hipMalloc(reinterpret_cast<void**>(&h->d_vlong), sizeof(u32x4) * vlong.size()) != hipSuccess ||
                  hipMalloc(reinterpret_cast<void**>(&h->d_vblob), vblob.size()) != hipSuccess)) {
     tt_destroy(h);
-    return TT_ERR_OOM;
+    return out_of_memory();
   }
   if (ignore &&
       (hipMemcpy(h->d_vdict, vdict.data(), sizeof(u32x4) * vdict.size(), hipMemcpyHostToDevice) != hipSuccess ||

@@ -191,6 +191,7 @@ extern "C" void fake_budgets(uint64_t device, uint64_t pinned) {
   budget[1] = pinned;
 }
 extern "C" uint64_t fake_used(int pinned) { return used[pinned]; }
+extern "C" int fake_last_error() { return (int)hipGetLastError(); }
 extern "C" void* fake_device(uint64_t n) {
   void* p = nullptr;
   return hipMalloc(&p, (size_t)n) == hipSuccess ? p : nullptr;

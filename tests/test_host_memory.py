@@ -81,3 +81,20 @@ def test_a_failed_allocation_does_not_fail_the_next_call(fake):
         assert ctypes.cast(ids, ctypes.POINTER(ctypes.c_int32))[:3] == _ids(b"xxx")
         for p in (text, ids, n):
             fake.fake_free(p)
+
+
+def test_a_failed_allocation_leaves_no_error_behind(fake):
+    """The status says what failed; the program's own check of the runtime after the call finds nothing."""
+    data, spans = b"x" * (1 << 20), 5 << 20
+    with _tok() as tok:
+        for device, pinned, call in ((16 << 20, ALL, lambda: tok.encode(data)), (ALL, 1 << 20, lambda: tok.encode(data)),
+                                     (180 << 20, ALL, lambda: tok.encode_spans(b"x" * spans))):
+            fake.fake_budgets(device, pinned)
+            with pytest.raises(TokTierError) as e:
+                call()
+            assert e.value.status == -8
+            assert fake.fake_last_error() == 0
+    fake.fake_budgets(1 << 18, ALL)
+    with pytest.raises(TokTierError) as e:
+        _tok()
+    assert e.value.status == -8 and fake.fake_last_error() == 0
