@@ -32,7 +32,9 @@
  *    calls add 5 bytes of pinned host memory per byte; span export (and
  *    sessions) 16 bytes of pinned host memory per byte up to 4 MiB, and past
  *    that 16 bytes of device memory per byte; batches 16 bytes of pinned host
- *    memory per document.  The capacity grows in powers of two from 64 KiB to
+ *    memory per document.  Batches, span export and sessions that find no
+ *    pinned memory copy between the caller's memory and the device instead
+ *    (tt_encode returns TT_ERR_OOM).  The capacity grows in powers of two from 64 KiB to
  *    the largest request seen on the stream (about 28 GB of device memory at
  *    TT_MAX_BYTES) and is freed by tt_destroy.
  */

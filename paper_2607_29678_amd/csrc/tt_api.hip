@@ -514,6 +514,16 @@ int encode_staged(tt_tokenizer* h, Workspace* s, const uint8_t* utf8, int64_t le
   return TT_OK;
 }
 
+// What a batch gives: where its IDs are (in the staging, or in `far`), and its
+// documents' output offsets (n_docs + 1, in the stream's pinned words, or in
+// `words`).
+struct BatchOut {
+  StagedIds ids;
+  const int64_t* offsets;
+  std::vector<int32_t> far;
+  std::vector<uint64_t> words;
+};
+
 // Fill a batch's words for its tiles (Work::tile_docs): both ends of the
 // windows only move forward.
 void fill_tile_docs(const int64_t* offsets, int64_t n_docs, uint32_t n_tiles, uint2* tiles) {
@@ -526,54 +536,72 @@ void fill_tile_docs(const int64_t* offsets, int64_t n_docs, uint32_t n_tiles, ui
   }
 }
 
-// One batch over host documents.  On success *od points at the documents'
-// output offsets (n_docs + 1, in the stream's pinned words) and *ids says where
-// the IDs are: in the staging, or, past PINNED_MAX, in `far`.
+// One batch over host documents.  Requests past PINNED_MAX are copied between
+// the caller's memory and the device, and so is whatever no pinned memory is to
+// be had for.
 int batch_staged(tt_tokenizer* h, hipStream_t st, const uint8_t* concat, int64_t len, const int64_t* offsets,
-                 int64_t n_docs, StagedIds* ids, const int64_t** od, std::vector<int32_t>& far) {
+                 int64_t n_docs, BatchOut* r) {
   if (n_docs > INT32_MAX) return TT_ERR_TOO_LARGE;
   if (hipSetDevice(h->device) != hipSuccess) return TT_ERR_HIP;
   Workspace* s = nullptr;
   int rc = get_ws(h, st, (uint64_t)len, &s);
   if (rc) return rc;
   const uint32_t n_tiles = n_tiles_for((uint32_t)len);
-  const uint64_t nd = (uint64_t)n_docs + 1;
-  rc = reserve_docs(s, 2 * nd + n_tiles);
-  if (rc) return rc;
-  int64_t* doc = reinterpret_cast<int64_t*>(s->h_docs);
-  uint2* tiles = reinterpret_cast<uint2*>(s->h_docs + nd);
-  int64_t* out = reinterpret_cast<int64_t*>(s->h_docs + nd + n_tiles);
-  const BatchDocs docs{doc, (int32_t)n_docs, tiles, out};
-  const bool staged = (uint64_t)len <= PINNED_MAX;
-  const uint8_t* src = s->d_in;
-  int64_t* length = s->d_len;
-  *ids = StagedIds{s->d_out, nullptr, nullptr};
+  const uint64_t nd = (uint64_t)n_docs + 1, n_words = 2 * nd + n_tiles;
+  // the words of the documents: as the host writes and reads them, and where the device does
+  struct DeviceWords {
+    uint64_t* p = nullptr;
+    ~DeviceWords() {
+      if (p) (void)hipFree(p);
+    }
+  } far_words;
+  rc = reserve_docs(s, n_words);
+  if (rc && rc != TT_ERR_OOM) return rc;
+  uint64_t *words = s->h_docs, *dev = s->h_docs;
+  if (rc) {
+    if (hipMalloc(reinterpret_cast<void**>(&far_words.p), 8 * n_words) != hipSuccess) return out_of_memory();
+    r->words.resize(n_words);
+    words = r->words.data();
+    dev = far_words.p;
+  }
+  std::memcpy(words, offsets, 8 * nd);
+  fill_tile_docs(offsets, n_docs, n_tiles, reinterpret_cast<uint2*>(words + nd));
+  int64_t* out = reinterpret_cast<int64_t*>(words + nd + n_tiles);
+  out[n_docs] = 0;
+  if (far_words.p && hipMemcpyAsync(dev, words, 8 * n_words, hipMemcpyHostToDevice, st) != hipSuccess) return TT_ERR_HIP;
+  const BatchDocs docs{reinterpret_cast<const int64_t*>(dev), (int32_t)n_docs, reinterpret_cast<const uint2*>(dev + nd),
+                       reinterpret_cast<int64_t*>(dev + nd + n_tiles)};
+  bool staged = (uint64_t)len <= PINNED_MAX;
   if (staged) {
     rc = reserve_pinned(s, (uint64_t)len);
-    if (rc) return rc;
+    if (rc && rc != TT_ERR_OOM) return rc;
+    staged = rc == TT_OK;
+  }
+  const uint8_t* src = s->d_in;
+  int64_t* length = s->d_len;
+  r->ids = StagedIds{s->d_out, nullptr, nullptr};
+  if (staged) {
     src = stage_in(s, concat, len, false);
     length = s->h_len;
-    *ids = staged_ids(h, s, len);
+    r->ids = staged_ids(h, s, len);
   } else if (hipMemcpyAsync(s->d_in, concat, (size_t)len, hipMemcpyHostToDevice, st) != hipSuccess) {
     return TT_ERR_HIP;
   }
-  std::memcpy(doc, offsets, 8 * nd);
-  fill_tile_docs(offsets, n_docs, n_tiles, tiles);
-  out[n_docs] = 0;
-  rc = run_chain(h, s, src, (uint32_t)len, ids->wide, length, st, 1, nullptr, ids->lo16, ids->hi8, &docs);
+  rc = run_chain(h, s, src, (uint32_t)len, r->ids.wide, length, st, 1, nullptr, r->ids.lo16, r->ids.hi8, &docs);
   if (rc) return rc;
+  if (far_words.p && hipMemcpyAsync(out, docs.out, 8 * nd, hipMemcpyDeviceToHost, st) != hipSuccess) return TT_ERR_HIP;
   if (hipStreamSynchronize(st) != hipSuccess) return TT_ERR_HIP;
   const int64_t T = out[n_docs];
   if (T < 0) return (int)T;
   if (T > len) return TT_ERR_HIP;  // cannot happen: at most one ID per byte
   if (!staged) {
-    far.resize((size_t)std::max<int64_t>(T, 1));
-    if (hipMemcpyAsync(far.data(), s->d_out, (size_t)T * 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
+    r->far.resize((size_t)std::max<int64_t>(T, 1));
+    if (hipMemcpyAsync(r->far.data(), s->d_out, (size_t)T * 4, hipMemcpyDeviceToHost, st) != hipSuccess ||
         hipStreamSynchronize(st) != hipSuccess)
       return TT_ERR_HIP;
-    ids->wide = far.data();
+    r->ids.wide = r->far.data();
   }
-  *od = out;
+  r->offsets = out;
   return TT_OK;
 }
 
@@ -1156,18 +1184,17 @@ int tt_encode(tt_tokenizer* h, const uint8_t* utf8, int64_t len, int32_t* out_id
     std::vector<AddedSet::Match> lits;
     added_documents(h->added, utf8, 0, len, docs, lits);
     if (!lits.empty()) {
-      std::vector<int32_t> far;
-      StagedIds ids;
-      const int64_t* od;
-      int rc = batch_staged(h, st, utf8, len, docs.data(), (int64_t)docs.size() - 1, &ids, &od, far);
+      BatchOut r;
+      int rc = batch_staged(h, st, utf8, len, docs.data(), (int64_t)docs.size() - 1, &r);
       if (rc) return rc;
+      const int64_t* od = r.offsets;
       int64_t T = 0;
       for (size_t j = 0; j + 1 < docs.size(); ++j) {
         if (j & 1) {
           out_ids[T++] = lits[j / 2].id;
         } else {
           const int64_t c = od[j + 1] - od[j];
-          ids.take(out_ids + T, (size_t)od[j], (size_t)c);
+          r.ids.take(out_ids + T, (size_t)od[j], (size_t)c);
           T += c;
         }
       }
@@ -1230,11 +1257,13 @@ int tt_encode_spans(tt_tokenizer* h, const uint8_t* utf8, int64_t len, int32_t* 
     int32_t *ids, *spans;
     int64_t T = 0;
     const int rc = encode_spans_staged(h, utf8, len, &ids, &spans, &T, stream);
-    if (rc) return rc;
-    host_copy(out_ids, ids, 4 * (size_t)T);
-    host_copy(out_spans, spans, 16 * (size_t)T);
-    *out_len = T;
-    return TT_OK;
+    if (rc == TT_OK) {
+      host_copy(out_ids, ids, 4 * (size_t)T);
+      host_copy(out_spans, spans, 16 * (size_t)T);
+      *out_len = T;
+    }
+    if (rc != TT_ERR_OOM) return rc;
+    // (no pinned memory: copied, as longer requests are)
   }
   if (hipSetDevice(h->device) != hipSuccess) return TT_ERR_HIP;
   Workspace* s = nullptr;
@@ -1287,11 +1316,10 @@ int tt_encode_batch(tt_tokenizer* h, const uint8_t* concat, const int64_t* doc_o
     }
     first_doc[(size_t)n_docs] = (int64_t)docs.size() - 1;
     first_lit[(size_t)n_docs] = (int64_t)lits.size();
-    std::vector<int32_t> far;
-    StagedIds ids;
-    const int64_t* od;
-    int rc = batch_staged(h, st, concat, len, docs.data(), (int64_t)docs.size() - 1, &ids, &od, far);
+    BatchOut r;
+    int rc = batch_staged(h, st, concat, len, docs.data(), (int64_t)docs.size() - 1, &r);
     if (rc) return rc;
+    const int64_t* od = r.offsets;
     int64_t T = 0;
     for (int32_t d = 0; d < n_docs; ++d) {
       out_doc_offsets[d] = T;
@@ -1300,7 +1328,7 @@ int tt_encode_batch(tt_tokenizer* h, const uint8_t* concat, const int64_t* doc_o
           out_ids[T++] = lits[(size_t)(first_lit[(size_t)d] + (j - first_doc[(size_t)d]) / 2)].id;
         } else {
           const int64_t c = od[(size_t)j + 1] - od[(size_t)j];
-          ids.take(out_ids + T, (size_t)od[(size_t)j], (size_t)c);
+          r.ids.take(out_ids + T, (size_t)od[(size_t)j], (size_t)c);
           T += c;
         }
       }
@@ -1308,13 +1336,11 @@ int tt_encode_batch(tt_tokenizer* h, const uint8_t* concat, const int64_t* doc_o
     out_doc_offsets[n_docs] = T;
     return TT_OK;
   }
-  std::vector<int32_t> far;
-  StagedIds ids;
-  const int64_t* od;
-  int rc = batch_staged(h, st, concat, len, doc_offsets, n_docs, &ids, &od, far);
+  BatchOut r;
+  int rc = batch_staged(h, st, concat, len, doc_offsets, n_docs, &r);
   if (rc) return rc;
-  ids.take(out_ids, 0, (size_t)od[n_docs]);
-  std::memcpy(out_doc_offsets, od, 8 * ((size_t)n_docs + 1));
+  r.ids.take(out_ids, 0, (size_t)r.offsets[n_docs]);
+  std::memcpy(out_doc_offsets, r.offsets, 8 * ((size_t)n_docs + 1));
   return TT_OK;
 }
 

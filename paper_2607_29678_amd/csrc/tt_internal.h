@@ -285,6 +285,7 @@ uint32_t handle_max_token_bytes(const tt_tokenizer* h);  // longest token, in by
 // Span export of a host request through the stream's pinned staging, with one
 // synchronisation: on success *ids and *spans point at the T records there,
 // valid (and writable) until the next call on the stream.  len <= SPANS_PINNED_MAX.
+// TT_ERR_OOM when there is no pinned memory for them (tt_encode_spans then copies).
 constexpr int64_t SPANS_PINNED_MAX = 1 << 22;
 int encode_spans_staged(tt_tokenizer* h, const uint8_t* utf8, int64_t len, int32_t** ids, int32_t** spans, int64_t* T,
                         void* stream);

@@ -219,13 +219,15 @@ int64_t encode_range(tt_session* s, int64_t from, int64_t chars_before, void* st
                      int32_t** spans) {
   const int64_t n = (int64_t)s->text.size() - from;
   int64_t T = 0;
+  int rc = TT_ERR_OOM;
   if (n <= tt::SPANS_PINNED_MAX) {
-    const int rc = tt::encode_spans_staged(s->h, s->text.data() + from, n, ids, spans, &T, stream);
-    if (rc != TT_OK) return rc;
-  } else {
+    rc = tt::encode_spans_staged(s->h, s->text.data() + from, n, ids, spans, &T, stream);
+    if (rc != TT_OK && rc != TT_ERR_OOM) return rc;
+  }
+  if (rc != TT_OK) {  // a longer range, or no pinned memory
     s->f_ids.resize((size_t)n);
     s->f_spans.resize(4 * (size_t)n);
-    const int rc = tt_encode_spans(s->h, s->text.data() + from, n, s->f_ids.data(), s->f_spans.data(), &T, stream);
+    rc = tt_encode_spans(s->h, s->text.data() + from, n, s->f_ids.data(), s->f_spans.data(), &T, stream);
     if (rc != TT_OK) return rc;
     *ids = s->f_ids.data();
     *spans = s->f_spans.data();

@@ -98,3 +98,60 @@ def test_a_failed_allocation_leaves_no_error_behind(fake):
     with pytest.raises(TokTierError) as e:
         _tok()
     assert e.value.status == -8 and fake.fake_last_error() == 0
+
+
+TEXT = "".join("wörd %d, 中文 – x%d\n" % (i, i * i) for i in range(9000))
+
+
+def _docs(n):
+    data = TEXT.encode()
+    cuts, at = [0], 0
+    for k in range(n):
+        at = min(len(data), at + (k * 7919) % (2 * len(data) // n + 1))
+        while at < len(data) and (data[at] & 0xC0) == 0x80:
+            at += 1
+        cuts.append(at)
+    return [data[a:b] for a, b in zip(cuts, cuts[1:])] + [b"", data[at:], b""]
+
+
+def _spans(data):
+    chars, out = 0, []
+    for i, b in enumerate(data):
+        chars += (b & 0xC0) != 0x80
+        out.append([i, i + 1, chars - 1, chars])
+    return out
+
+
+# no pinned memory but the length word; room for the documents' words, not for the IDs; room for the staged
+# IDs, not for the spans; all
+@pytest.mark.parametrize("pinned", [8, 64 << 10, 3 << 20, ALL])
+@pytest.mark.parametrize("bits", [16, 24, 32])
+def test_calls_without_pinned_memory(fake, bits, pinned):
+    """Batches, span export and sessions that find no pinned memory give the same results through copies."""
+    docs, data = _docs(300), TEXT.encode()
+    with _tok(bits) as tok:
+        fake.fake_budgets(ALL, pinned)
+        for batch in (docs, [b"a", b"", b"bc"], docs[:40]):
+            assert [g.tolist() for g in tok.encode_batch(batch)] == [_ids(d, bits) for d in batch]
+        with pytest.raises(TokTierError) as e:
+            tok.encode_batch([b"ab", b"\x80"])
+        assert e.value.status == -5
+        ids, spans = tok.encode_spans(data)
+        assert ids.tolist() == _ids(data, bits) and spans.tolist() == _spans(data)
+        with Session(tok, 16) as s:
+            step = len(TEXT) // 5 + 1
+            for k in range(0, len(TEXT), step):
+                s.append(TEXT[k:k + step].encode())
+            ids, spans = s.tokens()
+        assert ids.tolist() == _ids(data, bits) and spans.tolist() == _spans(data)
+        assert fake.fake_last_error() == 0
+        before = fake.fake_used(0)
+        assert [g.tolist() for g in tok.encode_batch(docs)] == [_ids(d, bits) for d in docs]
+        assert fake.fake_used(0) == before  # (what a call without pinned memory took is given back)
+    # literals: their segments go the way of a batch
+    fake.fake_budgets(ALL, ALL)
+    with _tok(bits, added=[("<|x|>", 999)]) as tok:
+        fake.fake_budgets(ALL, fake.fake_used(1) + pinned if pinned != ALL else ALL)
+        want = _ids(b"ab", bits) + [999] + _ids(data, bits)
+        assert tok.encode(b"ab<|x|>" + data).tolist() == want
+        assert [g.tolist() for g in tok.encode_batch([b"ab<|x|>", data])] == [want[:3], want[3:]]
