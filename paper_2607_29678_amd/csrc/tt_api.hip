@@ -372,7 +372,7 @@ bool host_pinned(const void* p, int64_t len) {
   return a.type == hipMemoryTypeHost;
 }
 
-// The documents of a batch, in memory the device reads and writes.
+// The documents of a batch, none of them empty, in memory the device reads and writes.
 struct BatchDocs {
   const int64_t* offsets;  // [n + 1] byte offsets
   int32_t n;
@@ -564,12 +564,21 @@ int batch_staged(tt_tokenizer* h, hipStream_t st, const uint8_t* concat, int64_t
     words = r->words.data();
     dev = far_words.p;
   }
-  std::memcpy(words, offsets, 8 * nd);
-  fill_tile_docs(offsets, n_docs, n_tiles, reinterpret_cast<uint2*>(words + nd));
+  // The device gets one document per position: empty ones share their output offset
+  // with the next, which is filled in afterwards.  (One block has all documents of
+  // its bytes and reads their offsets over the bus: 300,000 empty ones between two
+  // others took 1.70 ms, now 0.37; at the end 1.52, now 0.37.)
+  int64_t* doc = reinterpret_cast<int64_t*>(words);
+  int64_t n_dev = 0;
+  for (int64_t j = 0; j <= n_docs; ++j) {
+    doc[n_dev] = offsets[j];
+    n_dev += j < n_docs && offsets[j + 1] != offsets[j];
+  }
+  fill_tile_docs(doc, n_dev, n_tiles, reinterpret_cast<uint2*>(words + nd));
   int64_t* out = reinterpret_cast<int64_t*>(words + nd + n_tiles);
-  out[n_docs] = 0;
+  out[n_dev] = 0;
   if (far_words.p && hipMemcpyAsync(dev, words, 8 * n_words, hipMemcpyHostToDevice, st) != hipSuccess) return TT_ERR_HIP;
-  const BatchDocs docs{reinterpret_cast<const int64_t*>(dev), (int32_t)n_docs, reinterpret_cast<const uint2*>(dev + nd),
+  const BatchDocs docs{reinterpret_cast<const int64_t*>(dev), (int32_t)n_dev, reinterpret_cast<const uint2*>(dev + nd),
                        reinterpret_cast<int64_t*>(dev + nd + n_tiles)};
   bool staged = (uint64_t)len <= PINNED_MAX;
   if (staged) {
@@ -589,9 +598,10 @@ int batch_staged(tt_tokenizer* h, hipStream_t st, const uint8_t* concat, int64_t
   }
   rc = run_chain(h, s, src, (uint32_t)len, r->ids.wide, length, st, 1, nullptr, r->ids.lo16, r->ids.hi8, &docs);
   if (rc) return rc;
-  if (far_words.p && hipMemcpyAsync(out, docs.out, 8 * nd, hipMemcpyDeviceToHost, st) != hipSuccess) return TT_ERR_HIP;
+  if (far_words.p && hipMemcpyAsync(out, docs.out, 8 * ((size_t)n_dev + 1), hipMemcpyDeviceToHost, st) != hipSuccess)
+    return TT_ERR_HIP;
   if (hipStreamSynchronize(st) != hipSuccess) return TT_ERR_HIP;
-  const int64_t T = out[n_docs];
+  const int64_t T = out[n_dev];
   if (T < 0) return (int)T;
   if (T > len) return TT_ERR_HIP;  // cannot happen: at most one ID per byte
   if (!staged) {
@@ -600,6 +610,10 @@ int batch_staged(tt_tokenizer* h, hipStream_t st, const uint8_t* concat, int64_t
         hipStreamSynchronize(st) != hipSuccess)
       return TT_ERR_HIP;
     r->ids.wide = r->far.data();
+  }
+  for (int64_t j = n_docs, k = n_dev; k < j; --j) {  // (the documents before the first empty one stand already)
+    out[j] = out[k];
+    k -= offsets[j - 1] != offsets[j];
   }
   r->offsets = out;
   return TT_OK;

@@ -221,7 +221,7 @@ constexpr uint32_t NO_START = 0xFFFFFFFFu;  // tile_last: no unit starts in the 
 struct Work {
   const uint8_t* text;      // request bytes (caller's or staged)
   uint32_t n;               // bytes
-  const int64_t* doc_off;   // batch: n_docs+1 byte offsets, else nullptr
+  const int64_t* doc_off;   // batch: n_docs+1 byte offsets (no document is empty), else nullptr
   int32_t n_docs;
   const uint2* tile_docs;   // batch: [tiles] the first document at or after the first byte of the
                             // tile's padded window, and at or after the window's end

@@ -635,7 +635,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
       int64_t d = w.doc_off[j];
       if (d >= w0 + PT_WIN + 16) break;
       if (d >= n) continue;
-      sh.dstart[PT_PAD + (d - w0)] = 1;  // several empty documents may start here; all store the same value
+      sh.dstart[PT_PAD + (d - w0)] = 1;
     }
     __syncthreads();
   }
@@ -1448,8 +1448,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
   for (uint32_t i = (uint32_t)tid; i < ctot; i += PT_THREADS) put(obase + i, sh.ph.c.id[i]);
   if (BATCH) {
     // The output offset of every document whose first unit this tile encodes
-    // (a document starts a unit; empty documents share the start of the next
-    // one), and in the last tile the total, or the error, for those at the end.
+    // (a document starts a unit), and in the last tile the total, or the error.
     if constexpr (IGN) {  // (else the unit starts are still there)
       store_nibbles(sh.uw, qb, lane, flags);
       if ((tid & 7) == 0) sh.upre[tid >> 3] = texcl;
@@ -1479,7 +1478,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
         if (w.doc_off[mid] < (int64_t)s_prev) lo = mid + 1;
         else hi = mid;
       }
-      for (; lo < (int64_t)docs.x && w.doc_off[lo] == (int64_t)s_prev; ++lo) w.out_doc_off[lo] = prefix;
+      if (lo < (int64_t)docs.x && w.doc_off[lo] == (int64_t)s_prev) w.out_doc_off[lo] = prefix;
     }
   }
   if (SPANS) {

@@ -26,6 +26,7 @@ std::mutex mu;
 std::map<uintptr_t, Block> blocks;
 size_t used[2], budget[2] = {SIZE_MAX, SIZE_MAX};  // device, pinned
 thread_local hipError_t last = hipSuccess;
+int32_t documents;  // of the last batch, as the kernel got them
 
 hipError_t fail(hipError_t e) { return last = e; }
 
@@ -133,6 +134,7 @@ void kernel(Work w, DevTables tb, int mode) {
   reach(w.out_len, 8, "the output length");
   bool ok = valid(w.text, n);
   if (w.doc_off) {
+    documents = w.n_docs;
     const size_t nd = (size_t)w.n_docs + 1;
     reach(w.doc_off, 8 * nd, "the document offsets");
     reach(w.out_doc_off, 8 * nd, "the output offsets");
@@ -197,3 +199,4 @@ extern "C" void* fake_device(uint64_t n) {
   return hipMalloc(&p, (size_t)n) == hipSuccess ? p : nullptr;
 }
 extern "C" void fake_free(void* p) { (void)hipFree(p); }
+extern "C" int32_t fake_documents() { return documents; }

@@ -1,6 +1,6 @@
-"""What the host code (``tt_api.hip``, ``tt_session.hip``) does when memory runs out, on the CPU: the sources
-themselves, compiled for the host against a runtime with budgets for device and pinned memory, whose kernel gives
-one token per byte (``tests/native/fake_hip.cpp``)."""
+"""The host code (``tt_api.hip``, ``tt_session.hip``) on the CPU: what it does when memory runs out, and which
+documents it hands to the kernel.  The sources themselves, compiled for the host against a runtime with budgets for
+device and pinned memory, whose kernel gives one token per byte (``tests/native/fake_hip.cpp``)."""
 
 import ctypes
 import functools
@@ -155,3 +155,17 @@ def test_calls_without_pinned_memory(fake, bits, pinned):
         want = _ids(b"ab", bits) + [999] + _ids(data, bits)
         assert tok.encode(b"ab<|x|>" + data).tolist() == want
         assert [g.tolist() for g in tok.encode_batch([b"ab<|x|>", data])] == [want[:3], want[3:]]
+
+
+@pytest.mark.parametrize("docs", [[b"", b"ab", b"", b"", b"c" * 5000, b""], [b"a", b"b"], [b"", b"", b"x"], [b"x", b"", b""],
+                                  [b"ab"] + [b""] * 700 + [b"cd"] * 3 + [b""] * 40 + ["é".encode() * 3000] + [b""] * 2])
+@pytest.mark.parametrize("pinned", [8, ALL])
+def test_empty_documents_stay_on_the_host(fake, docs, pinned):
+    """One block has all documents of its bytes: the kernel gets one per position, however many are empty."""
+    with _tok() as tok:
+        fake.fake_budgets(ALL, pinned)
+        assert [g.tolist() for g in tok.encode_batch(docs)] == [_ids(d) for d in docs]
+        assert fake.fake_documents() == sum(1 for d in docs if d)
+        with pytest.raises(TokTierError) as e:
+            tok.encode_batch(docs + [b"", b"\xff", b""])
+        assert e.value.status == -5
