@@ -1564,18 +1564,18 @@ hipError_t launch_pat(const Work& w, const DevTables& tb, int mode, bool batch, 
   dim3 grid(w.n_tiles), block(PT_THREADS);
 #define TT_TILE_W(B, M, I, V) return launch(tile_kernel<PAT, B, M, I, V>, grid, block, s, w, tb)
 #define TT_TILE(B, M, I) TT_TILE_W(B, M, I, 6)
-  // GPT-2- and cl100k-style encoding fits 64 registers and 40 KB of LDS, so a
-  // fourth block fits on a compute unit: a 16M-character corpus takes 268 us
-  // instead of 309.  Where three blocks per unit already hold every tile the
-  // tighter registers only cost (1M characters 47.4 -> 47.7 us, 100K 18.7 ->
-  // 18.8), so the line is at the tiles that three blocks on each of the chip's
-  // 256 units hold.
+  // GPT-2- and cl100k-style encoding of one request fits 64 registers and 40 KB of
+  // LDS, so a fourth block fits on a compute unit: a 16M-character corpus takes 249 us
+  // instead of 305.  Where three blocks per unit already hold every tile the
+  // tighter registers only cost (1M multilingual characters 44.8 -> 46.6 us, 100K
+  // of prose and code 17.0 -> 18.1), so the line is at the tiles that three blocks on each of the chip's
+  // 256 units hold.  A batch does not fit (registers spill to scratch memory) and
+  // stays with three: 1.7M characters in 64 documents take 182 us, 199 with four
+  // blocks; 16M in 512 829 and 852 (GPT-2), 1,441 and 1,426 (cl100k, whose runs
+  // differ by 2 %); host to host.
   constexpr uint32_t RESIDENT_TILES = 3 * 256;
   if constexpr (PAT == TT_PATTERN_GPT2 || PAT == TT_PATTERN_CL100K) {
-    if (mode == 1 && !ignore && w.n_tiles > RESIDENT_TILES) {
-      if (batch) TT_TILE_W(true, 1, false, 8);
-      else TT_TILE_W(false, 1, false, 8);
-    }
+    if (mode == 1 && !ignore && !batch && w.n_tiles > RESIDENT_TILES) TT_TILE_W(false, 1, false, 8);
   }
   if (mode == 0) {
     if (ignore) return hipErrorInvalidValue;  // the split export has no model stage
