@@ -481,8 +481,9 @@ __device__ unsigned long long tt_phase_buf[TT_PHASE_TILES * TT_PHASE_SLOTS];
 #endif
 #define TT_PHASE(k) TT_PHASE_BY(k, tid == 0)
 
-// The kernel's arguments, read again from where the launch put them, for a rare
-// phase: it then adds nothing to what the phases around it hold in scalar registers.
+// The kernel's one argument; tile_args() reads it again from where the launch put
+// it, for a rare phase: it then adds nothing to what the phases around it hold in
+// scalar registers.
 struct TileArgs {
   Work w;
   DevTables tb;
@@ -500,7 +501,9 @@ __device__ __forceinline__ const TileArgs& tile_args() {
 // WAVES:  wavefronts per SIMD the registers are allotted for: 6 (three blocks on
 //         a compute unit) or 8 (four; launch_pat says when).
 template <int PAT, bool BATCH, int MODE, bool IGN, int WAVES>
-__global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))) void tile_kernel(Work w, DevTables tb) {
+__global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVES))) void tile_kernel(TileArgs args) {
+  const Work& w = args.w;
+  const DevTables& tb = args.tb;
   constexpr bool SEG = MODE >= 1;
   constexpr bool SPANS = MODE == 2;
   constexpr bool DS = PAT == TT_PATTERN_DEEPSEEK;
@@ -1562,7 +1565,7 @@ namespace {
 template <int PAT>
 hipError_t launch_pat(const Work& w, const DevTables& tb, int mode, bool batch, bool ignore, hipStream_t s) {
   dim3 grid(w.n_tiles), block(PT_THREADS);
-#define TT_TILE_W(B, M, I, V) return launch(tile_kernel<PAT, B, M, I, V>, grid, block, s, w, tb)
+#define TT_TILE_W(B, M, I, V) return launch(tile_kernel<PAT, B, M, I, V>, grid, block, s, TileArgs{w, tb})
 #define TT_TILE(B, M, I) TT_TILE_W(B, M, I, 6)
   // GPT-2- and cl100k-style encoding of one request fits 64 registers and 40 KB of
   // LDS, so a fourth block fits on a compute unit: a 16M-character corpus takes 249 us
