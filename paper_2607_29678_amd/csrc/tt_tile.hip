@@ -170,24 +170,6 @@ __device__ __forceinline__ uint32_t class_bits(uint32_t cls2) {  // 0 other, 1 l
   return 1u << ((AT >> (8u * cls2)) & 31u);
 }
 
-// Strict UTF-8 decode from bytes in registers, with selects only: the length
-// of the sequence that starts with b0 (0 if it is invalid or longer than
-// `avail`) and its code point.
-__device__ __forceinline__ uint32_t decode_sel(uint32_t b0, uint32_t b1, uint32_t b2, uint32_t b3, uint32_t avail,
-                                               uint32_t& cp) {
-  const uint32_t len = b0 < 0x80u ? 1u : b0 < 0xC2u ? 0u : b0 < 0xE0u ? 2u : b0 < 0xF0u ? 3u : b0 < 0xF5u ? 4u : 0u;
-  const uint32_t lo = b0 == 0xE0u ? 0xA0u : b0 == 0xF0u ? 0x90u : 0x80u;
-  const uint32_t hi = b0 == 0xEDu ? 0x9Fu : b0 == 0xF4u ? 0x8Fu : 0xBFu;
-  const bool ok1 = len < 2u || (b1 >= lo && b1 <= hi);
-  const bool ok2 = len < 3u || (b2 & 0xC0u) == 0x80u;
-  const bool ok3 = len < 4u || (b3 & 0xC0u) == 0x80u;
-  const uint32_t c2 = ((b0 & 0x1Fu) << 6) | (b1 & 0x3Fu);
-  const uint32_t c3 = ((b0 & 0x0Fu) << 12) | ((b1 & 0x3Fu) << 6) | (b2 & 0x3Fu);
-  const uint32_t c4 = ((b0 & 0x07u) << 18) | ((b1 & 0x3Fu) << 12) | ((b2 & 0x3Fu) << 6) | (b3 & 0x3Fu);
-  cp = len <= 1u ? b0 : len == 2u ? c2 : len == 3u ? c3 : c4;
-  return (len != 0u && len <= avail && ok1 && ok2 && ok3) ? len : 0u;
-}
-
 template <typename F>
 __device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v, int lane, F comb) {
 #pragma unroll
@@ -828,44 +810,13 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
         else if constexpr (WIDE) return cp < 128u ? o2_ascii_class(cp) : o2_table_class(ct.l1, ct.l2, cp);
         else return cp == 10u || cp == 13u ? 4u : cp < 128u ? (cp == 32u || (cp - 9u) < 5u ? 3u : 0u) : table_class(ct, cp);
       };
-      // The text after the window, 16 bytes per lane per step, from its first
-      // character to the first one that `in` does not hold, by the pattern's
-      // class (ASCII bytes by `plain`, which holds part of `in`): its class, or
-      // ~0 at the end of the text or document and for invalid input (reported
-      // elsewhere).  Every lane holds the same position and answer.
+      // The first class after the window that `in` does not hold (ASCII bytes by
+      // `plain`, which holds part of `in`), within the document.
       auto beyond = [&](auto plain, auto in) -> uint32_t {
         if (w0 + PT_WIN >= n) return ~0u;
-        const uint8_t* base = w.text + (w0 + PT_WIN);
         int64_t lim = n;
         if (BATCH && docs.y < (uint32_t)w.n_docs) lim = w.doc_off[docs.y];
-        const uint32_t end = (uint32_t)(lim - (w0 + PT_WIN));
-        uint32_t pos = 0;
-        while (pos < end && (base[pos] & 0xC0u) == 0x80u) ++pos;
-#pragma unroll 1
-        for (;;) {
-          uint32_t first = 16u;
-#pragma unroll 4
-          for (int k = 15; k >= 0; --k) {
-            const uint32_t p = pos + 16u * (uint32_t)lane + (uint32_t)k;
-            if (!(p < end && plain((uint32_t)base[p]))) first = (uint32_t)k;  // (the end counts as a stop)
-          }
-          const uint64_t m = __ballot(first < 16u);
-          if (m == 0ull) {
-            pos += 16u * 64u;
-            continue;
-          }
-          const int src = __builtin_ctzll(m);
-          const uint32_t p = pos + 16u * (uint32_t)src + (uint32_t)__builtin_amdgcn_readlane((int)first, src);
-          if (p >= end) return ~0u;
-          const uint32_t avail = end - p < 4u ? end - p : 4u;
-          auto at = [&](uint32_t k) -> uint32_t { return k < avail ? (uint32_t)base[p + k] : 0u; };
-          uint32_t cp = 0;
-          const uint32_t len = decode_sel(at(0), at(1), at(2), at(3), avail, cp);
-          if (len == 0u) return ~0u;
-          const uint32_t c = class_of(cp);
-          if (!in(c)) return c;
-          pos = p + len;
-        }
+        return first_outside(w.text + (w0 + PT_WIN), (uint32_t)(lim - (w0 + PT_WIN)), lane, plain, in, class_of);
       };
       constexpr uint32_t C_WS = DS ? (uint32_t)DS_WS : WIDE ? (uint32_t)O2_WS : 3u;
       constexpr uint32_t C_NL = DS ? (uint32_t)DS_NL : WIDE ? (uint32_t)O2_NL : 4u;

@@ -14,6 +14,8 @@
 
 #include <string.h>
 
+#include <unordered_map>
+
 #include "tt_runs.h"
 
 using namespace tt;
@@ -26,22 +28,9 @@ struct Tiles {
   const char* cls;
   const uint8_t* docs;  // 1 where a document starts, or null: one text
   std::vector<uint32_t> sums;
+  std::unordered_map<uint32_t, char> of;  // the class of every code point of the text
+  uint64_t ops;                           // cross-lane operations of the tile that takes the most
 };
-
-// class after the window's end: the first one (from its first character) not in
-// `in`, or 0 at the end of the text or document
-char beyond(const Tiles& T, int at, const char* in) {
-  int end = T.n;
-  if (T.docs)
-    for (int p = at; p < T.n; ++p)
-      if (T.docs[p]) {
-        end = p;
-        break;
-      }
-  for (int p = at; p < end; ++p)
-    if (T.cls[p] != '.' && !strchr(in, T.cls[p])) return T.cls[p];
-  return 0;
-}
 
 void one_tile(Tiles& T, int t, uint8_t* out) {
   const int w0 = t * PT_OWN - PT_HALO, n = T.n;
@@ -111,9 +100,21 @@ void one_tile(Tiles& T, int t, uint8_t* out) {
       }
       return RunCarry{acc % 3u, (val & SUM_TAIL) != 0u, (val >> SUM_STATE_SHIFT) & 15u};
     };
-    auto last_ws = [&]() -> bool { return beyond(T, w0 + PT_WIN, "WS") != 'R'; };
+    auto beyond = [&](auto plain, const char* set) -> uint32_t {
+      const int at = w0 + PT_WIN;
+      if (at >= n) return ~0u;
+      int end = n;
+      for (int p = at; T.docs && p < end; ++p)
+        if (T.docs[p]) end = p;
+      return first_outside(T.text + at, (uint32_t)(end - at), lane, plain,
+                           [&](uint32_t c) { return strchr(set, (int)c) != nullptr; },
+                           [&](uint32_t cp) { return (uint32_t)T.of.at(cp); });
+    };
+    auto last_ws = [&]() -> bool {
+      return beyond([](uint32_t c) { return c == 0x20u || c == 0x09u || c == 0x0Bu || c == 0x0Cu; }, "WS") != 'R';
+    };
     auto upper = [&]() -> bool {
-      const char c = beyond(T, w0 + PT_WIN, "U");
+      const uint32_t c = beyond([](uint32_t x) { return x - 'A' < 26u; }, "U");
       return c == 'l' || c == 'X' || c == 'M';
     };
     uint32_t st = 0;
@@ -127,6 +128,7 @@ void one_tile(Tiles& T, int t, uint8_t* out) {
     }
     starts[lane] = st & own;
   });
+  T.ops = std::max(T.ops, wave::count[0]);
   for (int q = PT_HALO; q < PT_HALO + PT_OWN && w0 + q < n; ++q)
     out[w0 + q] = (starts[q >> 5] >> (q & 31)) & 1u;
 }
@@ -136,8 +138,17 @@ void one_tile(Tiles& T, int t, uint8_t* out) {
 // The bytes a tile owns.
 extern "C" int run_rules_own() { return PT_OWN; }
 
-// out[p] = 1 where a piece starts.
-extern "C" void run_rules(int pattern, const uint8_t* text, const char* cls, int n, const uint8_t* docs, uint8_t* out) {
-  Tiles T{pattern, n, text, cls, docs, {}};
+// out[p] = 1 where a piece starts; returns the cross-lane operations of the tile
+// that takes the most.
+extern "C" uint64_t run_rules(int pattern, const uint8_t* text, const char* cls, int n, const uint8_t* docs, uint8_t* out) {
+  Tiles T{pattern, n, text, cls, docs, {}, {}, 0};
+  for (int p = 0; p < n; ++p)
+    if (cls[p] != '.') {
+      auto at = [&](int k) -> uint32_t { return p + k < n ? text[p + k] : 0u; };
+      uint32_t cp;
+      decode_sel(at(0), at(1), at(2), at(3), 4u, cp);
+      T.of[cp] = cls[p];
+    }
   for (int t = 0; t * PT_OWN < n; ++t) one_tile(T, t, out);
+  return T.ops;
 }

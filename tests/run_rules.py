@@ -55,6 +55,7 @@ def rules(own=1984):
         assert r.returncode == 0, r.stderr[-4000:]
         lib = ctypes.CDLL(so)
         assert lib.run_rules_own() == own
+        lib.run_rules.restype = ctypes.c_uint64
         return lib
     finally:
         shutil.rmtree(tmp)
@@ -91,6 +92,11 @@ def class_letter(ch, pattern):
 
 def starts(text, pattern, own=1984, docs=None):
     """Byte offsets of the piece starts of ``text``, or of the documents ``docs`` side by side."""
+    return starts_and_operations(text, pattern, own, docs)[0]
+
+
+def starts_and_operations(text, pattern, own=1984, docs=None):
+    """The same, and the cross-lane operations of the tile that takes the most."""
     parts = [text] if docs is None else docs
     whole = "".join(parts)
     data = whole.encode()
@@ -100,6 +106,7 @@ def starts(text, pattern, own=1984, docs=None):
         flags = np.zeros(len(data) + 1, dtype=np.uint8)
         flags[np.cumsum([0] + [len(d.encode()) for d in docs])] = 1
     out = np.zeros(max(1, len(data)), dtype=np.uint8)
-    rules(own).run_rules(IDS[pattern], data, cls, len(data), None if flags is None else flags.ctypes.data_as(ctypes.c_void_p),
-                         out.ctypes.data_as(ctypes.c_void_p))
-    return np.flatnonzero(out[:len(data)]).tolist()
+    ops = rules(own).run_rules(IDS[pattern], data, cls, len(data),
+                               None if flags is None else flags.ctypes.data_as(ctypes.c_void_p),
+                               out.ctypes.data_as(ctypes.c_void_p))
+    return np.flatnonzero(out[:len(data)]).tolist(), ops

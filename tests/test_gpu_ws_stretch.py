@@ -82,3 +82,23 @@ def test_long_stretch_deep_in_a_large_request(gpu, tail):
     ids = tok.encode(data).tolist()
     assert ids == oracle_ids(data, table, "cl100k")
     assert tok.pretokenize(data).tolist() == piece_byte_starts(text, "cl100k")
+
+
+@pytest.mark.parametrize("pattern,lead,run,tail", [(p, "a\n", "　", t) for p in ("cl100k", "o200k", "deepseek")
+                                                   for t in ("\nx", "x", "")]
+                         + [("o200k", "中", "Я", "я"), ("o200k", "中", "Я", "!"), ("o200k", "中", "Я\U00010400", "")])
+def test_long_multi_byte_runs(gpu, pattern, lead, run, tail):
+    """Runs of characters of two to four bytes that a tile follows past its window: a step takes the characters of
+    1,024 bytes (one character a step took 0.3 s for each of these)."""
+    from conftest import stored_table
+    from paper_2607_29678_amd import Tokenizer
+
+    text = "Word, " * 300 + lead + run * (300_000 // len(run.encode())) + tail
+    data = text.encode("utf-8")
+    with Tokenizer(*stored_table(K), pattern) as tok:
+        starts = tok.pretokenize(data).tolist()
+        t0 = time.perf_counter()
+        tok.pretokenize(data)
+        dt = time.perf_counter() - t0
+    assert starts == piece_byte_starts(text, pattern)
+    assert dt < 0.05, dt
