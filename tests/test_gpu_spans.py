@@ -71,6 +71,30 @@ def test_spans_multibyte_mix(gpu):
         _check(tok, 4, data, what="mix %d" % i)
 
 
+def test_spans_of_long_multibyte_units(gpu):
+    """One unit over several tiles, whose tokens begin and end inside characters: lengths around the 16 bytes that are
+    counted at once and around the window's edge, with and without text after the unit."""
+    from oracle.bpe import MergeTable
+    from paper_2607_29678_amd import Tokenizer
+    from test_gpu_random_merges import _pack, random_merges
+
+    letters = "aé中ж"
+    merges, vocab = random_merges(31, letters, 2500)
+    table = MergeTable(merges, vocab)
+    rng = random.Random(8)
+    with Tokenizer(np.array(merges, dtype=np.int32), *_pack(vocab), "gpt2") as tok:
+        for i, n in enumerate([2016 + o for o in range(-3, 20)] + [4000, 4001, 6100, 9999, 20_003]):
+            unit, size = [], 0
+            while size < n:
+                unit.append(rng.choice(letters))
+                size += len(unit[-1].encode())
+            data = ("a1" * rng.randint(0, 12) + "".join(unit) + rng.choice(["", "1", "1a中", "1" * 40])).encode()
+            ids, spans = tok.encode_spans(data)
+            want = oracle_ids(data, table, "gpt2")
+            assert ids.tolist() == want, i
+            assert [tuple(r) for r in spans.tolist()] == spans_of(want, data, table), (i, n)
+
+
 def test_spans_empty_and_invalid(gpu):
     tok = lib_tokenizer(1)
     ids, spans = tok.encode_spans(b"")
