@@ -357,7 +357,7 @@ def stress_block(ctx):
     sb = stored_shapes().get("C5_batch")
     if sb:
         batch["max_rounds_per_piece"] = sb["max_rounds_per_piece"]
-    # the same request under the walked patterns (its 65,550-byte letter run and its
+    # the same request under the o200k- and DeepSeek-style patterns (its 65,550-byte letter run and its
     # long whitespace and digit runs are single long pieces there too)
     walked = {}
     for pat in ("cl100k", "o200k", "deepseek"):

@@ -47,7 +47,8 @@ __host__ __device__ inline uint32_t bucket_of(uint32_t h, uint32_t nb) { return 
 // The two hashes of a pair are sums of 24-bit products (internal IDs have 21
 // bits, so they cost two full-rate instructions each; a 32-bit product takes
 // four times as long) and the bucket is their top bits: the bucket count is
-// 2^(32 - shift), at a load of 0.4 to 0.8.
+// 2^(32 - shift), at a load of at most 0.8 (half of that where the next power of two
+// is just reached, and less where a small table's pairs crowd a few buckets).
 constexpr uint32_t PAIR_K[4] = {0x9E3779u, 0xC2B2AFu, 0x85EBCBu, 0xD6E8FDu};
 __host__ __device__ inline uint32_t mul24(uint32_t a, uint32_t k) {
 #ifdef __HIP_DEVICE_COMPILE__
@@ -234,7 +235,7 @@ struct Work {
   uint64_t* tile_agg;       // [tiles] output counts for the placement look-back (epoch-tagged)
   uint64_t* tile_cagg;      // [tiles] span export: non-continuation byte counts, same protocol
   uint32_t* stage;          // [n] tokens of incoming units, at the unit's first byte
-  uint32_t* scratch;        // rows of units longer than 64 bytes: 4 * n words, then n / 16 + 8 masks
+  uint32_t* scratch;        // rows of units longer than ROWS_LDS bytes: 4 * n words, then n / 16 + 8 masks
   int32_t* out_spans;       // span export: [T][4] byte begin, byte end, char begin, char end
   int32_t* out_ids;         // output (caller IDs, or piece offsets for the split export)
   uint16_t* out16;          // encode without span export: when set, the IDs go here as 16-bit

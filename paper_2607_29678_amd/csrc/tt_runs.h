@@ -453,9 +453,9 @@ __device__ __forceinline__ uint32_t cl100k_starts(const RunBits& b, uint32_t own
 //     behind its own apostrophe.
 //   - A symbol piece takes the CR/LF after it and then CR/LF and slashes.
 //   - Everything else as in cl100k.
-// The whole set was compared with a matcher that tries the alternatives, on all
-// strings of up to four of 15 characters of every class and on random longer
-// ones.
+// tests/test_run_rules.py compares the whole set with a matcher that tries the
+// alternatives, on all strings of up to four of 15 characters of every class and
+// on random longer ones, in tiles of this size and of 32 to 96 bytes.
 //
 // The context tells the state at the tile's first byte when a character in it
 // resets the rules whatever precedes it (`reset` below), or when it is one run
@@ -612,9 +612,8 @@ __device__ __forceinline__ uint32_t o200k_starts(RunBits b, O2Maps m, uint32_t o
 //     before it; of a run of O's only the last is taken;
 //   - symbols as in cl100k, whitespace as in cl100k.
 // In the CJK/kana set letters and marks, symbols, and the others form runs, of
-// the others again the last joins letters.  Compared with the splitters applied
-// in sequence, on all strings of up to four of 16 characters and on random
-// longer ones.
+// the others again the last joins letters.  Compared in the same way with the
+// splitters applied in sequence.
 struct DsMaps {
   uint32_t AL, L, AP, PS, O, KL, KP, KO;
 };

@@ -30,7 +30,7 @@ from . import _build, _lib
 
 SLOTS, MAX_TILES, PT_OWN = 32, 8192, 1984
 PHASES = ["ticket and tables", "window staging", "decode and classify", "span export: character counts", "piece starts",
-          "units and dispatch", "thread and wave engines", "block engine", "placement look-back", "writing tokens"]
+          "units and dispatch", "wave engines", "block engine", "placement look-back", "writing tokens"]
 DISPATCH = ["unit scan", "unit starts listed", "incoming unit and dictionaries", "length lists", "to the engines",
             "incoming unit's start known (after the listing)"]
 PRED = ["rules on the bitmaps, units", "vocabulary probes", "junction cuts (ignore_merges)", "piece starts, slowest wave"]

@@ -7,7 +7,7 @@ over an alphabet with every class the splitters distinguish (ASCII and other
 letters, marks, numbers, ASCII and other punctuation and symbols, U+0020,
 other whitespace, CR/LF, control characters, and letters, marks, symbols and
 unassigned code points of the CJK/kana ranges), and on long runs placed across
-tile edges, which exercise the walks that start in the previous tile and the
+tile edges, which exercise what a tile takes over from the previous one and the
 grouping of numbers in threes from the head of their run.
 """
 

@@ -6,7 +6,7 @@ Split level and ID level are compared on the seeded texts, on fuzz strings
 over an alphabet with every class the pattern distinguishes (upper, lower and
 title-case letters, Lo and Lm letters, marks, numbers, CR/LF, "/", the
 apostrophe and contraction letters), and on long runs placed across tile
-edges, which exercise the walks that start in the previous tile.
+edges, which exercise what a tile takes over from the previous one.
 """
 
 import random

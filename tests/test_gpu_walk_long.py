@@ -1,10 +1,10 @@
-"""Pieces far longer than a tile under the walked patterns (o200k-style and
-DeepSeek-style), against the oracle at split and ID level.
+"""Pieces far longer than a tile under the o200k-style and DeepSeek-style
+patterns, against the oracle at split and ID level.
 
-A piece of 64K characters covers about 33 tiles.  The tile it starts in walks
-it once; every tile it covers takes it over from the previous tile's last
-piece without walking it again, so the request costs one walk of the piece,
-not one per tile.  The runs cover the alternatives that make long pieces:
+A piece of 64K characters covers about 33 tiles.  Each of them decides its own
+bytes from bitmaps of its window; where its context is one run, it takes what
+the run carries (a lower-case letter in it, a symbol before it, a count) from
+the words that the tiles before it publish.  The runs cover the alternatives that make long pieces:
 lower-case and upper-case letter runs, an upper-case run with Lo letters and
 marks inside (whose split depends on its last Lo letter), letters with marks,
 whitespace with and without CR/LF, symbols, CJK/kana stretches, and digit
@@ -67,10 +67,9 @@ def test_runs_of_64k_characters(gpu, pattern):
             ids = tok.encode(data).tolist()
             assert starts == piece_byte_starts(text, pattern), (pattern, name, off)
             assert ids == oracle_ids(data, table, pattern, memo), (pattern, name, off)
-            # one walk of the piece per request, its part past the window read
-            # 16 bytes at a time, and digit runs marked three bytes a step:
-            # a warm call takes well under 20 ms (a character per step took
-            # about 30 ms for these runs, a piece per step for digits more)
+            # every tile decides its part of the run by itself: a warm call
+            # takes well under 20 ms (reading the run a character per step
+            # took about 30 ms)
             t0 = time.perf_counter()
             tok.encode(data)
             dt = time.perf_counter() - t0

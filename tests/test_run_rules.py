@@ -1,6 +1,7 @@
 """Piece starts by the library's rules (``tt_runs.h``), run on the CPU, against the oracle: what the rules take
 from the 32 bytes before a tile, at the library's tile size and at small ones."""
 
+import itertools
 import random
 
 import pytest
@@ -90,3 +91,73 @@ def test_a_long_run_past_the_window_takes_few_steps(text, pattern):
     got, ops = starts_and_operations(text, pattern)
     assert got == piece_byte_starts(text, pattern)
     assert ops < 400 + 4 * len(text.encode()) // 1024
+
+
+# representatives of every class a pattern tells apart
+ALPHABET = {
+    "gpt2": ["a", "s", "é", "1", "²", " ", "\t", "\n", "'", "!", "…"],
+    "cl100k": ["a", "S", "é", "ſ", "1", "²", " ", "\u3000", "\n", "\r", "'", "!", "…"],
+    "o200k": ["a", "s", "S", "É", "中", "\u0301", "1", " ", "\u3000", "\n", "'", "/", "!", "…", "ſ"],
+    "deepseek": ["a", "é", "\u0301", "1", "٣", " ", "\u3000", "\n", "!", "'", "…", "中", "か", "・", "\u3097", "\x01"],
+}
+
+
+@pytest.mark.parametrize("pattern", sorted(ALPHABET))
+@pytest.mark.parametrize("own,longest", [(OWN, 4), (32, 3)])
+def test_all_short_strings(pattern, own, longest):
+    """Side by side, as documents: the rules themselves, and that none looks across a document's start."""
+    docs = ["".join(t) for n in range(1, longest + 1) for t in itertools.product(ALPHABET[pattern], repeat=n)]
+    got = set(starts(None, pattern, own, docs))
+    at = 0
+    for d in docs:
+        n = len(d.encode())
+        assert [x for x in range(n) if at + x in got] == piece_byte_starts(d, pattern), (pattern, d)
+        at += n
+
+
+MORE = {
+    "gpt2": ["'s", "'ll", "'v", "ſ", "😀", "S", "中", "٣", "\r", "\u3000"],
+    "cl100k": ["'s", "'ll", "'v", "😀", "中", "٣", "\t"],
+    "o200k": ["'s", "'ll", "'S", "'ſ", "é", "ʰ", "\u0e31", "٣", "\t", "\r", "😀"],
+    "deepseek": ["S", "\t", "\r", "😀", "\u3099", "\u0e31", "\u200b"],
+}
+
+
+# units whose runs carry something along, and text that what precedes a run decides on
+CARRY = ["\n", "a", "1", " ", "!", "中", "\u0301", "A", "/"]
+DECIDED = ["  \nx", "\t\r", "\u3000\n", "é", "É", "x", "A", "1", "中", "!", "'s"]
+
+
+def _edge_case(rng, pattern):
+    """A short lead whose last bytes lie around a window's first one, a run up to about a tile's first byte or beyond,
+    and what follows it; sometimes cut into documents near the lead."""
+    parts = ALPHABET[pattern] + MORE[pattern]
+    own, tile = rng.choice((32, 32, 64, 96)), rng.choice((1, 2, 2, 3))
+    edge = own * tile - HALO if own * tile > HALO else own
+    lead = "".join(rng.choice(parts) for _ in range(rng.choice((1, 2, 2, 3))))
+    room = max(0, edge + rng.choice((-1, 0, 1, 1, 2, 3, 4, 5)) - len(lead.encode()))
+    fill = rng.choice(("w ", "w", "1", " ", "\n", "!", "中", "S"))
+    text = fill * (room // len(fill.encode()))
+    text += "w" * (room - len(text.encode())) + lead
+    at = len(text)
+    unit = rng.choice(CARRY if rng.random() < 0.6 else parts) + (rng.choice(parts) if rng.random() < 0.15 else "")
+    end = edge + HALO + rng.choice((-2, -1, 0, 0, 1, 2, 3, own, own + 1, 2 * own))
+    text += unit * max(0, (end - len(text.encode())) // len(unit.encode()) + 1)
+    text += rng.choice(DECIDED) if rng.random() < 0.5 else "".join(rng.choice(parts) for _ in range(rng.choice((1, 2, 3))))
+    if rng.random() < 0.3:
+        text += rng.choice(parts) * rng.randint(20, 80) + "".join(rng.choice(parts) for _ in range(2))
+    docs = None
+    if rng.random() < 0.25:
+        cuts = sorted(min(len(text), max(0, at + rng.choice((-3, -2, -1, 0, 1, 20)))) for _ in range(2))
+        docs = [text[a:b] for a, b in zip([0] + cuts, cuts + [len(text)])]
+    return text, own, docs
+
+
+@pytest.mark.parametrize("pattern", sorted(ALPHABET))
+def test_random_strings_in_small_tiles(pattern):
+    """What the rules take from the context before a tile, from the words of earlier tiles and from beyond the
+    window."""
+    rng = random.Random(41)
+    for _ in range(6000):
+        text, own, docs = _edge_case(rng, pattern)
+        _same(text, pattern, own, docs)
