@@ -6,8 +6,9 @@
 // length on the device and sizes launches from buffer capacity):
 //   tile kernel (pre-tokenize + BPE + placement of every tile's outputs, with
 //   the documents' offsets of a batch and the tokens' spans of a span export)
-// Blocking calls synchronise once (requests past 256 MiB, spans past 4 MiB and
-// the split export twice: for the length, then for the outputs).
+// Blocking calls synchronise once (requests past 256 MiB, spans past 4 MiB, the
+// split export, and batches and spans that find no pinned memory twice: for the
+// length, then for the outputs).
 #include <algorithm>
 #include <cstdint>
 #include <cstdlib>
@@ -456,10 +457,10 @@ constexpr uint64_t PINNED_MAX = 1ull << 28;
 // way out (they promise no output for invalid input), and so do the windows of
 // sessions.  Copying between pageable memory and the device instead, with a
 // second synchronisation for the length, took 254 us for 64 documents of about
-// 16,384 characters (now 138) and 182 us for the spans of 200,000 characters
-// (now 110); a session of 100,000 characters and 12 appends, which allocated
-// pinned buffers of its own and read back room for one token per byte, 938 us
-// (now 577).
+// 16,384 characters (138 this way) and 182 us for the spans of 200,000 characters
+// (110; 97 with the rules on bitmaps); a session of 100,000 characters and 12
+// appends, which allocated pinned buffers of its own and read back room for one
+// token per byte, 938 us (577).
 
 // The IDs of a staged call: where the device puts them and in what width.
 struct StagedIds {

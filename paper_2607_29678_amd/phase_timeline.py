@@ -59,13 +59,15 @@ def timeline(workload, pattern, table, samples=8, reps=2, host=False):
         raise RuntimeError("the loaded library has no phase stamps (not the --phases build)")
     lib.tt_phase_stamps.restype = ctypes.c_int
     lib.tt_phase_stamps.argtypes = [ctypes.c_void_p, ctypes.c_int]
-    k = int(workload.lstrip("Cc"))
+    k, joined = (int(x) for x in (workload.lstrip("Cc") + "x1").split("x")[:2])
     dev = torch.device("cuda:0")
     torch.cuda.set_device(dev)
     stream = torch.cuda.current_stream(dev)
     m, vb, vo = load_table(table)
     tok = Tokenizer(m, vb, vo, pattern)
-    texts = [textgen.latency_sample(k, s).encode() for s in range(samples)]
+    texts = [textgen.latency_sample(k, s).encode() for s in range(max(samples, joined))]
+    if joined > 1:  # one long request
+        texts = [b"".join(texts[:joined])]
     d_in = [torch.from_numpy(np.frombuffer(t, dtype=np.uint8).copy()).to(dev) for t in texts]
     d_out = torch.empty(max(len(t) for t in texts), dtype=torch.int32, device=dev)
     d_len = torch.zeros(1, dtype=torch.int64, device=dev)
@@ -80,13 +82,13 @@ def timeline(workload, pattern, table, samples=8, reps=2, host=False):
         else:
             tok.encode_device(d_in[i], len(texts[i]), d_out, d_len, stream.cuda_stream)
 
-    for i in range(2):
+    for i in range(min(2, len(texts))):
         call(i)
     torch.cuda.synchronize()
     buf = np.zeros(MAX_TILES * SLOTS, dtype=np.uint64)
     phases, disp, pred, crit, spans, late, starts, counts = [], [], [], [], [], [], [], []
     by_cu = {}  # tiles on a compute unit -> times at which such tiles publish their counts
-    tok.set_profiling(samples * reps)
+    tok.set_profiling(len(texts) * reps)
     for _ in range(reps):
         for i, t in enumerate(texts):
             nt = (len(t) + PT_OWN - 1) // PT_OWN
@@ -124,7 +126,7 @@ def timeline(workload, pattern, table, samples=8, reps=2, host=False):
     kernel_us = [x["tile"] * 1e3 for x in tok.stage_times(stream.cuda_stream)]
     tok.set_profiling(0)
     tok.close()
-    out = {"workload": workload, "pattern": pattern, "table": table, "calls": samples * reps,
+    out = {"workload": workload, "pattern": pattern, "table": table, "calls": len(texts) * reps,
            "delivery": "tt_encode from pageable host arrays" if host else "device-resident (tt_encode_device)",
            "kernel_us_p50_hip_events": round(float(np.median(kernel_us)), 2),
            "stamp_span_us_p50": round(float(np.median(spans)), 2),
@@ -142,7 +144,7 @@ def main(argv=None):
     ap = argparse.ArgumentParser(description=__doc__.split("\n\n")[0])
     ap.add_argument("--build", action="store_true", help="compile the phase-stamp build and exit")
     ap.add_argument("--runs", default="C3:gpt2:3,C4:cl100k:4",
-                    help="comma-separated WORKLOAD:PATTERN:TABLE (tables as in workloads.tables)")
+                    help="comma-separated WORKLOAD:PATTERN:TABLE (tables as in workloads.tables; C3x16: 16 samples joined)")
     ap.add_argument("--samples", type=int, default=8)
     ap.add_argument("--host", action="store_true", help="time tt_encode from host arrays instead of device-resident calls")
     args = ap.parse_args(argv)
