@@ -539,9 +539,9 @@ void fill_tile_docs(const int64_t* offsets, int64_t n_docs, uint32_t n_tiles, ui
 
 // One batch over host documents.  Requests past PINNED_MAX are copied between
 // the caller's memory and the device, and so is whatever no pinned memory is to
-// be had for.
+// be had for.  empty: some documents may be empty.
 int batch_staged(tt_tokenizer* h, hipStream_t st, const uint8_t* concat, int64_t len, const int64_t* offsets,
-                 int64_t n_docs, BatchOut* r) {
+                 int64_t n_docs, bool empty, BatchOut* r) {
   if (n_docs > INT32_MAX) return TT_ERR_TOO_LARGE;
   if (hipSetDevice(h->device) != hipSuccess) return TT_ERR_HIP;
   Workspace* s = nullptr;
@@ -565,22 +565,6 @@ int batch_staged(tt_tokenizer* h, hipStream_t st, const uint8_t* concat, int64_t
     words = r->words.data();
     dev = far_words.p;
   }
-  // The device gets one document per position: empty ones share their output offset
-  // with the next, which is filled in afterwards.  (One block has all documents of
-  // its bytes and reads their offsets over the bus: 300,000 empty ones between two
-  // others took 1.70 ms, now 0.37; at the end 1.52, now 0.37.)
-  int64_t* doc = reinterpret_cast<int64_t*>(words);
-  int64_t n_dev = 0;
-  for (int64_t j = 0; j <= n_docs; ++j) {
-    doc[n_dev] = offsets[j];
-    n_dev += j < n_docs && offsets[j + 1] != offsets[j];
-  }
-  fill_tile_docs(doc, n_dev, n_tiles, reinterpret_cast<uint2*>(words + nd));
-  int64_t* out = reinterpret_cast<int64_t*>(words + nd + n_tiles);
-  out[n_dev] = 0;
-  if (far_words.p && hipMemcpyAsync(dev, words, 8 * n_words, hipMemcpyHostToDevice, st) != hipSuccess) return TT_ERR_HIP;
-  const BatchDocs docs{reinterpret_cast<const int64_t*>(dev), (int32_t)n_dev, reinterpret_cast<const uint2*>(dev + nd),
-                       reinterpret_cast<int64_t*>(dev + nd + n_tiles)};
   bool staged = (uint64_t)len <= PINNED_MAX;
   if (staged) {
     rc = reserve_pinned(s, (uint64_t)len);
@@ -597,6 +581,24 @@ int batch_staged(tt_tokenizer* h, hipStream_t st, const uint8_t* concat, int64_t
   } else if (hipMemcpyAsync(s->d_in, concat, (size_t)len, hipMemcpyHostToDevice, st) != hipSuccess) {
     return TT_ERR_HIP;
   }
+  // The device gets one document per position: empty ones share their output offset
+  // with the next, which is filled in afterwards.  (One block has all documents of
+  // its bytes and reads their offsets over the bus: 300,000 empty ones between two
+  // others took 1.70 ms, now 0.40; at the end 1.52, now 0.39.)
+  int64_t* doc = reinterpret_cast<int64_t*>(words);
+  int64_t n_dev = empty ? 0 : n_docs;
+  if (!empty) std::memcpy(doc, offsets, 8 * nd);
+  else
+    for (int64_t j = 0; j <= n_docs; ++j) {
+      doc[n_dev] = offsets[j];
+      n_dev += j < n_docs && offsets[j + 1] != offsets[j];
+    }
+  fill_tile_docs(empty ? doc : offsets, n_dev, n_tiles, reinterpret_cast<uint2*>(words + nd));
+  int64_t* out = reinterpret_cast<int64_t*>(words + nd + n_tiles);
+  out[n_dev] = 0;
+  if (far_words.p && hipMemcpyAsync(dev, words, 8 * n_words, hipMemcpyHostToDevice, st) != hipSuccess) return TT_ERR_HIP;
+  const BatchDocs docs{reinterpret_cast<const int64_t*>(dev), (int32_t)n_dev, reinterpret_cast<const uint2*>(dev + nd),
+                       reinterpret_cast<int64_t*>(dev + nd + n_tiles)};
   rc = run_chain(h, s, src, (uint32_t)len, r->ids.wide, length, st, 1, nullptr, r->ids.lo16, r->ids.hi8, &docs);
   if (rc) return rc;
   if (far_words.p && hipMemcpyAsync(out, docs.out, 8 * ((size_t)n_dev + 1), hipMemcpyDeviceToHost, st) != hipSuccess)
@@ -1200,7 +1202,7 @@ int tt_encode(tt_tokenizer* h, const uint8_t* utf8, int64_t len, int32_t* out_id
     added_documents(h->added, utf8, 0, len, docs, lits);
     if (!lits.empty()) {
       BatchOut r;
-      int rc = batch_staged(h, st, utf8, len, docs.data(), (int64_t)docs.size() - 1, &r);
+      int rc = batch_staged(h, st, utf8, len, docs.data(), (int64_t)docs.size() - 1, true, &r);
       if (rc) return rc;
       const int64_t* od = r.offsets;
       int64_t T = 0;
@@ -1309,8 +1311,12 @@ int tt_encode_batch(tt_tokenizer* h, const uint8_t* concat, const int64_t* doc_o
                     int32_t* out_ids, int64_t* out_doc_offsets, void* stream) {
   if (!h || !doc_offsets || !out_doc_offsets) return TT_ERR_NULL_ARG;
   if (n_docs < 0 || doc_offsets[0] != 0) return TT_ERR_BAD_ARG;
+  bool empty = false;
   for (int32_t j = 0; j < n_docs; ++j)
-    if (doc_offsets[j + 1] < doc_offsets[j]) return TT_ERR_BAD_ARG;
+    if (doc_offsets[j + 1] <= doc_offsets[j]) {
+      if (doc_offsets[j + 1] < doc_offsets[j]) return TT_ERR_BAD_ARG;
+      empty = true;
+    }
   const int64_t len = doc_offsets[n_docs];
   if (len > TT_MAX_BYTES) return TT_ERR_TOO_LARGE;
   if (len > 0 && (!concat || !out_ids)) return TT_ERR_NULL_ARG;
@@ -1332,7 +1338,7 @@ int tt_encode_batch(tt_tokenizer* h, const uint8_t* concat, const int64_t* doc_o
     first_doc[(size_t)n_docs] = (int64_t)docs.size() - 1;
     first_lit[(size_t)n_docs] = (int64_t)lits.size();
     BatchOut r;
-    int rc = batch_staged(h, st, concat, len, docs.data(), (int64_t)docs.size() - 1, &r);
+    int rc = batch_staged(h, st, concat, len, docs.data(), (int64_t)docs.size() - 1, true, &r);
     if (rc) return rc;
     const int64_t* od = r.offsets;
     int64_t T = 0;
@@ -1352,7 +1358,7 @@ int tt_encode_batch(tt_tokenizer* h, const uint8_t* concat, const int64_t* doc_o
     return TT_OK;
   }
   BatchOut r;
-  int rc = batch_staged(h, st, concat, len, doc_offsets, n_docs, &r);
+  int rc = batch_staged(h, st, concat, len, doc_offsets, n_docs, empty, &r);
   if (rc) return rc;
   r.ids.take(out_ids, 0, (size_t)r.offsets[n_docs]);
   std::memcpy(out_doc_offsets, r.offsets, 8 * ((size_t)n_docs + 1));

@@ -169,3 +169,48 @@ def test_empty_documents_stay_on_the_host(fake, docs, pinned):
         with pytest.raises(TokTierError) as e:
             tok.encode_batch(docs + [b"", b"\xff", b""])
         assert e.value.status == -5
+
+
+def _pairs_of_results(vocab, n):
+    for a in range(n):
+        for b in range(n):
+            yield a, b
+    first = len(vocab)
+    for i in range(256, min(first, 256 + 8 * n)):
+        for j in range(256, min(first, 256 + 8 * n)):
+            yield i, j
+
+
+def _letters_then(vocab, n):
+    for a in range(97, 97 + n):
+        for b in range(97, 97 + n):
+            yield a, b
+    for r in range(256, len(vocab)):
+        for b in range(97, 97 + n):
+            yield r, b
+
+
+def _one_letter(vocab, n):
+    yield 97, 97
+    for _ in range(n - 1):
+        yield len(vocab) - 1, 97
+
+
+@pytest.mark.parametrize("pairs,n", [(_letters_then, 2), (_letters_then, 26), (_pairs_of_results, 8), (_pairs_of_results, 32),
+                                     (_pairs_of_results, 256), (_one_letter, 1500)])
+def test_merge_tables_of_neighbouring_pairs(fake, pairs, n):
+    """The merge table's hashes are sums of products: lists whose pairs are neighbours in both operands, which such
+    hashes put side by side, are accepted too, in tables of a few times the load of others."""
+    vocab, merges, seen = [bytes([b]) for b in range(256)], [], set()
+    for a, b in pairs(vocab, n):
+        if (a, b) not in seen:
+            seen.add((a, b))
+            merges.append((a, b, len(vocab)))
+            vocab.append(vocab[a] + vocab[b])
+            if len(merges) >= 80_000:
+                break
+    offsets = np.concatenate([[0], np.cumsum([len(v) for v in vocab])]).astype(np.int64)
+    before = fake.fake_used(0)
+    with Tokenizer(np.array(merges, dtype=np.int32), np.frombuffer(b"".join(vocab), dtype=np.uint8), offsets, "gpt2"):
+        # (besides the merge table: the byte pairs and junctions, the dictionaries, 8 bytes per ID)
+        assert fake.fake_used(0) - before < (1 << 20) + (8 + 4 * 16 + 4 * 32) * len(merges)
