@@ -124,8 +124,7 @@ def _spans(data):
 
 # no pinned memory but the length word; room for the documents' words, not for the IDs; room for the staged
 # IDs, not for the spans; all
-@pytest.mark.parametrize("pinned", [8, 64 << 10, 3 << 20, ALL])
-@pytest.mark.parametrize("bits", [16, 24, 32])
+@pytest.mark.parametrize("bits,pinned", [(b, p) for b in (16, 24) for p in (8, 64 << 10, 3 << 20, ALL)] + [(32, 8), (32, ALL)])
 def test_calls_without_pinned_memory(fake, bits, pinned):
     """Batches, span export and sessions that find no pinned memory give the same results through copies."""
     docs, data = _docs(300), TEXT.encode()
